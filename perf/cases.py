@@ -37,7 +37,7 @@ def listed():
         {"name": "decode_61", "kind": "linear", "M": 61, "d_out": 11008, "d_in": 4096, "dtype": "bf16", "scales": "row"},
         # decode of independent layers in one launch: the 14 projections of two blocks, one with
         # row and one with column scales
-        {"name": "decode_stack", "kind": "stack", "M": 1, "blocks": 2, "dtype": "f16"},
+        {"name": "decode_stack", "kind": "stack", "M": 1, "layers": 14, "dtype": "f16"},
         # sixteen requests for sixteen fine-tunes of one base
         {"name": "variants_16", "kind": "variants", "R": 16, "d_out": 4096, "d_in": 4096, "dtype": "f16", "scales": "row"},
         # a short prompt of odd length
@@ -57,6 +57,8 @@ def listed():
 
 # the most arithmetic that one call of the listed cases does
 MAX_FLOPS = 2 * 2048 * 11008 * 4096
+# the weights of one block
+BLOCK_WEIGHTS = sum(d_out * d_in for _, d_out, d_in in synth.STACK_BLOCK)
 
 
 def _log(rng, lo, hi):
@@ -84,8 +86,7 @@ def draw(rng):
             scales = rng.choice(["scalar"] + ["g%d" % g for g in fits])
         return {"kind": "linear", "M": M, "d_out": d_out, "d_in": d_in, "dtype": dtype, "scales": scales}
     if kind == "stack":
-        M = rng.choice((1, 1, 2, 3, 4, 8))
-        return {"kind": "stack", "M": M, "blocks": rng.choice((1, 2)) if M == 1 else 1, "dtype": dtype}
+        return {"kind": "stack", "M": rng.choice((1, 1, 1, 2, 3, 4, 6, 8)), "layers": rng.randint(2, 14), "dtype": dtype}
     if kind == "variants":
         return {"kind": "variants", "R": int(_log(rng, 2, 17)), "d_out": d_out, "d_in": max(128, d_in // 128 * 128), "dtype": dtype,
                 "scales": rng.choice(("row", "col", "mixed"))}
@@ -93,11 +94,9 @@ def draw(rng):
         d_out = max(32, d_out // 32 * 32)
         M = min(int(_log(rng, 64, 4097)), MAX_FLOPS // (2 * d_out * d_in))
         return {"kind": "grad", "M": M, "d_out": d_out, "d_in": d_in, "dtype": dtype, "scales": rng.choice(("row", "col"))}
-    layers = rng.choice((1, 1, 7))
-    if layers == 7:
-        d_out = d_in = 0
+    layers = max(1, min(rng.choice((1, 1, rng.randint(2, 12))), BLOCK_WEIGHTS // (d_out * d_in)))
     if kind == "pack":
-        scales = "both" if layers == 7 else rng.choice(("both", "both", "row", "col", "g128" if d_in % 128 == 0 else "both", "scalar"))
+        scales = "both" if layers > 1 else rng.choice(("both", "both", "row", "col", "g128" if d_in % 128 == 0 else "both", "scalar"))
     else:
         scales = rng.choice(("row", "col"))
     return {"kind": kind, "layers": layers, "d_out": d_out, "d_in": d_in, "dtype": dtype, "scales": scales}
@@ -149,9 +148,17 @@ def _group(case):
 
 
 def _layers(case):
-    if case["layers"] == 1:
-        return [(case["d_out"], case["d_in"])]
+    """(d_out, d_in) of each layer: the block's own, or several of one size."""
+    if case["d_out"]:
+        return [(case["d_out"], case["d_in"])] * case["layers"]
     return [(d_out, d_in) for _, d_out, d_in in synth.STACK_BLOCK]
+
+
+def _stack(case):
+    """(scales, d_out, d_in) of each layer of a stack: block after block, the first with row scales,
+    the next with column scales."""
+    per = len(synth.STACK_BLOCK)
+    return [(("row", "col")[k // per % 2], *synth.STACK_BLOCK[k % per][1:]) for k in range(case["layers"])]
 
 
 def prepare(case, seed):
@@ -170,11 +177,9 @@ def prepare(case, seed):
         st["Y"] = torch.empty((M, d_out), dtype=DTYPES[dtype], device=DEV) if M <= DECODE_MAX_TOKENS else None
     elif kind == "stack":
         items = []
-        for b in range(case["blocks"]):
-            scales = "row" if b % 2 == 0 else "col"
-            for _, d_out, d_in in synth.STACK_BLOCK:
-                X, W_b = _tokens(case["M"], d_in, dtype, seeds), _weights(d_out, d_in, dtype, seeds)
-                items.append((X, W_b, *_delta(d_out, d_in, scales, seeds), AXES[scales]))
+        for scales, d_out, d_in in _stack(case):
+            X, W_b = _tokens(case["M"], d_in, dtype, seeds), _weights(d_out, d_in, dtype, seeds)
+            items.append((X, W_b, *_delta(d_out, d_in, scales, seeds), AXES[scales]))
         st["plan"] = pd.pdelta_linear_batch_plan(items)
     elif kind == "variants":
         R, d_out, d_in = case["R"], case["d_out"], case["d_in"]
@@ -255,10 +260,9 @@ def work(case):
         return {"bytes": 2 * d_out * d_in + sets * (d_out * d_in // 8 + 2 * v_len) + 2 * M * (d_in + d_out), "flops": 2 * M * d_out * d_in}
     if kind == "stack":
         nbytes = flops = 0
-        for b in range(case["blocks"]):
-            for _, d_out, d_in in synth.STACK_BLOCK:
-                nbytes += 2 * d_out * d_in + d_out * d_in // 8 + 2 * (d_out if b % 2 == 0 else d_in) + 2 * case["M"] * (d_in + d_out)
-                flops += 2 * case["M"] * d_out * d_in
+        for scales, d_out, d_in in _stack(case):
+            nbytes += 2 * d_out * d_in + d_out * d_in // 8 + 2 * (d_out if scales == "row" else d_in) + 2 * case["M"] * (d_in + d_out)
+            flops += 2 * case["M"] * d_out * d_in
         return {"bytes": nbytes, "flops": flops}
     if kind == "grad":
         M, d_out, d_in = case["M"], case["d_out"], case["d_in"]
@@ -291,3 +295,58 @@ def tolerance(case):
     if kind == "linear" and case["M"] > DECODE_MAX_TOKENS:
         return {"rel": 1.2e-3, "max": 5e-3}
     return {"rel": 8e-4, "max": 2e-3}
+
+
+# ---- the same results in 64 bits ----------------------------------------------------------------
+
+def _signs64(B, d_in):
+    bits = (B.unsqueeze(-1) >> torch.arange(32, dtype=torch.int32, device=B.device)) & 1
+    return (bits.reshape(B.shape[0], d_in) * 2 - 1).double()
+
+
+def _merged64(W_b, B, v, scales, group=0):
+    signs, v = _signs64(B, W_b.shape[1]), v.double()
+    if scales == "row":
+        v = v.unsqueeze(1)
+    elif scales != "col":
+        v = v.repeat_interleave(group, dim=1)
+    return signs.mul_(v).add_(W_b.double())
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits; the sign words have no such value."""
+    st, kind, scales = prepare(case, seed), case["kind"], case.get("scales")
+    if kind == "linear":
+        group = 0 if scales in AXES else _group(case)[0]
+        return st["X"].double() @ _merged64(st["W_b"], st["B"], st["v"], scales, group).T
+    if kind == "stack":
+        out = []
+        for (scales, _, _), (X, W_b, B, v, _) in zip(_stack(case), st["plan"].tensors):
+            out.append(X.double() @ _merged64(W_b, B, v, scales).T)
+        return out
+    if kind == "variants":
+        # the same draws as in prepare(), which hands the deltas to the library
+        seeds, d_out, d_in = _seeds(seed), case["d_out"], case["d_in"]
+        _tokens(1, 1, case["dtype"], seeds), _weights(1, 1, case["dtype"], seeds)
+        rows = []
+        for r in range(case["R"]):
+            axis = ("row", "col")[r % 2] if scales == "mixed" else scales
+            rows.append(st["X"][r:r + 1].double() @ _merged64(st["W_b"], *_delta(d_out, d_in, axis, seeds), axis).T)
+        return torch.cat(rows)
+    if kind == "grad":
+        X, dY, signs = st["X"].double(), st["dY"].double(), _signs64(st["B"], case["d_in"])
+        return (dY * (X @ signs.T)).sum(0) if scales == "row" else (X * (dY @ signs)).sum(0)
+    if kind == "pack":
+        out = []
+        for W_f, W_b in st["pairs"]:
+            size = (W_f.double() - W_b.double()).abs_()
+            if scales in ("both", "row", "col"):
+                means = [size.mean(1) if scales != "col" else None, size.mean(0) if scales != "row" else None]
+                out.append([None] + [m for m in means if m is not None])
+            elif scales == "scalar":
+                out.append([None, size.mean().reshape(1, 1)])
+            else:
+                out.append([None, size.reshape(size.shape[0], -1, _group(case)[0]).mean(2)])
+        return out if st["plan"] is not None else out[0]
+    out = [_merged64(W_b, B, v, scales) for W_b, B, v, _, _ in st["items"]]
+    return out if st["plan"] is not None else out[0]
