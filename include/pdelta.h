@@ -161,6 +161,23 @@ int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
                       int x_dtype, int y_dtype, void* stream);
 
 /*
+ * The same two layers with a workspace (axis: PDELTA_ROW or PDELTA_COL).  Some prefill shapes (M > 64)
+ * leave part of the chip without a tile; with a workspace those tiles are computed in several parts
+ * of d_in whose fp32 sums are added in the order of d_in (reproducible; the sums of one output differ
+ * from the ones without a workspace only in where they are cut).  pdelta_linear_workspace_bytes: the
+ * bytes such a call uses, at most 64 MiB, 0 when none is used (always for M <= 64).  workspace may be
+ * NULL with workspace_bytes = 0: exactly pdelta_linear_row / _col.  Otherwise PDELTA_EWORKSPACE if it
+ * is smaller than that, PDELTA_EALIGN unless 16-byte aligned, PDELTA_EINVAL if it overlaps a tensor of
+ * the call.  Its contents on entry are ignored; it belongs to the call until the call's work on the
+ * stream has finished.
+ */
+size_t pdelta_linear_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype);
+
+int pdelta_linear_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
+                     int axis, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype,
+                     int y_dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Merge the delta into the weights (Eq. 1; the paper's deployed path adds all residual terms
  * once, Limitations section, and applies a saved delta module by module, algorithm "Model-wide
  * application from a saved delta file"):
@@ -351,6 +368,12 @@ int pdelta_pack_group(const void* W_f, const void* W_b, int64_t d_out, int64_t d
 int pdelta_linear_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                         int64_t group, int shared_rows, void* Y, int64_t M, int64_t d_out,
                         int64_t d_in, int x_dtype, int y_dtype, void* stream);
+
+/* With the workspace of pdelta_linear_ws (same size, same rules). */
+int pdelta_linear_group_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
+                           int64_t group, int shared_rows, void* Y, int64_t M, int64_t d_out,
+                           int64_t d_in, int x_dtype, int y_dtype, void* workspace,
+                           size_t workspace_bytes, void* stream);
 
 int pdelta_patch_group(const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
                        int shared_rows, void* W_out, int64_t d_out, int64_t d_in, int w_dtype,

@@ -70,6 +70,10 @@ def lib() -> ctypes.CDLL:
             f = getattr(L, name)
             f.restype = i32
             f.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, i32, i32, vp]
+        L.pdelta_linear_workspace_bytes.restype = sz
+        L.pdelta_linear_workspace_bytes.argtypes = [i64, i64, i64, i32]
+        L.pdelta_linear_ws.restype = i32
+        L.pdelta_linear_ws.argtypes = [vp, vp, vp, vp, i32, vp, i64, i64, i64, i32, i32, vp, sz, vp]
         L.pdelta_patch.restype = i32
         L.pdelta_patch.argtypes = [vp, vp, vp, i32, vp, i64, i64, i32, vp]
         L.pdelta_linear_batch_plan.restype = i32
@@ -95,6 +99,8 @@ def lib() -> ctypes.CDLL:
         L.pdelta_pack_group.argtypes = [vp, vp, i64, i64, i32, i64, i32, vp, vp, vp, sz, vp]
         L.pdelta_linear_group.restype = i32
         L.pdelta_linear_group.argtypes = [vp, vp, vp, vp, i64, i32, vp, i64, i64, i64, i32, i32, vp]
+        L.pdelta_linear_group_ws.restype = i32
+        L.pdelta_linear_group_ws.argtypes = [vp, vp, vp, vp, i64, i32, vp, i64, i64, i64, i32, i32, vp, sz, vp]
         L.pdelta_patch_group.restype = i32
         L.pdelta_patch_group.argtypes = [vp, vp, vp, i64, i32, vp, i64, i64, i32, vp]
         L.pdelta_probe_read_stream.restype = i32
@@ -189,6 +195,21 @@ def pdelta_pack_noalloc(W_f: torch.Tensor, W_b: torch.Tensor, out):
 _DTYPE_CODE = {torch.float16: F16, torch.bfloat16: BF16, torch.float32: F32}
 
 
+_DECODE_MAX_TOKENS = 64
+
+
+def _prefill_workspace(M: int, d_out: int, d_in: int, x: torch.Tensor):
+    """Workspace of a prefill call, or None when the call uses none or the memory for it is not there
+    (the layer is then computed without)."""
+    need = lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[x.dtype])
+    if need == 0:
+        return None
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=x.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
     M, d_in = X.shape
     d_out = W_b.shape[0]
@@ -196,6 +217,15 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
         raise ValueError("X and W_b must agree in d_in and dtype")
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
+    if M > _DECODE_MAX_TOKENS and X.is_cuda:
+        ws = _prefill_workspace(M, d_out, d_in, X)
+        if ws is not None:
+            rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+                                        ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
+                                        _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], ws.data_ptr(), ws.numel(),
+                                        _stream())
+            _check(rc, fn_name)
+            return out
     fn = getattr(_lib, fn_name) if _lib is not None else getattr(lib(), fn_name)
     rc = fn(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"), _dev(out, "Y"),
             M, d_out, d_in, _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], _stream())
@@ -466,9 +496,12 @@ def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=Non
         raise ValueError("X and W_b must agree in d_in and dtype")
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
-    rc = lib().pdelta_linear_group(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
-                                   group, shared, _dev(out, "Y") or None, M, d_out, d_in, dtype_code(X.dtype),
-                                   dtype_code(out.dtype), _stream())
+    x_dtype = dtype_code(X.dtype)
+    ws = _prefill_workspace(M, d_out, d_in, X) if M > _DECODE_MAX_TOKENS and X.is_cuda else None
+    rc = lib().pdelta_linear_group_ws(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+                                      group, shared, _dev(out, "Y") or None, M, d_out, d_in, x_dtype,
+                                      dtype_code(out.dtype), ws.data_ptr() if ws is not None else None,
+                                      ws.numel() if ws is not None else 0, _stream())
     _check(rc, "pdelta_linear_group")
     return out
 

@@ -80,12 +80,34 @@ int check_dims(int64_t d_out, int64_t d_in)
 int linear_check(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                  void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype, int axis);
 
+// Checks of the optional workspace of the prefill path (no launch): none at all, or one that is large
+// enough, aligned and apart from the layer's tensors.
+int linear_workspace_check(const void* X, const void* W_b, const void* B_packed, const void* v, size_t v_bytes,
+                           const void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
+                           const void* workspace, size_t workspace_bytes)
+{
+    if (workspace == nullptr) return workspace_bytes == 0 ? PDELTA_OK : PDELTA_EINVAL;
+    if (misaligned(workspace)) return PDELTA_EALIGN;
+    if (workspace_bytes < (M > kSkinnyMaxM ? linear_gemm_workspace_bytes(M, d_out, d_in, x_dtype) : 0)) return PDELTA_EWORKSPACE;
+    if (M == 0 || workspace_bytes == 0) return PDELTA_OK;
+    if (overlaps(workspace, workspace_bytes, X, (size_t)M * d_in * 2) ||
+        overlaps(workspace, workspace_bytes, W_b, (size_t)d_out * d_in * 2) ||
+        overlaps(workspace, workspace_bytes, B_packed, (size_t)d_out * d_in / 8) ||
+        overlaps(workspace, workspace_bytes, v, v_bytes) ||
+        overlaps(workspace, workspace_bytes, Y, (size_t)M * d_out * (y_dtype == PDELTA_F32 ? 4 : 2)))
+        return PDELTA_EINVAL;
+    return PDELTA_OK;
+}
+
 int linear_common(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                   void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
-                  int axis, void* stream)
+                  int axis, void* workspace, size_t workspace_bytes, void* stream)
 {
     const TuneScope tune_scope;
     if (const int rc = linear_check(X, W_b, B_packed, v, Y, M, d_out, d_in, x_dtype, y_dtype, axis))
+        return rc;
+    if (const int rc = linear_workspace_check(X, W_b, B_packed, v, (size_t)(axis == PDELTA_ROW ? d_out : d_in) * 2, Y, M,
+                                              d_out, d_in, x_dtype, y_dtype, workspace, workspace_bytes))
         return rc;
     if (M == 0) return PDELTA_OK;
     hipStream_t s = (hipStream_t)stream;
@@ -93,7 +115,7 @@ int linear_common(const void* X, const void* W_b, const uint32_t* B_packed, cons
                        ? pdelta::launch_linear_skinny(x_dtype, y_dtype, axis, X, W_b, B_packed, v, Y, M,
                                                       d_out, d_in, s)
                        : pdelta::launch_linear_gemm(x_dtype, y_dtype, axis, X, W_b, B_packed, v, Y, M,
-                                                    d_out, d_in, s);
+                                                    d_out, d_in, workspace, workspace_bytes, s);
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 
@@ -265,7 +287,7 @@ int pdelta_linear_row(const void* X, const void* W_b, const uint32_t* B_packed,
                       int x_dtype, int y_dtype, void* stream)
 {
     return pdelta::linear_common(X, W_b, B_packed, v_row, Y, M, d_out, d_in, x_dtype, y_dtype,
-                                 PDELTA_ROW, stream);
+                                 PDELTA_ROW, nullptr, 0, stream);
 }
 
 int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
@@ -273,7 +295,23 @@ int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
                       int x_dtype, int y_dtype, void* stream)
 {
     return pdelta::linear_common(X, W_b, B_packed, v_col, Y, M, d_out, d_in, x_dtype, y_dtype,
-                                 PDELTA_COL, stream);
+                                 PDELTA_COL, nullptr, 0, stream);
+}
+
+size_t pdelta_linear_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype)
+{
+    using namespace pdelta;
+    const TuneScope tune_scope;
+    if (M <= kSkinnyMaxM || M > kMaxTokens || check_dims(d_out, d_in) != PDELTA_OK || !is_w_dtype(x_dtype)) return 0;
+    return linear_gemm_workspace_bytes(M, d_out, d_in, x_dtype);
+}
+
+int pdelta_linear_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int axis, void* Y,
+                     int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype, void* workspace,
+                     size_t workspace_bytes, void* stream)
+{
+    return pdelta::linear_common(X, W_b, B_packed, v, Y, M, d_out, d_in, x_dtype, y_dtype, axis, workspace, workspace_bytes,
+                                 stream);
 }
 
 static int patch_check(const void* W_b, const uint32_t* B_packed, const uint16_t* v, int axis,
@@ -379,7 +417,7 @@ int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* lay
             rc = M <= kSkinnyMaxM ? launch_linear_skinny(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
                                                          L.v, L.Y, M, L.d_out, L.d_in, s)
                                   : launch_linear_gemm(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
-                                                       L.v, L.Y, M, L.d_out, L.d_in, s);
+                                                       L.v, L.Y, M, L.d_out, L.d_in, nullptr, 0, s);
         }
     }
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
@@ -521,9 +559,9 @@ int pdelta_pack_group(const void* W_f, const void* W_b, int64_t d_out, int64_t d
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 
-int pdelta_linear_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
-                        int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
-                        void* stream)
+int pdelta_linear_group_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
+                           int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
+                           void* workspace, size_t workspace_bytes, void* stream)
 {
     using namespace pdelta;
     const TuneScope tune_scope;
@@ -540,12 +578,23 @@ int pdelta_linear_group(const void* X, const void* W_b, const uint32_t* B_packed
     if (overlaps(Y, y_bytes, X, (size_t)M * d_in * 2) || overlaps(Y, y_bytes, W_b, (size_t)d_out * d_in * 2) ||
         overlaps(Y, y_bytes, B_packed, (size_t)d_out * d_in / 8) || overlaps(Y, y_bytes, v, v_bytes))
         return PDELTA_EINVAL;
+    if (const int rc = linear_workspace_check(X, W_b, B_packed, v, v_bytes, Y, M, d_out, d_in, x_dtype, y_dtype, workspace,
+                                              workspace_bytes))
+        return rc;
     hipStream_t s = (hipStream_t)stream;
     const int rc = M <= kSkinnyMaxM ? launch_linear_skinny_group(x_dtype, y_dtype, X, W_b, B_packed, v, Y, M, d_out,
                                                                  d_in, v_stride, g_shift, s)
                                     : launch_linear_gemm_group(x_dtype, y_dtype, X, W_b, B_packed, v, Y, M, d_out,
-                                                               d_in, v_stride, g_shift, s);
+                                                               d_in, v_stride, g_shift, workspace, workspace_bytes, s);
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
+}
+
+int pdelta_linear_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
+                        int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
+                        void* stream)
+{
+    return pdelta_linear_group_ws(X, W_b, B_packed, v, group, shared_rows, Y, M, d_out, d_in, x_dtype, y_dtype, nullptr, 0,
+                                  stream);
 }
 
 int pdelta_patch_group(const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group, int shared_rows,

@@ -27,90 +27,10 @@
 // inside that XCD's 4 MB L2.
 #include <type_traits>
 
-#include "pdelta_device.h"
+#include "pdelta_gemm_tile.h"
 #include "pdelta_host.h"
 
 namespace pdelta {
-
-constexpr int kGemmBN = 128, kGemmBK = 64;
-constexpr int kGemmLDK = kGemmBK + 8;   // padded LDS row in halves (144 bytes)
-constexpr int kXcds = 8;
-
-__device__ __forceinline__ uint32_t bf16pair_to_f16pair(uint32_t d) {
-    const float lo = __builtin_bit_cast(float, d << 16);
-    const float hi = __builtin_bit_cast(float, d & 0xFFFF0000u);
-    return as_u32(__builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(lo, hi)));
-}
-
-template <int XDT>
-__device__ __forceinline__ uint4v to_f16x8(uint4v a) {
-    if constexpr (XDT == kBF16) {
-        uint4v r;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const uint32_t ap = a[p];
-            r[p] = bf16pair_to_f16pair(ap);
-        }
-        return r;
-    } else {
-        return a;
-    }
-}
-
-// Eight fp16 weights and eight "negate" bits (bit e set: element e gets -|v|, clear: +|v|) with
-// the packed magnitudes |v| of elements 2p (low half) and 2p+1 (high half) in vabs[p].
-// Row mode: |v| is one value per row and the sign of v is folded into the bits by the caller.
-__device__ __forceinline__ uint4v add_signed_scale(uint4v w, uint32_t negbits, uint4v vabs) {
-    uint4v r;
-    negbits &= 0xFFu;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        // bit 2p -> position 15, bit 2p+1 -> position 31; everything else is masked by the insert
-        const uint32_t spread = (negbits << (30 - 2 * p)) | (negbits << (15 - 2 * p));
-        const uint32_t va = vabs[p], wp = w[p];
-        const uint32_t sv = (spread & 0x80008000u) | (va & 0x7FFF7FFFu);        // v_bfi_b32
-        r[p] = as_u32(as_half2(wp) + as_half2(sv));                              // v_pk_add_f16
-    }
-    return r;
-}
-
-// Epilogue of the 64 x 64 wave tile for 16-bit outputs: the accumulators go through a wave-private
-// LDS region (32 rows x 64 columns at a time, rows padded to 144 bytes) and leave as 16-byte
-// stores, eight lanes per 128-byte line of Y, instead of 64 two-byte store instructions per
-// accumulator tile (measured 2-3 % of the run time).  `region` holds 32 * kGemmLDK halves of this wave.
-// Returns false (nothing stored) when the tile is not fully inside Y or rows of Y are not
-// 16-byte aligned; the caller then stores element by element.
-template <int FM>
-__device__ __forceinline__ bool store_tile_16bit(const float16v (&acc)[FM][2], uint16_t* region, void* Y,
-                                                 int y_dtype, int tok0, int o0, int M, int d_out, int lane)
-{
-    if (y_dtype == kF32 || (d_out & 7) != 0 || o0 + 64 > d_out || tok0 + FM * 32 > M) return false;   // wave-uniform
-    uint16_t* Yh = (uint16_t*)Y;
-#pragma unroll
-    for (int f = 0; f < FM; ++f) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), col = h * 32 + (lane & 31);
-                const float val = acc[f][h][r];
-                region[row * kGemmLDK + col] =
-                    (uint16_t)(y_dtype == kBF16 ? f32_to_bf16_bits(val) : f32_to_f16_bits(val));
-            }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int row = it * 8 + (lane >> 3), chunk = lane & 7;
-            const uint4v vals = *(const uint4v*)(region + row * kGemmLDK + chunk * 8);
-            *(uint4v*)(Yh + (int64_t)(tok0 + f * 32 + row) * d_out + o0 + chunk * 8) = vals;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-    return true;
-}
 
 // WM x 2 waves; a wave owns (BM / WM) tokens x 64 output rows.
 template <int XDT, int AXIS, int BM, int WM>
@@ -782,8 +702,13 @@ static int launch_gemm(const void* X, const void* W_b, const uint32_t* B_packed,
 template <int XDT, int AXIS>
 static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                           void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
-                          hipStream_t stream)
+                          void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
+    // 256 x 256 tiles with direct loads (and split tiles where there is a workspace) when they are
+    // expected to be faster; see linear_gemm_big_split.
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, workspace_bytes);
+    if (sp.parts > 0)
+        return launch_linear_gemm_big(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, 0, 31, workspace, sp, stream);
     // Under-filled grids (at most 128 tiles of 256 x 128, i.e. a few hundred tokens): the
     // small-tile kernel is 2-3x faster there; from about 1000 tokens on the big tiles win.
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
@@ -806,8 +731,13 @@ static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_pack
 template <int XDT>
 static int launch_gemm_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y,
                              int64_t M, int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift,
-                             hipStream_t stream)
+                             void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
+    // 256 x 256 tiles with direct loads (and split tiles where there is a workspace) when they are
+    // expected to be faster; see linear_gemm_big_split.
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, workspace_bytes);
+    if (sp.parts > 0)
+        return launch_linear_gemm_big(XDT, y_dtype, 2, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, workspace, sp, stream);
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int small = tune_value("gemm_small", -1);
     if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128)))
@@ -821,22 +751,25 @@ static int launch_gemm_group(const void* X, const void* W_b, const uint32_t* B_p
 
 int launch_linear_gemm_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                              const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, hipStream_t stream)
+                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, void* workspace,
+                             size_t workspace_bytes, hipStream_t stream)
 {
     if (x_dtype == kBF16)
-        return launch_gemm_group<kBF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
-    return launch_gemm_group<kF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
+        return launch_gemm_group<kBF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, workspace,
+                                        workspace_bytes, stream);
+    return launch_gemm_group<kF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, workspace,
+                                   workspace_bytes, stream);
 }
 
 int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                        const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                       int64_t d_out, int64_t d_in, hipStream_t stream)
+                       int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     if (x_dtype == kBF16)
-        return axis == 0 ? launch_gemm_bm<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-                         : launch_gemm_bm<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-    return axis == 0 ? launch_gemm_bm<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-                     : launch_gemm_bm<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
+        return axis == 0 ? launch_gemm_bm<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream)
+                         : launch_gemm_bm<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream);
+    return axis == 0 ? launch_gemm_bm<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream)
+                     : launch_gemm_bm<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream);
 }
 
 // Measurement builds of the pipelined kernel (bf16 operands, row scales) with parts of its loop

@@ -1,0 +1,70 @@
+"""The 256 x 256 prefill kernel, whole tiles and tiles in parts of d_in, at the edges of its tiles, steps
+and parts, against the fp64 oracle under the rule of parity_util.py, and its workspace rules."""
+import pytest
+import torch
+
+from oracle import pdelta_oracle as orc
+from paper_2512_19720_amd import binding as pd
+from paper_2512_19720_amd import synth
+from parity_util import check_y, f16_dev, gpu_linear, make_case
+
+GB = 1 << 30
+
+
+# one step pair; a short last group of signs (d_in % 256 = 128); tiles cut in both directions; parts of
+# unequal length; more parts than the call has steps for fall back to whole tiles
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,d_out,d_in", [(65, 40, 128), (256, 256, 256), (257, 300, 384), (300, 264, 640), (129, 513, 1152)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("parts", [1, 2, 3])
+def test_whole_and_split_tiles(M, d_out, d_in, dtype, parts, monkeypatch):
+    monkeypatch.setenv("PDELTA_TUNE", f"gemm_big={parts}")
+    L = make_case(d_out, d_in, M, dtype, "row", 77 * M + d_out + d_in)
+    d = L["d"]
+    for axis, v_bits, v_dev in ((orc.ROW, L["v_row"], d["v_row"]), (orc.COL, L["v_col"], d["v_col"])):
+        ref = orc.linear(L["X"], L["W_b"], L["B"], v_bits, axis, L["dtype"])
+        for y in (torch.float32, torch.float16 if dtype == synth.F16 else torch.bfloat16):
+            check_y(gpu_linear(axis, d["X"], d["W_b"], d["B"], v_dev, y), ref, f"big M={M} {d_out}x{d_in} dt={dtype} axis={axis} parts={parts}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group,shared", [(32, False), (64, False), (128, True), (640, False), (640, True)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_blockwise_scales(group, shared, dtype, monkeypatch):
+    M, d_out, d_in = 130, 264, 640
+    L = make_case(d_out, d_in, M, dtype, "row", 9 + group)
+    d = L["d"]
+    _, v_bits = orc.pack_group(L["dW"], L["dW"] * 0, group, shared, dtype)
+    v_dev = f16_dev(v_bits)
+    ref = orc.linear_group(L["X"], L["W_b"], L["B"], v_bits, group, dtype)
+    for parts in (1, 2):
+        monkeypatch.setenv("PDELTA_TUNE", f"gemm_big={parts}")
+        Y = pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], v_dev, group, out_dtype=torch.float32)
+        check_y(Y, ref, f"big group={group} shared={shared} dt={dtype} parts={parts}")
+
+
+def test_workspace_rules_without_a_gpu():
+    L = pd.lib()
+    A = 1 << 40
+    M, d_out, d_in = 1024, 4096, 4096                                   # 64 tiles in 4 parts
+    need = L.pdelta_linear_workspace_bytes(M, d_out, d_in, pd.F16)
+    assert need == 256 * 256 * 256 * 4
+    assert L.pdelta_linear_workspace_bytes(64, d_out, d_in, pd.F16) == 0            # decode
+    assert L.pdelta_linear_workspace_bytes(M, d_out, 4096 + 32, pd.F16) == 0        # another kernel's d_in
+    assert L.pdelta_linear_workspace_bytes(M, d_out, 100, pd.F16) == 0 and L.pdelta_linear_workspace_bytes(M, d_out, d_in, pd.F32) == 0
+    for m in (65, 251, 777, 2048, 4096):
+        for o in (1, 256, 4096, 11008, 14336):
+            for k in (128, 640, 4096, 11008):
+                assert L.pdelta_linear_workspace_bytes(m, o, k, pd.BF16) <= 64 << 20
+
+    def call(ws=A + 5 * GB, n=need, axis=pd.ROW):
+        return L.pdelta_linear_ws(A, A + GB, A + 2 * GB, A + 3 * GB, axis, A + 4 * GB, M, d_out, d_in, pd.F16, pd.F16, ws, n, None)
+
+    assert call(n=need - 1) == pd.EWORKSPACE
+    assert call(ws=A + 5 * GB + 8) == pd.EALIGN
+    assert call(ws=None) == pd.EINVAL
+    for k in range(5):
+        assert call(ws=A + k * GB) == pd.EINVAL                         # on X, W_b, B_packed, v, Y
+    assert call(axis=2) == pd.EINVAL
+    assert L.pdelta_linear_group_ws(A, A + GB, A + 2 * GB, A + 3 * GB, 128, 0, A + 4 * GB, M, d_out, d_in, pd.F16, pd.F16,
+                                    A + 5 * GB, need - 1, None) == pd.EWORKSPACE
