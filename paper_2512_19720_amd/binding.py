@@ -91,6 +91,8 @@ def lib() -> ctypes.CDLL:
                                              i32, i32, vp]
         L.pdelta_grad_v_workspace_bytes.restype = sz
         L.pdelta_grad_v_workspace_bytes.argtypes = [i64, i64, i64, i32]
+        L.pdelta_grad_v_split_workspace_bytes.restype = sz
+        L.pdelta_grad_v_split_workspace_bytes.argtypes = [i64, i64, i64, i32]
         L.pdelta_grad_v.restype = i32
         L.pdelta_grad_v.argtypes = [vp, vp, vp, i32, vp, i64, i64, i64, i32, vp, sz, vp]
         L.pdelta_pack_group_workspace_bytes.restype = sz
@@ -451,8 +453,8 @@ def pdelta_grad_v(X, dY, B_packed, axis: int, out=None, workspace: torch.Tensor 
     if out is None:
         out = torch.empty(d_out if axis == ROW else d_in, dtype=torch.float32, device=X.device)
     if workspace is None:
-        workspace = torch.empty(max(pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis), 16), dtype=torch.uint8,
-                                device=X.device)
+        workspace = torch.empty(max(lib().pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis), 16),
+                                dtype=torch.uint8, device=X.device)
     rc = lib().pdelta_grad_v(_dev(X, "X") or None, _dev(dY, "dY") or None, _dev(B_packed, "B_packed"), axis,
                              _dev(out, "grad_v"), M, d_out, d_in, dtype_code(X.dtype), _dev(workspace, "workspace"),
                              workspace.numel(), _stream())

@@ -471,6 +471,13 @@ size_t pdelta_grad_v_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int
     return pdelta::grad_v_workspace_bytes(M, d_out, d_in, axis);
 }
 
+size_t pdelta_grad_v_split_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis)
+{
+    const pdelta::TuneScope tune_scope;
+    if (M < 0 || d_out <= 0 || d_in <= 0 || (axis != PDELTA_ROW && axis != PDELTA_COL)) return 0;
+    return pdelta::grad_v_split_workspace_bytes(M, d_out, d_in, axis);
+}
+
 int pdelta_grad_v(const void* X, const void* dY, const uint32_t* B_packed, int axis, float* grad_v,
                   int64_t M, int64_t d_out, int64_t d_in, int dtype, void* workspace,
                   size_t workspace_bytes, void* stream)
@@ -494,7 +501,7 @@ int pdelta_grad_v(const void* X, const void* dY, const uint32_t* B_packed, int a
         overlaps(grad_v, g_bytes, B_packed, (size_t)d_out * d_in / 8) ||
         overlaps(grad_v, g_bytes, workspace, workspace_bytes))
         return PDELTA_EINVAL;
-    const int rc = launch_grad_v(dtype, axis, X, dY, B_packed, grad_v, M, d_out, d_in, workspace, (hipStream_t)stream);
+    const int rc = launch_grad_v(dtype, axis, X, dY, B_packed, grad_v, M, d_out, d_in, workspace, workspace_bytes, (hipStream_t)stream);
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 

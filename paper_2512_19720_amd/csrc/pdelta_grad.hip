@@ -13,11 +13,13 @@
 // The epilogue multiplies each accumulator by its G entry and sums the tile's 256 tokens; tiles
 // write one partial per (token tile, output) to the workspace and a second kernel adds the
 // partials in a fixed order: no atomics, reproducible.
+#include <algorithm>
 #include <type_traits>
 
 #include "pdelta.h"
 #include "pdelta_device.h"
 #include "pdelta_host.h"
+#include "pdelta_lds_load.h"
 
 namespace pdelta {
 
@@ -353,14 +355,222 @@ static int launch_grad_tile_pipe(const uint16_t* A, const uint16_t* G, const uin
     return 0;
 }
 
+// ---------------------------------------------------------------------------------------------
+// 256 tokens x 256 outputs x 64 inputs, the form of the 256 x 256 prefill kernel (Kc a multiple of 128):
+// A comes by direct loads into LDS, the sign tile is expanded from sign words that were fetched for four
+// steps at a time, two LDS stages, one barrier per step three quarters into it.  Half the A traffic per
+// product of the 256 x 128 kernel, and none of it through registers.  The contraction may be cut into
+// `parts`, each with partial sums of its own: the epilogue is linear, so a part costs one more row of
+// partials and nothing else.  2048 tokens, 4096 x 4096 bf16: see grad_big_parts.
+constexpr int kGbTile = 256, kGbBK = 64, kGbUnitK = 128;
+constexpr int kGbAB = kGbTile * kGbBK * 2, kGbStage = 2 * kGbAB;      // bytes of A (of the signs) and of a stage
+constexpr int kGbSigns = 2 * kGbStage, kGbLds = kGbSigns + 8 * 1024;  // + sign words: 1 KB per wave
+
+template <int DT>
+__global__ void __launch_bounds__(512, 2)
+grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, const uint32_t* __restrict__ bits,
+                float* __restrict__ partial, int M, int Nc, int Kc, int m_tiles, int tiles, int parts)
+{
+    constexpr int FM = 4, FN = 2;                     // a wave owns 128 tokens x 64 outputs
+    extern __shared__ __attribute__((aligned(16))) unsigned char gb_smem[];
+
+    // each XCD takes a contiguous range of units: token tiles first, then output tiles, then parts
+    const int units = tiles * parts, per = (units + 7) / 8;
+    const int unit = (int)(blockIdx.x % 8) * per + (int)blockIdx.x / 8;
+    if (unit >= units) return;                        // whole workgroup
+    const int part = unit / tiles, tile = unit % tiles;
+    const int tile_m = tile % m_tiles, m0 = tile_m * kGbTile, n0 = tile / m_tiles * kGbTile;
+    const int k_units = Kc / kGbUnitK;
+    const int k_first = (int)((int64_t)k_units * part / parts), k_end = (int)((int64_t)k_units * (part + 1) / parts);
+    const int n_steps = (k_end - k_first) * (kGbUnitK / kGbBK);       // even, at least 2
+    const int kb0 = k_first * kGbUnitK, kb_end = k_end * kGbUnitK;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)gb_smem;
+
+    // A load covers 8 rows of 128 bytes, a wave loads 32 rows of A and expands 32 rows of signs; rows past
+    // the end repeat the last one (they only feed results that are never used).  The 16-byte piece p of LDS
+    // row r holds inputs 8 (p ^ ((r >> 1) & 7)) .. +7.
+    const char* abase = (const char*)(A + (int64_t)m0 * Kc + kb0);
+    uint32_t chunk[2], aoff[4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) chunk[q] = (uint32_t)((lane & 7) ^ (q * 4 + (lane >> 4)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        aoff[q] = (uint32_t)(min(m0 + wave * 32 + q * 8 + (lane >> 3), M - 1) - m0) * (uint32_t)Kc * 2u + chunk[q & 1] * 16u;
+    // lanes 0-31: sign words of the wave's rows for two steps, lanes 32-63 for the next two
+    const int srow = min(n0 + wave * 32 + (lane & 31), Nc - 1);
+    const char* sptr = (const char*)bits + (int64_t)srow * (Kc >> 3) + (kb0 >> 3);
+
+    auto request = [&](int s, uint32_t stage) {
+        const int rel = s * kGbBK;
+        if ((s & 3) == 0) {                           // never past Kc: a short last group repeats its first half
+            const int half = (lane >= 32 && kb0 + rel + 128 < kb_end) ? 16 : 0;
+            load_lds_16v(lds0 + kGbSigns + wave * 1024, sptr + (rel >> 3) + half);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_lds_16(lds0 + stage + (wave * 4 + q) * 1024, aoff[q], abase + (int64_t)rel * 2);
+    };
+    uint32_t sbyte[4];
+    auto fetch_signs = [&](int s) {
+        const unsigned char* signs = gb_smem + kGbSigns + wave * 1024 + ((s >> 1) & 1) * 512 + (s & 1) * 8;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sbyte[q] = signs[(q * 8 + (lane >> 3)) * 16 + chunk[q & 1]];
+    };
+    auto expand = [&](uint32_t stage) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t neg = ~sbyte[q] & 0xFFu;
+            uint32_t y = neg | (neg << 15);           // bit 2p + 1 at 2p + 16
+            asm("" : "+v"(y));                        // (else y and its shifts become full multiplications)
+            uint4v r;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) r[p] = ((y << (15 - 2 * p)) & 0x80008000u) | (DT == kBF16 ? 0x3F803F80u : 0x3C003C00u);
+            *(uint4v*)(gb_smem + stage + kGbAB + (wave * 4 + q) * 1024 + lane * 16) = r;
+        }
+    };
+
+    float16v acc[FM][FN];
+#pragma unroll
+    for (int f = 0; f < FM; ++f)
+#pragma unroll
+        for (int h = 0; h < FN; ++h)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[f][h][r] = 0.f;
+
+    uint32_t frag[4];                                 // byte offset of this lane's piece of 16 inputs ks
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+        frag[ks] = (uint32_t)((lane & 31) * 128 + (((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16));
+    uint4v a[2][FM], b[2][FN];
+    auto read_frags = [&](uint32_t stage, int ks) {
+        const unsigned char* xa = gb_smem + stage + wm * 128 * 128 + frag[ks];
+        const unsigned char* sa = gb_smem + stage + kGbAB + wn * 64 * 128 + frag[ks];
+#pragma unroll
+        for (int h = 0; h < FN; ++h) b[ks & 1][h] = *(const uint4v*)(sa + h * 32 * 128);
+#pragma unroll
+        for (int f = 0; f < FM; ++f) a[ks & 1][f] = *(const uint4v*)(xa + f * 32 * 128);
+    };
+    auto multiply = [&](int ks) {
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+#pragma unroll
+            for (int h = 0; h < FN; ++h) acc[f][h] = grad_mfma<DT>(a[ks & 1][f], b[ks & 1][h], acc[f][h]);
+    };
+
+    request(0, 0);
+    wait_loads<0>();
+    fetch_signs(0);
+    expand(0);
+    lds_barrier();
+    request(1, kGbStage);
+    read_frags(0, 0);
+
+    // Step s; REQ: request step s + 2, MORE: there is a step s + 1.  The fences keep the LDS reads above
+    // the MFMAs and the expansion between them.
+    auto step = [&](int s, uint32_t cur, uint32_t nxt, auto req, auto more) {
+        constexpr bool REQ = decltype(req)::value, MORE = decltype(more)::value;
+        read_frags(cur, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(cur, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_loads<0>();
+        if constexpr (MORE) fetch_signs(s + 1);
+        read_frags(cur, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(2);
+        if constexpr (MORE) { expand(nxt); interleave<FM * FN, 6>(); }
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+        if constexpr (MORE) read_frags(nxt, 0);
+        if constexpr (REQ) request(s + 2, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(3);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int s = 0;
+    for (; s + 2 < n_steps; s += 2) {
+        step(s, 0, kGbStage, std::true_type{}, std::true_type{});
+        step(s + 1, kGbStage, 0, std::true_type{}, std::true_type{});
+    }
+    step(s, 0, kGbStage, std::false_type{}, std::true_type{});
+    step(s + 1, kGbStage, 0, std::false_type{}, std::false_type{});
+
+    // epilogue as in grad_tile_kernel, a sum of its own for each 32 tokens (the last barrier came after the
+    // last fragment read: the stages are free)
+    float* red = (float*)gb_smem;                      // [2 wm][256]
+#pragma unroll
+    for (int h = 0; h < FN; ++h) {
+        const int n = n0 + wn * 64 + h * 32 + (lane & 31);
+        const int nc = min(n, Nc - 1);
+        float sum[FM];
+#pragma unroll
+        for (int f = 0; f < FM; ++f) {
+            sum[f] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int tok = m0 + wm * 128 + f * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+                const uint32_t gbits = G[(int64_t)min(tok, M - 1) * Nc + nc];
+                const float gval = tok < M ? bits_to_f32<DT>(gbits) : 0.f;
+                sum[f] += gval * acc[f][h][r];
+            }
+        }
+        float t = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        t += __shfl_xor(t, 32, kWave);
+        if (lane < 32) red[wm * kGbTile + wn * 64 + h * 32 + lane] = t;
+    }
+    __syncthreads();
+    const int tid = threadIdx.x;
+    if (tid < kGbTile && n0 + tid < Nc)
+        partial[(int64_t)(part * m_tiles + tile_m) * Nc + n0 + tid] = red[tid] + red[kGbTile + tid];
+}
+
+// Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel.  That one takes 7 us
+// and 0.8 us per step of 64 inputs when it has few tiles, however few they are; this one 24 us (its epilogue
+// reads G for every part) and 1.05 per step with at most 128 workgroups.  Above 64 tiles, or where the
+// workgroups would be more than 128, the epilogues cost what the shorter loops give.  256 tokens, 4096 x
+// 4096 fp16 row 60 -> 31 us, 512 tokens bf16 row 60 -> 41, col 73 -> 60, 128 tokens on 4096 x 11008 145 -> 49; 2048 tokens, 4096 x
+// 4096 in two parts 84-91 us against 71-78; 512 tokens in 8 parts 54 instead of 41.
+static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
+{
+    const int forced = tune_value("grad_big", -1);     // 0: never; n > 0: in n parts
+    if (Kc % kGbUnitK != 0 || M <= 0 || forced == 0 || (forced < 0 && tune_value("grad_pipe", -1) >= 0)) return 0;
+    const int64_t tiles = (M + kGbTile - 1) / kGbTile * ((Nc + kGbTile - 1) / kGbTile), units = Kc / kGbUnitK;
+    if (tiles > (1 << 24)) return 0;
+    if (forced > 0) return (int)std::min<int64_t>(forced, units);
+    if (tiles > 64) return 0;
+    const int64_t p = std::min<int64_t>(std::min<int64_t>(128 / tiles, units), 16);
+    return 24 + 1.05 * 2 * (double)((units + p - 1) / p) < 0.9 * (7 + 0.8 * 2 * (double)units) ? (int)p : 0;
+}
+
+template <int DT>
+static int launch_grad_big(const uint16_t* A, const uint16_t* G, const uint32_t* bits, float* partial, int M, int Nc, int Kc,
+                           int m_tiles, int parts, hipStream_t stream)
+{
+    auto kernel = grad_big_kernel<DT>;
+    static unsigned lds_opted_in = 0;                 // per template instance: one kernel
+    if (opt_in_dynamic_lds((const void*)kernel, kGbLds, &lds_opted_in) != 0) return -1;
+    const int tiles = m_tiles * ((Nc + kGbTile - 1) / kGbTile);
+    const unsigned grid = (unsigned)((tiles * parts + 7) / 8 * 8);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), kGbLds, stream, A, G, bits, partial, M, Nc, Kc, m_tiles, tiles, parts);
+    return 0;
+}
+
 __global__ void __launch_bounds__(256)
 grad_reduce_kernel(const float* __restrict__ partial, float* __restrict__ grad, int n, int m_tiles)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    float s = 0.f;
-    for (int t = 0; t < m_tiles; ++t) s += partial[(int64_t)t * n + i];
-    grad[i] = s;
+    double s = 0.0;                                    // (up to 16 parts times the token tiles)
+#pragma unroll 4
+    for (int t = 0; t < m_tiles; ++t) s += (double)partial[(int64_t)t * n + i];
+    grad[i] = (float)s;
 }
 
 // Bt[i][o / 32] bit (o % 32) = B[o][i / 32] bit (i % 32); d_out % 32 == 0.  A wave takes 64 rows
@@ -389,27 +599,34 @@ transpose_bits_kernel(const uint32_t* __restrict__ B, uint32_t* __restrict__ Bt,
     }
 }
 
-size_t grad_v_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis)
+static size_t grad_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis, int parts)
 {
     const int64_t m_tiles = (M + kGradBM - 1) / kGradBM;
     const int64_t n = axis == 0 ? d_out : d_in;
-    size_t bytes = (size_t)(m_tiles > 0 ? m_tiles : 1) * n * sizeof(float);
+    size_t bytes = (size_t)(m_tiles > 0 ? m_tiles : 1) * parts * n * sizeof(float);
     bytes = (bytes + 255) & ~(size_t)255;
     if (axis == 1) bytes += (size_t)d_in * (d_out / 8);            // transposed sign bits
     return bytes;
 }
+size_t grad_v_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis) { return grad_bytes(M, d_out, d_in, axis, 1); }
+size_t grad_v_split_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis)
+{
+    return grad_bytes(M, d_out, d_in, axis, std::max(1, grad_big_parts(M, axis == 0 ? d_out : d_in, axis == 0 ? d_in : d_out)));
+}
 
 int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint32_t* B_packed, float* grad,
-                  int64_t M, int64_t d_out, int64_t d_in, void* workspace, hipStream_t stream)
+                  int64_t M, int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     const int64_t m_tiles = (M + kGradBM - 1) / kGradBM;
     const int64_t Nc = axis == 0 ? d_out : d_in, Kc = axis == 0 ? d_in : d_out;
+    int parts = grad_big_parts(M, Nc, Kc);
+    if (parts > 1 && grad_bytes(M, d_out, d_in, axis, parts) > workspace_bytes) parts = 0;
     float* partial = (float*)workspace;
     const uint16_t* A = (const uint16_t*)(axis == 0 ? X : dY);
     const uint16_t* G = (const uint16_t*)(axis == 0 ? dY : X);
     const uint32_t* bits = B_packed;
     if (axis == 1 && m_tiles > 0) {
-        size_t off = (size_t)m_tiles * Nc * sizeof(float);
+        size_t off = (size_t)m_tiles * std::max(1, parts) * Nc * sizeof(float);
         off = (off + 255) & ~(size_t)255;
         uint32_t* Bt = (uint32_t*)((char*)workspace + off);
         const dim3 grid((unsigned)((d_in / 32 + 3) / 4), (unsigned)((d_out + 63) / 64));
@@ -420,6 +637,11 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
     const dim3 grid((unsigned)(m_tiles * n_tiles));
     if (m_tiles == 0) {
         // no tokens: the reduction below writes zeros
+    } else if (parts > 0) {
+        const int rc = dtype == kBF16
+            ? launch_grad_big<kBF16>(A, G, bits, partial, (int)M, (int)Nc, (int)Kc, (int)m_tiles, parts, stream)
+            : launch_grad_big<kF16>(A, G, bits, partial, (int)M, (int)Nc, (int)Kc, (int)m_tiles, parts, stream);
+        if (rc != 0) return rc;
     } else if (tune_value("grad_pipe", 1) != 0) {
         // the pipelined kernel is the default (grad_pipe=0: the two-workgroups-per-CU kernel)
         const int rc = dtype == kBF16
@@ -433,7 +655,7 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
         hipLaunchKernelGGL(grad_tile_kernel<kF16>, grid, dim3(512), 0, stream, A, G, bits, partial, (int)M, (int)Nc,
                            (int)Kc, (int)m_tiles);
     hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((Nc + 255) / 256)), dim3(256), 0, stream,
-                       (const float*)partial, grad, (int)Nc, (int)m_tiles);
+                       (const float*)partial, grad, (int)Nc, (int)m_tiles * std::max(1, parts));
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

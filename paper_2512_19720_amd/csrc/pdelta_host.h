@@ -76,8 +76,10 @@ int launch_linear_variants(int x_dtype, int y_dtype, int axis, const void* X, co
 // dL/dv from dY (training of the scale vectors).  Workspace: partial sums per token tile, plus
 // the transposed sign bits in column mode.
 size_t grad_v_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis);
+// The same with partial sums for every part of a split contraction (at least the size above).
+size_t grad_v_split_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis);
 int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint32_t* B_packed, float* grad,
-                  int64_t M, int64_t d_out, int64_t d_in, void* workspace, hipStream_t stream);
+                  int64_t M, int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 // Prefill-shaped layer (many tokens): MFMA tile kernel.  workspace: nullptr with 0 bytes, or at least
 // linear_gemm_workspace_bytes.

@@ -1,0 +1,34 @@
+"""The 256 x 256 gradient kernel, whole and in parts of the contraction, at the edges of its tiles, steps and
+parts, against the fp64 oracle under the rule of test_gpu_grad_v.py, and its workspace sizes."""
+import pytest
+
+from oracle import pdelta_oracle as orc
+from paper_2512_19720_amd import binding as pd
+from paper_2512_19720_amd import synth
+from parity_util import to_dev, words_dev
+from test_gpu_grad_v import check_grad, make
+
+
+# one step pair; a short last group of signs (contraction % 256 = 128); tiles cut in both directions
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,d_out,d_in", [(1, 128, 128), (257, 128, 384), (300, 384, 640), (64, 640, 1152)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("axis", [orc.ROW, orc.COL])
+@pytest.mark.parametrize("parts", [1, 2, 3])
+def test_whole_and_split_contraction(M, d_out, d_in, dtype, axis, parts, monkeypatch):
+    monkeypatch.setenv("PDELTA_TUNE", f"grad_big={parts}")
+    X, dY, B = make(M, d_out, d_in, dtype, 31 * M + d_in + parts)
+    ref = orc.grad_v(X, dY, B, axis, dtype)
+    got = pd.pdelta_grad_v(to_dev(X, dtype), to_dev(dY, dtype), words_dev(B), axis)
+    check_grad(got, ref, f"grad big M={M} {d_out}x{d_in} dt={dtype} axis={axis} parts={parts}")
+
+
+def test_split_workspace_sizes():
+    L = pd.lib()
+    assert L.pdelta_grad_v_split_workspace_bytes(256, 4096, 4096, pd.ROW) == 8 * 4096 * 4        # 16 tiles in 8 parts
+    assert L.pdelta_grad_v_split_workspace_bytes(0, 64, 96, pd.ROW) == 64 * 4
+    assert L.pdelta_grad_v_split_workspace_bytes(5, 0, 96, pd.ROW) == 0
+    for M in (1, 64, 300, 2048, 4096):
+        for d_out, d_in in ((32, 32), (256, 640), (4096, 4096), (14336, 4096), (4096, 11008)):
+            for axis in (pd.ROW, pd.COL):
+                assert L.pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis) >= pd.pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis)
