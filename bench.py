@@ -418,7 +418,7 @@ def main() -> int:
         if group_prefill is not None:
             out["prefill"]["blockwise_scales"] = group_prefill
         out["prefill"]["parts"] = prefill_parts
-        out["roofline_prefill"] = {"bound": "mfma", "kernel": "linear_gemm_pipe_kernel (prefill, bf16 in, fp16 MFMA)",
+        out["roofline_prefill"] = {"bound": "mfma", "kernel": "linear_gemm_big_kernel / linear_gemm_pipe_kernel (prefill, bf16 in, fp16 MFMA)",
                                    "achieved": round(agg, 1), "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                                    "frac": round(agg / MFMA_PEAK_TFLOPS, 4), "traffic": None}
         torch.cuda.empty_cache()

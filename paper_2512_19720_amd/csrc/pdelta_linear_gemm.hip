@@ -10,7 +10,8 @@
 // WM x 2 waves (8 waves of 64 x 64 outputs for BM = 256), each wave's outputs as MFMA 32x32x16
 // tiles; LDS rows padded to 144 bytes so that 16-byte fragment reads of 16 consecutive rows touch
 // all 64 banks once.  Three kernels share the tile:
-//   linear_gemm_pipe_kernel   the default above 128 tokens: one workgroup per CU, two LDS stages,
+//   linear_gemm_pipe_kernel   above 128 tokens where the 256 x 256 tiles of pdelta_linear_gemm_dma.hip
+//                             (d_in a multiple of 128) are not the better ones: one workgroup per CU, two LDS stages,
 //                             two register sets, one barrier per step (described at the kernel);
 //   linear_gemm_kernel        one LDS stage, the loads of step s+1 in flight while step s is
 //                             multiplied, two workgroups per CU so that one stages while the
