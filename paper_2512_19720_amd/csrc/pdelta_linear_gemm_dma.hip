@@ -47,6 +47,21 @@ constexpr int kBigXB = kBigTile * kBigBK * 2, kBigStage = 2 * kBigXB;   // bytes
 constexpr int kBigSigns = 2 * kBigStage, kBigScales = kBigSigns + 8 * 1024, kBigTouch = kBigScales + 8 * 1024, kBigLds = kBigTouch + 8 * 256;
 constexpr size_t kPartBytes = (size_t)kBigTile * kBigTile * 4;      // fp32 partial sums of one tile
 
+// x ^ C.  HERE: computed where it stands.  As ordinary expressions the LDS addresses of the loop are all kept in
+// registers, up to 20 of them, and for fp16 with column or blockwise scales there are not enough (accumulators, two
+// sets of fragments and raw weights take 200 of the 256): 5 and 11 were spilled and reloaded between the MFMAs, each
+// reload waiting for the direct loads before it.  fp16, column / blockwise, with and without the spills: 2048 x 8192 x
+// 4096 154 -> 143 / 165 -> 148 us, 777 x 4096 x 11008 blockwise 137 -> 123.  bf16 reads the raw weights when fewer
+// fragments are held, and with row scales there is no scale to fetch.
+template <bool HERE, int C>
+__device__ __forceinline__ uint32_t xor_at(uint32_t x)
+{
+    if constexpr (!HERE) return x ^ (uint32_t)C;
+    uint32_t r;
+    asm volatile("v_xor_b32 %0, %1, %2" : "=v"(r) : "n"(C), "v"(x));
+    return r;
+}
+
 template <int WDT, int AXIS>
 __global__ void __launch_bounds__(512, 2)
 linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
@@ -55,6 +70,7 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
                        int m_tiles, int whole, int split, int parts, int v_stride, int g_shift)
 {
     constexpr int FM = 4, FN = 2;                     // a wave owns 128 tokens x 64 output rows
+    constexpr bool HERE = WDT != kBF16 && AXIS != 0;  // see xor_at
     extern __shared__ __attribute__((aligned(16))) unsigned char dma_smem[];
 
     // tile and part of this workgroup (see the map in the header comment)
@@ -101,25 +117,24 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
         if constexpr (AXIS == 0) vrow[q] = (uint32_t)v[n0 + row] * 0x10001u;
     }
     // lanes 0-31: sign words of the wave's rows for two steps, lanes 32-63 for the next two
-    const int srow = min(n0 + wave * 32 + (lane & 31), d_out - 1);
-    const char* sptr = (const char*)B_packed + (int64_t)srow * (K >> 3) + (kb0 >> 3);
-    const uint16_t* vgrow = v + (int64_t)srow * v_stride;
+    const int srow = min(n0 + wave * 32 + (lane & 31), d_out - 1) - n0;
+    const char* sbase = (const char*)B_packed + (int64_t)n0 * (K >> 3) + (kb0 >> 3);
+    const uint32_t soff = (uint32_t)srow * (uint32_t)(K >> 3) + (lane >> 5) * 16u;
+    const uint16_t* vgbase = v + (int64_t)n0 * v_stride;
+    const uint32_t vgoff = (uint32_t)srow * (uint32_t)v_stride;
     const int g_step = AXIS == 2 && g_shift < 31 ? max(1 << g_shift, kBigBK) : 0;   // 0: one scale for all of d_in
 
     // signs and scales of step s (if it is the first that they serve), then W_b, then X
     auto request = [&](int s, uint32_t stage) {
         const int rel = s * kBigBK, kb = kb0 + rel;
         if ((s & 3) == 0) {                           // never past d_in: a short last group repeats its first half
-            const int half = (lane >= 32 && kb + 128 < kb_end) ? 16 : 0;
-            load_lds_16v(lds0 + kBigSigns + wave * 1024, sptr + (rel >> 3) + half);
-            if constexpr (AXIS == 1) {
-                const int i = min(kb + (lane & 31) * 8, kb_end - 8);
-                load_lds_16v(lds0 + kBigScales + wave * 1024, v + i);
-            }
+            load_lds_16(lds0 + kBigSigns + wave * 1024, kb + 128 < kb_end ? soff : soff - (lane >> 5) * 16u, sbase + (rel >> 3));
+            if constexpr (AXIS == 1)
+                load_lds_16(lds0 + kBigScales + wave * 1024, (uint32_t)min(kb + (lane & 31) * 8, kb_end - 8) * 2u, v);
         }
         if constexpr (AXIS == 2) {
             if (s == 0 || (g_step != 0 && (kb & (g_step - 1)) == 0))
-                load_lds_2(lds0 + kBigScales + wave * 1024, vgrow + ((kb + (lane >> 5) * 32) >> g_shift));
+                load_lds_2(lds0 + kBigScales + wave * 1024, (vgoff + (uint32_t)((kb + (lane >> 5) * 32) >> g_shift)) * 2u, vgbase);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) load_lds_16(lds0 + stage + kBigXB + (wave * 4 + q) * 1024, woff[q], wbase + (int64_t)rel * 2);
@@ -130,24 +145,27 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
     // L2 prefetch of W_b, kBigFar steps ahead: the workgroups of one output-row tile on an XCD share its 256
     // rows, 4 to 8 lanes of each wave touch one 128-byte line each.  (The data goes to LDS that nobody reads.)
     const int sharers = min(m_tiles, 8), lanes = min(32 / sharers, 8);
-    const int prow = min(n0 + (tile % m_tiles % sharers) * (256 / sharers) + wave * lanes + lane, d_out - 1) - n0;
-    const char* pline = wbase + (int64_t)prow * K * 2;
+    const uint32_t poff = (uint32_t)(min(n0 + (tile % m_tiles % sharers) * (256 / sharers) + wave * lanes + lane, d_out - 1) - n0) * (uint32_t)K * 2u;
     auto prefetch = [&](int s) {
-        if (lane < lanes) load_lds_4(lds0 + kBigTouch + wave * 256, pline + (int64_t)min(s + kBigFar, n_steps - 1) * (kBigBK * 2));
+        if (lane < lanes) load_lds_4(lds0 + kBigTouch + wave * 256, poff, wbase + (int64_t)min(s + kBigFar, n_steps - 1) * (kBigBK * 2));
     };
 
     // In place: the wave's own pieces of W_b -> W_hat, of bf16 X -> fp16.
     uint4v raw[4], wvec[2];
     uint32_t sbyte[4], wscale[4];
+    // sign byte and scale of the wave's rows lane / 8 + 8 q, LDS piece lane % 8
+    const uint32_t sign0 = (uint32_t)(lane >> 3) * 16 + chunk[0], scale0 = ((chunk[0] >> 2) * 32 + (uint32_t)(lane >> 3)) * 4;
     auto fetch_w = [&](int s, uint32_t stage) {
         const unsigned char* signs = dma_smem + kBigSigns + wave * 1024 + ((s >> 1) & 1) * 512 + (s & 1) * 8;
         const unsigned char* scales = dma_smem + kBigScales + wave * 1024;
+        const uint32_t sign_at[2] = {sign0, xor_at<HERE, 4>(sign0)};      // chunk[1] = chunk[0] ^ 4
+        uint32_t scale_at[2] = {scale0, 0};
+        if constexpr (AXIS == 2) scale_at[1] = xor_at<HERE, 128>(scale0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int r = q * 8 + (lane >> 3);
             raw[q] = *(const uint4v*)(dma_smem + stage + kBigXB + (wave * 4 + q) * 1024 + lane * 16);
-            sbyte[q] = signs[r * 16 + chunk[q & 1]];
-            if constexpr (AXIS == 2) wscale[q] = *(const uint16_t*)(scales + ((chunk[q & 1] >> 2) * 32 + r) * 4);
+            sbyte[q] = signs[q * 128 + sign_at[q & 1]];
+            if constexpr (AXIS == 2) wscale[q] = *(const uint16_t*)(scales + q * 32 + scale_at[q & 1]);
         }
         if constexpr (AXIS == 1) {
 #pragma unroll
@@ -189,14 +207,14 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[f][h][r] = 0.f;
 
-    uint32_t frag[4];                                 // byte offset of this lane's piece of 16 inputs ks
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-        frag[ks] = (uint32_t)((lane & 31) * 128 + (((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16));
+    // this lane's piece of 16 inputs ks is at byte frag ^ (32 ks)
+    const uint32_t frag = (uint32_t)((lane & 31) * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) * 16));
     half8 a[2][FM], b[2][FN];
-    auto read_frags = [&](uint32_t stage, int ks) {
-        const unsigned char* xa = dma_smem + stage + wm * 128 * 128 + frag[ks];
-        const unsigned char* wa = dma_smem + stage + kBigXB + wn * 64 * 128 + frag[ks];
+    auto read_frags = [&](uint32_t stage, auto step16) {
+        constexpr int ks = decltype(step16)::value;
+        const uint32_t piece = xor_at<HERE, ks * 32>(frag);
+        const unsigned char* xa = dma_smem + stage + wm * 128 * 128 + piece;
+        const unsigned char* wa = dma_smem + stage + kBigXB + wn * 64 * 128 + piece;
 #pragma unroll
         for (int h = 0; h < FN; ++h) b[ks & 1][h] = *(const half8*)(wa + h * 32 * 128);
 #pragma unroll
@@ -217,13 +235,13 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
     if constexpr (WDT == kBF16) { fetch_x(0); convert_x(0); }
     lds_barrier();
     request(1, kBigStage);
-    read_frags(0, 0);
+    read_frags(0, std::integral_constant<int, 0>{});
 
     // Step s; REQ: request step s + 2, MORE: there is a step s + 1.  The fences keep the LDS reads above
     // the MFMAs (left alone, the compiler sinks them below) and the conversion between them.
     auto step = [&](int s, uint32_t cur, uint32_t nxt, auto req, auto more) {
         constexpr bool REQ = decltype(req)::value, MORE = decltype(more)::value;
-        read_frags(cur, 1);
+        read_frags(cur, std::integral_constant<int, 1>{});
         __builtin_amdgcn_sched_barrier(0);
         multiply(0);
         __builtin_amdgcn_sched_barrier(0);
@@ -232,7 +250,7 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
             if constexpr (WDT == kBF16) fetch_w(s + 1, nxt);
         }
         if constexpr (REQ && WDT != kBF16) prefetch(s);
-        read_frags(cur, 2);
+        read_frags(cur, std::integral_constant<int, 2>{});
         if constexpr (MORE && WDT != kBF16) fetch_w(s + 1, nxt);
         __builtin_amdgcn_sched_barrier(0);
         multiply(1);
@@ -240,14 +258,14 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (MORE && WDT == kBF16) { wait_loads<0>(); fetch_x(nxt); }
         if constexpr (REQ && WDT == kBF16) prefetch(s);
-        read_frags(cur, 3);
+        read_frags(cur, std::integral_constant<int, 3>{});
         __builtin_amdgcn_sched_barrier(0);
         multiply(2);
         if constexpr (MORE && WDT == kBF16) { convert_x(nxt); interleave<FM * FN, 6>(); }
         if constexpr (MORE && WDT != kBF16) { convert_w(nxt); interleave<FM * FN, 7>(); }
         __builtin_amdgcn_sched_barrier(0);
         lds_barrier();
-        if constexpr (MORE) read_frags(nxt, 0);
+        if constexpr (MORE) read_frags(nxt, std::integral_constant<int, 0>{});
         if constexpr (REQ) request(s + 2, cur);
         __builtin_amdgcn_sched_barrier(0);
         multiply(3);

@@ -1,0 +1,35 @@
+"""What the compiler made of the kernels, read from the code objects inside the built library: the prefill
+kernels with hand-counted waits must not touch scratch memory, because a reload there waits for every direct
+load that was issued before it."""
+import re
+import struct
+import subprocess
+
+from paper_2512_19720_amd import binding as pd
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+EM_AMDGPU = 224
+
+
+def kernels(tmp_path):
+    """{mangled name: metadata text} of every kernel of the library."""
+    blob = open(pd.lib()._name, "rb").read()
+    out = {}
+    for k, m in enumerate(re.finditer(rb"\x7fELF\x02\x01", blob)):
+        if m.start() == 0 or struct.unpack_from("<H", blob, m.start() + 18)[0] != EM_AMDGPU:
+            continue
+        path = tmp_path / f"{k}.elf"
+        path.write_bytes(blob[m.start():])
+        text = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True).stdout
+        for entry in re.split(r"\n  - (?=\.)", text):
+            name = re.search(r"\.symbol:\s+(\S+)\.kd", entry)
+            if name:
+                out[name.group(1)] = entry
+    return out
+
+
+def test_prefill_kernels_do_not_spill(tmp_path):
+    found = {n: e for n, e in kernels(tmp_path).items() if "linear_gemm_big_kernel" in n or "linear_gemm_pipe_kernel" in n}
+    assert sum("linear_gemm_big_kernel" in n for n in found) == 6            # two operand types, three kinds of scales
+    for name, entry in found.items():
+        assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
