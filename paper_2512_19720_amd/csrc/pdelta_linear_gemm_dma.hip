@@ -350,10 +350,12 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // (us, 256 CUs, steps of 64 inputs): here a step takes 1.75 (fp16) or 1.95 (bf16), a call 8 beside its
 // steps, a split 8 more for its second launch and 0.06 per part for the sums that it writes and reads;
 // the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernel 0.34 a step for each of its
-// workgroups on a CU (0.45 at least) and 3 a call.  bf16, this kernel against the others: 2048 x 11008 x
-// 4096 (88 of 344 tiles in 2 parts) 213 against 224-229, 777 x 4096 x 11008 blockwise (64 tiles in 4 parts)
-// 117 against 236, 1024 x 4096 x 4096 58 against 82; 512 x 4096 x 4096 42 against 45 and 251 tokens 32
-// against 30 lie below the line, which asks for 13 % on paper from the small kernel, whose price is rough.
+// workgroups on a CU (0.42 / 0.47 at least) and 3 a call.  Against the latter a split pays 0.4 more per part: it
+// has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, this
+// kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 213 against 224-229, 777 x 4096 x
+// 11008 blockwise (64 tiles in 4 parts) 117 against 236, 1024 x 4096 x 4096 58 against 82; 256 x 512 x 8192 (2 tiles
+// in 16 parts) 36 against 58.  Below the line: 256 x 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 26, 512 x 300 x
+// 3968 32 against 26, 251 x 4096 x 4096 32 against 30.
 BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, size_t workspace_bytes)
 {
     const BigSplit none{0, 0, 0};
@@ -376,9 +378,12 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     }
     const int64_t tiles128 = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int64_t tiles64 = ((M + 63) / 64) * ((d_out + 63) / 64);
-    const double other = tiles128 <= 128 ? 3 + n * std::max(0.45, 0.34 * (double)tiles64 / 256)
-                                         : 15 + n * (double)((tiles128 + 255) / 256) * (x_dtype == kBF16 ? 1.08 : 1.0);
-    return best < (tiles128 <= 128 ? 0.87 : 0.97) * other ? sp : none;
+    if (tiles128 <= 128) {
+        const double small = 3 + n * std::max(x_dtype == kBF16 ? 0.47 : 0.42, 0.34 * (double)tiles64 / 256);
+        return best + (sp.split > 0 ? 0.4 * sp.parts : 0) < small ? sp : none;
+    }
+    const double pipe = 15 + n * (double)((tiles128 + 255) / 256) * (x_dtype == kBF16 ? 1.08 : 1.0);
+    return best < 0.97 * pipe ? sp : none;
 }
 
 size_t linear_gemm_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype)

@@ -68,3 +68,14 @@ def test_workspace_rules_without_a_gpu():
     assert call(axis=2) == pd.EINVAL
     assert L.pdelta_linear_group_ws(A, A + GB, A + 2 * GB, A + 3 * GB, 128, 0, A + 4 * GB, M, d_out, d_in, pd.F16, pd.F16,
                                     A + 5 * GB, need - 1, None) == pd.EWORKSPACE
+
+
+def test_small_grids_stay_with_the_small_tiles():
+    """Few tiles in many parts were measured slower than the 64 x 64 kernel on the first shapes (26 against 35 us on
+    256 x 1024 x 4096 fp16) and faster on the last ones (58 against 36 us on 256 x 512 x 8192 bf16)."""
+    need = pd.lib().pdelta_linear_workspace_bytes
+    for M, d_out, d_in in ((129, 1024, 4096), (200, 1024, 4096), (256, 1024, 4096), (256, 300, 3968), (512, 300, 3968), (251, 4096, 4096)):
+        assert need(M, d_out, d_in, pd.F16) == 0, (M, d_out, d_in)
+    assert need(256, 1024, 4096, pd.BF16) == 0
+    for M, d_out, d_in in ((256, 512, 8192), (1024, 4096, 4096), (256, 4096, 11008), (777, 4096, 11008)):
+        assert need(M, d_out, d_in, pd.F16) > 0 and need(M, d_out, d_in, pd.BF16) > 0, (M, d_out, d_in)
