@@ -162,14 +162,14 @@ int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
 
 /*
  * The same two layers with a workspace (axis: PDELTA_ROW or PDELTA_COL).  Some prefill shapes (M > 64)
- * leave part of the chip without a tile; with a workspace those tiles are computed in several parts
- * of d_in whose fp32 sums are added in the order of d_in (reproducible; the sums of one output differ
- * from the ones without a workspace only in where they are cut).  pdelta_linear_workspace_bytes: the
- * bytes such a call uses, at most 64 MiB, 0 when none is used (always for M <= 64).  workspace may be
- * NULL with workspace_bytes = 0: exactly pdelta_linear_row / _col.  Otherwise PDELTA_EWORKSPACE if it
- * is smaller than that, PDELTA_EALIGN unless 16-byte aligned, PDELTA_EINVAL if it overlaps a tensor of
- * the call.  Its contents on entry are ignored; it belongs to the call until the call's work on the
- * stream has finished.
+ * leave part of the chip without a tile; here those tiles are computed in several parts of d_in whose
+ * fp32 sums are added in the order of d_in (reproducible; the sums of one output differ from those of
+ * pdelta_linear_row / _col only in where they are cut).  pdelta_linear_workspace_bytes: the bytes such a
+ * call uses, at most 64 MiB, 0 when none is used (always for M <= 64).  workspace may be NULL with
+ * workspace_bytes = 0: the same result, bit for bit, with the parts of a tile one after another, which
+ * takes longer.  Otherwise PDELTA_EWORKSPACE if it is smaller than that, PDELTA_EALIGN unless 16-byte
+ * aligned, PDELTA_EINVAL if it overlaps a tensor of the call.  Its contents on entry are ignored; it
+ * belongs to the call until the call's work on the stream has finished.
  */
 size_t pdelta_linear_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype);
 

@@ -201,8 +201,8 @@ _DECODE_MAX_TOKENS = 64
 
 
 def _prefill_workspace(M: int, d_out: int, d_in: int, x: torch.Tensor):
-    """Workspace of a prefill call, or None when the call uses none or the memory for it is not there
-    (the layer is then computed without)."""
+    """Workspace of a prefill call, or None when the call uses none or the memory for it is not there (the
+    result is the same without, bit for bit, and takes longer)."""
     need = lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[x.dtype])
     if need == 0:
         return None
@@ -221,13 +221,12 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
         ws = _prefill_workspace(M, d_out, d_in, X)
-        if ws is not None:
-            rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
-                                        ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
-                                        _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], ws.data_ptr(), ws.numel(),
-                                        _stream())
-            _check(rc, fn_name)
-            return out
+        rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+                                    ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
+                                    _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], ws.data_ptr() if ws is not None else None,
+                                    ws.numel() if ws is not None else 0, _stream())
+        _check(rc, fn_name)
+        return out
     fn = getattr(_lib, fn_name) if _lib is not None else getattr(lib(), fn_name)
     rc = fn(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"), _dev(out, "Y"),
             M, d_out, d_in, _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], _stream())

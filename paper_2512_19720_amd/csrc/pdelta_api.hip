@@ -101,7 +101,7 @@ int linear_workspace_check(const void* X, const void* W_b, const void* B_packed,
 
 int linear_common(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                   void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
-                  int axis, void* workspace, size_t workspace_bytes, void* stream)
+                  int axis, bool may_split, void* workspace, size_t workspace_bytes, void* stream)
 {
     const TuneScope tune_scope;
     if (const int rc = linear_check(X, W_b, B_packed, v, Y, M, d_out, d_in, x_dtype, y_dtype, axis))
@@ -115,7 +115,7 @@ int linear_common(const void* X, const void* W_b, const uint32_t* B_packed, cons
                        ? pdelta::launch_linear_skinny(x_dtype, y_dtype, axis, X, W_b, B_packed, v, Y, M,
                                                       d_out, d_in, s)
                        : pdelta::launch_linear_gemm(x_dtype, y_dtype, axis, X, W_b, B_packed, v, Y, M,
-                                                    d_out, d_in, workspace, workspace_bytes, s);
+                                                    d_out, d_in, PrefillSplit{may_split, workspace}, s);
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 
@@ -287,7 +287,7 @@ int pdelta_linear_row(const void* X, const void* W_b, const uint32_t* B_packed,
                       int x_dtype, int y_dtype, void* stream)
 {
     return pdelta::linear_common(X, W_b, B_packed, v_row, Y, M, d_out, d_in, x_dtype, y_dtype,
-                                 PDELTA_ROW, nullptr, 0, stream);
+                                 PDELTA_ROW, false, nullptr, 0, stream);
 }
 
 int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
@@ -295,7 +295,7 @@ int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
                       int x_dtype, int y_dtype, void* stream)
 {
     return pdelta::linear_common(X, W_b, B_packed, v_col, Y, M, d_out, d_in, x_dtype, y_dtype,
-                                 PDELTA_COL, nullptr, 0, stream);
+                                 PDELTA_COL, false, nullptr, 0, stream);
 }
 
 size_t pdelta_linear_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype)
@@ -310,7 +310,7 @@ int pdelta_linear_ws(const void* X, const void* W_b, const uint32_t* B_packed, c
                      int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype, void* workspace,
                      size_t workspace_bytes, void* stream)
 {
-    return pdelta::linear_common(X, W_b, B_packed, v, Y, M, d_out, d_in, x_dtype, y_dtype, axis, workspace, workspace_bytes,
+    return pdelta::linear_common(X, W_b, B_packed, v, Y, M, d_out, d_in, x_dtype, y_dtype, axis, true, workspace, workspace_bytes,
                                  stream);
 }
 
@@ -417,7 +417,7 @@ int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* lay
             rc = M <= kSkinnyMaxM ? launch_linear_skinny(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
                                                          L.v, L.Y, M, L.d_out, L.d_in, s)
                                   : launch_linear_gemm(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
-                                                       L.v, L.Y, M, L.d_out, L.d_in, nullptr, 0, s);
+                                                       L.v, L.Y, M, L.d_out, L.d_in, PrefillSplit{false, nullptr}, s);
         }
     }
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
@@ -566,9 +566,9 @@ int pdelta_pack_group(const void* W_f, const void* W_b, int64_t d_out, int64_t d
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 
-int pdelta_linear_group_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
-                           int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
-                           void* workspace, size_t workspace_bytes, void* stream)
+static int linear_group_common(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
+                               int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
+                               bool may_split, void* workspace, size_t workspace_bytes, void* stream)
 {
     using namespace pdelta;
     const TuneScope tune_scope;
@@ -592,7 +592,7 @@ int pdelta_linear_group_ws(const void* X, const void* W_b, const uint32_t* B_pac
     const int rc = M <= kSkinnyMaxM ? launch_linear_skinny_group(x_dtype, y_dtype, X, W_b, B_packed, v, Y, M, d_out,
                                                                  d_in, v_stride, g_shift, s)
                                     : launch_linear_gemm_group(x_dtype, y_dtype, X, W_b, B_packed, v, Y, M, d_out,
-                                                               d_in, v_stride, g_shift, workspace, workspace_bytes, s);
+                                                               d_in, v_stride, g_shift, PrefillSplit{may_split, workspace}, s);
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
 }
 
@@ -600,8 +600,16 @@ int pdelta_linear_group(const void* X, const void* W_b, const uint32_t* B_packed
                         int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
                         void* stream)
 {
-    return pdelta_linear_group_ws(X, W_b, B_packed, v, group, shared_rows, Y, M, d_out, d_in, x_dtype, y_dtype, nullptr, 0,
-                                  stream);
+    return linear_group_common(X, W_b, B_packed, v, group, shared_rows, Y, M, d_out, d_in, x_dtype, y_dtype, false, nullptr, 0,
+                               stream);
+}
+
+int pdelta_linear_group_ws(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group,
+                           int shared_rows, void* Y, int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int y_dtype,
+                           void* workspace, size_t workspace_bytes, void* stream)
+{
+    return linear_group_common(X, W_b, B_packed, v, group, shared_rows, Y, M, d_out, d_in, x_dtype, y_dtype, true, workspace,
+                               workspace_bytes, stream);
 }
 
 int pdelta_patch_group(const void* W_b, const uint32_t* B_packed, const uint16_t* v, int64_t group, int shared_rows,

@@ -46,10 +46,13 @@ int launch_linear_skinny(int x_dtype, int y_dtype, int axis, const void* X, cons
 int launch_linear_skinny_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                                const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                                int64_t d_out, int64_t d_in, int v_stride, int g_shift, hipStream_t stream);
+// Prefill: may tiles be computed in parts of d_in, and the memory for their sums (linear_gemm_workspace_bytes).
+// Without the memory the same sums are formed by one workgroup per tile.
+struct PrefillSplit { bool allowed; void* workspace; };
 int launch_linear_gemm_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                              const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, void* workspace,
-                             size_t workspace_bytes, hipStream_t stream);
+                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, PrefillSplit ps,
+                             hipStream_t stream);
 int launch_patch_group(int w_dtype, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                        void* W_out, int64_t d_out, int64_t d_in, int v_stride, int g_shift,
                        hipStream_t stream);
@@ -81,18 +84,17 @@ size_t grad_v_split_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int 
 int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint32_t* B_packed, float* grad,
                   int64_t M, int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
-// Prefill-shaped layer (many tokens): MFMA tile kernel.  workspace: nullptr with 0 bytes, or at least
-// linear_gemm_workspace_bytes.
+// Prefill-shaped layer (many tokens): MFMA tile kernel.
 size_t linear_gemm_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype);
 int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                        const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                       int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream);
+                       int64_t d_out, int64_t d_in, PrefillSplit ps, hipStream_t stream);
 
 // The same on 256 x 256 tiles with direct loads into LDS; axis 2: blockwise scales.  The first `whole`
 // tiles are computed in one go, the other `split` ones in `parts` pieces of d_in each, whose fp32
 // sums go through the workspace.  parts = 0: another kernel is the better one, or the only one.
 struct BigSplit { int whole, split, parts; };
-BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, size_t workspace_bytes);
+BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed);
 int launch_linear_gemm_big(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                            const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M, int64_t d_out,
                            int64_t d_in, int v_stride, int g_shift, void* workspace, BigSplit sp, hipStream_t stream);

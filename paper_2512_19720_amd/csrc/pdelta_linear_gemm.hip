@@ -533,22 +533,35 @@ struct SmallRegs {
     uint32_t sb[2], vg[2];               // vg: grouped mode, the step's scale per W row
 };
 
-template <int XDT, int AXIS, int DEPTH>
+//
+// CUT: the split tiles of a 256 x 256 call that has no memory for the parts' sums.  A block of this kernel takes 64 x
+// 64 outputs of such a tile and adds the parts itself: each starts from zero and is added to the ones before, so
+// an output has the same bits as with the workspace.  Repeated inputs, bf16 row, with the workspace / without / the
+// kernels that do not split: 777 x 4096 x 11008 115 / 208 / 196 us, 2048 x 11008 x 4096 237 / 273 / 225.
+template <int XDT, int AXIS, int DEPTH, bool CUT>
 __global__ void __launch_bounds__(256, 2)
 linear_gemm_small_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
                          const uint32_t* __restrict__ B_packed, const uint16_t* __restrict__ v,
                          void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int m_tiles,
-                         int n_tiles, int v_stride, int g_shift)
+                         int n_tiles, int v_stride, int g_shift, int whole, int parts)
 {
     constexpr int BM = 64, BN = 64, ROWS = 32, Q = 2;
     constexpr int XS = BM * kGemmLDK, STAGE = (BM + BN) * kGemmLDK;               // halves
     __shared__ __attribute__((aligned(16))) uint16_t lds[2 * STAGE];              // 36,864 bytes
 
-    const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    const int tile_n = (local / m_tiles) * kXcds + xcd;
-    const int tile_m = local % m_tiles;
-    if (tile_n >= n_tiles) return;       // whole workgroup
-    const int n0 = tile_n * BN, m0 = tile_m * BM;
+    int n0, m0;
+    if constexpr (CUT) {                 // m_tiles: of 256 tokens
+        const int tile = whole + (int)blockIdx.x / 16, sub = blockIdx.x % 16;
+        m0 = tile % m_tiles * 256 + (sub & 3) * BM;
+        n0 = tile / m_tiles * 256 + (sub >> 2) * BN;
+        if (m0 >= M || n0 >= d_out) return;               // whole workgroup
+    } else {
+        const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
+        const int tile_n = (local / m_tiles) * kXcds + xcd;
+        const int tile_m = local % m_tiles;
+        if (tile_n >= n_tiles) return;   // whole workgroup
+        n0 = tile_n * BN, m0 = tile_m * BM;
+    }
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -633,6 +646,14 @@ linear_gemm_small_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
         for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks], b[ks], acc, 0, 0, 0);
     };
 
+    // parts begin at multiples of 128 inputs, as in linear_gemm_big_kernel
+    float16v total;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) total[r] = 0.f;
+    int part = 0;
+    auto part_end = [&](int p) { return (int)((int64_t)(K / 128) * (p + 1) / parts) * 2; };
+    int next = CUT ? part_end(0) : 0;
+
     const int n_steps = K / kGemmBK;
     SmallRegs G[DEPTH];
 #pragma unroll
@@ -651,6 +672,11 @@ linear_gemm_small_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
                 uint16_t* rd = lds + (s & 1) * STAGE;
                 uint16_t* wr = lds + ((s + 1) & 1) * STAGE;
                 multiply(rd);
+                if (CUT && s + 1 == next) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { total[r] += acc[r]; acc[r] = 0.f; }
+                    next = part_end(++part);
+                }
                 if (s + 1 < n_steps) convert(G[(d + 1) % DEPTH], wr);
             }
             __syncthreads();
@@ -663,9 +689,10 @@ linear_gemm_small_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
         const int tok = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
         if (tok < M && o < d_out) {
             const int64_t yi = (int64_t)tok * d_out + o;
-            if (y_dtype == kF32) store_y<kF32>(Y, yi, acc[r]);
-            else if (y_dtype == kBF16) store_y<kBF16>(Y, yi, acc[r]);
-            else store_y<kF16>(Y, yi, acc[r]);
+            const float val = CUT ? total[r] : acc[r];
+            if (y_dtype == kF32) store_y<kF32>(Y, yi, val);
+            else if (y_dtype == kBF16) store_y<kBF16>(Y, yi, val);
+            else store_y<kF16>(Y, yi, val);
         }
     }
 }
@@ -679,9 +706,26 @@ static int launch_gemm_small(const void* X, const void* W_b, const uint32_t* B_p
     const int n_groups = (n_tiles + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)((int64_t)n_groups * kXcds * m_tiles));
     // four steps in flight (eight were measured too: 3-10 % slower, they halve the occupancy)
-    hipLaunchKernelGGL((linear_gemm_small_kernel<XDT, AXIS, 4>), grid, dim3(256), 0, stream,
+    hipLaunchKernelGGL((linear_gemm_small_kernel<XDT, AXIS, 4, false>), grid, dim3(256), 0, stream,
                        (const uint16_t*)X, (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out,
-                       (int)d_in, y_dtype, m_tiles, n_tiles, v_stride, g_shift);
+                       (int)d_in, y_dtype, m_tiles, n_tiles, v_stride, g_shift, 0, 1);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// A call on 256 x 256 tiles: the split ones in parts through the workspace, or without one with the same sums.
+template <int XDT, int AXIS>
+static int launch_gemm_tiles256(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y,
+                                int64_t M, int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift,
+                                void* workspace, BigSplit sp, hipStream_t stream)
+{
+    if (sp.split == 0 || workspace != nullptr)
+        return launch_linear_gemm_big(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, workspace, sp, stream);
+    if (sp.whole > 0 && launch_linear_gemm_big(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, nullptr,
+                                               BigSplit{sp.whole, 0, 1}, stream) != 0)
+        return -1;
+    hipLaunchKernelGGL((linear_gemm_small_kernel<XDT, AXIS, 4, true>), dim3((unsigned)sp.split * 16), dim3(256), 0, stream,
+                       (const uint16_t*)X, (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype,
+                       (int)((M + 255) / 256), 0, v_stride, g_shift, sp.whole, sp.parts);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -703,13 +747,13 @@ static int launch_gemm(const void* X, const void* W_b, const uint32_t* B_packed,
 template <int XDT, int AXIS>
 static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                           void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
-                          void* workspace, size_t workspace_bytes, hipStream_t stream)
+                          PrefillSplit ps, hipStream_t stream)
 {
-    // 256 x 256 tiles with direct loads (and split tiles where there is a workspace) when they are
+    // 256 x 256 tiles with direct loads (and split tiles where the call may split) when they are
     // expected to be faster; see linear_gemm_big_split.
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, workspace_bytes);
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, ps.allowed);
     if (sp.parts > 0)
-        return launch_linear_gemm_big(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, 0, 31, workspace, sp, stream);
+        return launch_gemm_tiles256<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps.workspace, sp, stream);
     // Under-filled grids (at most 128 tiles of 256 x 128, i.e. a few hundred tokens): the
     // small-tile kernel is 2-3x faster there; from about 1000 tokens on the big tiles win.
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
@@ -732,13 +776,13 @@ static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_pack
 template <int XDT>
 static int launch_gemm_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y,
                              int64_t M, int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift,
-                             void* workspace, size_t workspace_bytes, hipStream_t stream)
+                             PrefillSplit ps, hipStream_t stream)
 {
-    // 256 x 256 tiles with direct loads (and split tiles where there is a workspace) when they are
+    // 256 x 256 tiles with direct loads (and split tiles where the call may split) when they are
     // expected to be faster; see linear_gemm_big_split.
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, workspace_bytes);
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, ps.allowed);
     if (sp.parts > 0)
-        return launch_linear_gemm_big(XDT, y_dtype, 2, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, workspace, sp, stream);
+        return launch_gemm_tiles256<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps.workspace, sp, stream);
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int small = tune_value("gemm_small", -1);
     if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128)))
@@ -752,25 +796,23 @@ static int launch_gemm_group(const void* X, const void* W_b, const uint32_t* B_p
 
 int launch_linear_gemm_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                              const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, void* workspace,
-                             size_t workspace_bytes, hipStream_t stream)
+                             int64_t d_out, int64_t d_in, int v_stride, int g_shift, PrefillSplit ps,
+                             hipStream_t stream)
 {
     if (x_dtype == kBF16)
-        return launch_gemm_group<kBF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, workspace,
-                                        workspace_bytes, stream);
-    return launch_gemm_group<kF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, workspace,
-                                   workspace_bytes, stream);
+        return launch_gemm_group<kBF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream);
+    return launch_gemm_group<kF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream);
 }
 
 int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                        const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                       int64_t d_out, int64_t d_in, void* workspace, size_t workspace_bytes, hipStream_t stream)
+                       int64_t d_out, int64_t d_in, PrefillSplit ps, hipStream_t stream)
 {
     if (x_dtype == kBF16)
-        return axis == 0 ? launch_gemm_bm<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream)
-                         : launch_gemm_bm<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream);
-    return axis == 0 ? launch_gemm_bm<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream)
-                     : launch_gemm_bm<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, workspace, workspace_bytes, stream);
+        return axis == 0 ? launch_gemm_bm<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream)
+                         : launch_gemm_bm<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream);
+    return axis == 0 ? launch_gemm_bm<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream)
+                     : launch_gemm_bm<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream);
 }
 
 // Measurement builds of the pipelined kernel (bf16 operands, row scales) with parts of its loop

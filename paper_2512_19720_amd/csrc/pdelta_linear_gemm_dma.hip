@@ -26,8 +26,8 @@
 // 8 (p ^ ((r >> 1) & 7)) .. +7, so that 16 consecutive rows of one fragment read touch all 64 banks once.
 // The permutation is applied by choosing which 16 bytes each lane loads.
 //
-// Work split: tiles that fill whole rounds of the 256 CUs are computed in one go; the remaining ones, when
-// there is a workspace, in parts of d_in, whose sums a second kernel adds in the order of d_in.
+// Work split: tiles that fill whole rounds of the 256 CUs are computed in one go; the remaining ones, in the
+// calls that may split, in parts of d_in, whose sums a second kernel adds in the order of d_in.
 // Workgroup w runs on XCD w % 8; each XCD takes a contiguous range of the whole tiles (token tiles of one
 // output-row tile first, so that its CUs share W_b panels in its L2), then one of the parts.
 #include <algorithm>
@@ -356,7 +356,7 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // 11008 blockwise (64 tiles in 4 parts) 117 against 236, 1024 x 4096 x 4096 58 against 82; 256 x 512 x 8192 (2 tiles
 // in 16 parts) 36 against 58.  Below the line: 256 x 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 26, 512 x 300 x
 // 3968 32 against 26, 251 x 4096 x 4096 32 against 30.
-BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, size_t workspace_bytes)
+BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed)
 {
     const BigSplit none{0, 0, 0};
     const int forced = tune_value("gemm_big", -1);    // 0: never; n > 0: in n parts (1: whole tiles only)
@@ -367,7 +367,7 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     if (tiles > (1 << 24)) return none;
     const int rest = (int)(tiles % 256), whole = (int)(tiles - rest);
     const double n = (double)(d_in / kBigBK), step = x_dtype == kBF16 ? 1.95 : 1.75;
-    auto fits = [&](int p) { return p <= d_in / kBigUnitK && (size_t)rest * p <= 256 && (size_t)rest * p * kPartBytes <= workspace_bytes; };
+    auto fits = [&](int p) { return split_allowed && p <= d_in / kBigUnitK && rest * p <= 256; };
     if (forced == 1 || (forced > 1 && !fits(forced))) return BigSplit{(int)tiles, 0, 1};
     if (forced > 1) return rest > 0 ? BigSplit{whole, rest, forced} : BigSplit{whole, 0, 1};
     double best = 8 + (double)((tiles + 255) / 256) * n * step;
@@ -388,7 +388,7 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
 
 size_t linear_gemm_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype)
 {
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, x_dtype, ~(size_t)0);
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, x_dtype, true);
     return (size_t)sp.split * sp.parts * kPartBytes;
 }
 
