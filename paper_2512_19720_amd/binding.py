@@ -206,8 +206,8 @@ def _prefill_workspace(M: int, d_out: int, d_in: int, x: torch.Tensor):
     need = lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[x.dtype])
     if need == 0:
         return None
-    try:
-        return torch.empty(need, dtype=torch.uint8, device=x.device)
+    try:                                   # on the device whose stream runs the call: it is released when the call returns
+        return torch.empty(need, dtype=torch.uint8, device="cuda")
     except torch.cuda.OutOfMemoryError:
         return None
 
