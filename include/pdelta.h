@@ -234,6 +234,16 @@ int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* lay
                         int32_t n_layers, int64_t M, int x_dtype, int y_dtype, void* stream);
 
 /*
+ * The same with the workspace of pdelta_linear_ws (same rules), which the layers use one after another:
+ * every layer computes exactly what pdelta_linear_ws computes.
+ * pdelta_linear_batch_workspace_bytes: the largest pdelta_linear_workspace_bytes of the layers.
+ */
+size_t pdelta_linear_batch_workspace_bytes(const pdelta_layer* layers_host, int32_t n_layers, int64_t M, int x_dtype);
+
+int pdelta_linear_batch_ws(const pdelta_layer* layers_host, const pdelta_layer* layers_device, int32_t n_layers,
+                           int64_t M, int x_dtype, int y_dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Merge the deltas of many layers in one launch: the paper's "Model-wide application from a
  * saved delta file" (every module of the model is patched; Eq. 1 per layer).  Each layer computes
  * exactly what pdelta_patch computes.  Descriptors are pdelta_layer records planned with

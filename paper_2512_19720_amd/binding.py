@@ -80,6 +80,10 @@ def lib() -> ctypes.CDLL:
         L.pdelta_linear_batch_plan.argtypes = [ctypes.POINTER(Layer), ctypes.c_int32]
         L.pdelta_linear_batch.restype = i32
         L.pdelta_linear_batch.argtypes = [ctypes.POINTER(Layer), vp, ctypes.c_int32, i64, i32, i32, vp]
+        L.pdelta_linear_batch_workspace_bytes.restype = sz
+        L.pdelta_linear_batch_workspace_bytes.argtypes = [ctypes.POINTER(Layer), ctypes.c_int32, i64, i32]
+        L.pdelta_linear_batch_ws.restype = i32
+        L.pdelta_linear_batch_ws.argtypes = [ctypes.POINTER(Layer), vp, ctypes.c_int32, i64, i32, i32, vp, sz, vp]
         L.pdelta_patch_batch.restype = i32
         L.pdelta_patch_batch.argtypes = [ctypes.POINTER(Layer), vp, ctypes.c_int32, i32, vp]
         L.pdelta_pack_batch_plan.restype = i32
@@ -200,10 +204,9 @@ _DTYPE_CODE = {torch.float16: F16, torch.bfloat16: BF16, torch.float32: F32}
 _DECODE_MAX_TOKENS = 64
 
 
-def _prefill_workspace(M: int, d_out: int, d_in: int, x: torch.Tensor):
-    """Workspace of a prefill call, or None when the call uses none or the memory for it is not there (the
-    result is the same without, bit for bit, and takes longer)."""
-    need = lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[x.dtype])
+def _prefill_workspace(need: int):
+    """Workspace of a prefill call that uses ``need`` bytes, or None when that is 0 or the memory for it is not
+    there (the result is the same without, bit for bit, and takes longer)."""
     if need == 0:
         return None
     try:                                   # on the device whose stream runs the call: it is released when the call returns
@@ -220,7 +223,7 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
-        ws = _prefill_workspace(M, d_out, d_in, X)
+        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[X.dtype]))
         rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                     ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
                                     _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], ws.data_ptr() if ws is not None else None,
@@ -303,8 +306,14 @@ def pdelta_linear_batch_plan(layers, out_dtype=None) -> BatchPlan:
 
 def pdelta_linear_batch(plan: BatchPlan):
     """Run every layer of the plan (one launch when the layers fit the batched decode kernel)."""
-    rc = lib().pdelta_linear_batch(plan.host, plan.device.data_ptr(), len(plan), plan.M, plan.x_dtype,
-                                   plan.y_dtype, _stream())
+    if plan.M > _DECODE_MAX_TOKENS:
+        ws = _prefill_workspace(lib().pdelta_linear_batch_workspace_bytes(plan.host, len(plan), plan.M, plan.x_dtype))
+        rc = lib().pdelta_linear_batch_ws(plan.host, plan.device.data_ptr(), len(plan), plan.M, plan.x_dtype, plan.y_dtype,
+                                          ws.data_ptr() if ws is not None else None, ws.numel() if ws is not None else 0,
+                                          _stream())
+    else:
+        rc = lib().pdelta_linear_batch(plan.host, plan.device.data_ptr(), len(plan), plan.M, plan.x_dtype,
+                                       plan.y_dtype, _stream())
     _check(rc, "pdelta_linear_batch")
     return plan.Y
 
@@ -498,7 +507,9 @@ def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=Non
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     x_dtype = dtype_code(X.dtype)
-    ws = _prefill_workspace(M, d_out, d_in, X) if M > _DECODE_MAX_TOKENS and X.is_cuda else None
+    ws = None
+    if M > _DECODE_MAX_TOKENS and X.is_cuda:
+        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype))
     rc = lib().pdelta_linear_group_ws(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                       group, shared, _dev(out, "Y") or None, M, d_out, d_in, x_dtype,
                                       dtype_code(out.dtype), ws.data_ptr() if ws is not None else None,

@@ -6,6 +6,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "pdelta_host.h"
 
 namespace pdelta {
@@ -387,8 +389,9 @@ int pdelta_linear_batch_plan(pdelta_layer* layers_host, int32_t n_layers)
     return PDELTA_OK;
 }
 
-int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* layers_device,
-                        int32_t n_layers, int64_t M, int x_dtype, int y_dtype, void* stream)
+static int linear_batch_common(const pdelta_layer* layers_host, const pdelta_layer* layers_device, int32_t n_layers,
+                               int64_t M, int x_dtype, int y_dtype, bool may_split, void* workspace,
+                               size_t workspace_bytes, void* stream)
 {
     using namespace pdelta;
     const TuneScope tune_scope;
@@ -401,6 +404,9 @@ int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* lay
         const pdelta_layer& L = layers_host[l];
         if (const int rc = linear_check(L.X, L.W_b, L.B_packed, L.v, L.Y, M, L.d_out, L.d_in, x_dtype,
                                         y_dtype, L.axis))
+            return rc;
+        if (const int rc = linear_workspace_check(L.X, L.W_b, L.B_packed, L.v, (size_t)(L.axis == PDELTA_ROW ? L.d_out : L.d_in) * 2,
+                                                  L.Y, M, L.d_out, L.d_in, x_dtype, y_dtype, workspace, workspace_bytes))
             return rc;
         if (L.first_block != (int32_t)first) return PDELTA_EINVAL;     // not planned, or edited
         first += (L.d_out + 15) / 16;
@@ -417,10 +423,30 @@ int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* lay
             rc = M <= kSkinnyMaxM ? launch_linear_skinny(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
                                                          L.v, L.Y, M, L.d_out, L.d_in, s)
                                   : launch_linear_gemm(x_dtype, y_dtype, L.axis, L.X, L.W_b, L.B_packed,
-                                                       L.v, L.Y, M, L.d_out, L.d_in, PrefillSplit{false, nullptr}, s);
+                                                       L.v, L.Y, M, L.d_out, L.d_in, PrefillSplit{may_split, workspace}, s);
         }
     }
     return rc == 0 ? PDELTA_OK : PDELTA_EHIP;
+}
+
+int pdelta_linear_batch(const pdelta_layer* layers_host, const pdelta_layer* layers_device,
+                        int32_t n_layers, int64_t M, int x_dtype, int y_dtype, void* stream)
+{
+    return linear_batch_common(layers_host, layers_device, n_layers, M, x_dtype, y_dtype, false, nullptr, 0, stream);
+}
+
+size_t pdelta_linear_batch_workspace_bytes(const pdelta_layer* layers_host, int32_t n_layers, int64_t M, int x_dtype)
+{
+    size_t need = 0;
+    for (int32_t l = 0; layers_host != nullptr && l < n_layers; ++l)
+        need = std::max(need, pdelta_linear_workspace_bytes(M, layers_host[l].d_out, layers_host[l].d_in, x_dtype));
+    return need;
+}
+
+int pdelta_linear_batch_ws(const pdelta_layer* layers_host, const pdelta_layer* layers_device, int32_t n_layers, int64_t M,
+                           int x_dtype, int y_dtype, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return linear_batch_common(layers_host, layers_device, n_layers, M, x_dtype, y_dtype, true, workspace, workspace_bytes, stream);
 }
 
 int pdelta_linear_variants(const void* X, const void* W_b, const pdelta_variant* variants_host,

@@ -15,8 +15,28 @@ def test_prefill_workspace_belongs_to_the_device_whose_stream_runs_the_call(monk
 
     monkeypatch.setattr(torch, "empty", empty)
 
-    class OnAnotherDevice:
-        dtype, device = torch.float16, torch.device("cuda:1")
-
-    assert pd._prefill_workspace(1024, 4096, 4096, OnAnotherDevice) == "workspace"
+    assert pd._prefill_workspace(1024) == "workspace"
     assert seen == [torch.device("cuda")]                     # no index: the current device
+
+
+def test_batch_workspace_rules():
+    L, A, M = pd.lib(), 1 << 40, 1024
+    GB = 1 << 30
+    arr = (pd.Layer * 2)()
+    for k, (d_out, d_in) in enumerate([(256, 640), (4096, 4096)]):
+        base = A + k * 8 * GB
+        arr[k] = pd.Layer(base, base + GB, base + 2 * GB, base + 3 * GB, base + 4 * GB, d_out, d_in, k, -1)
+    assert L.pdelta_linear_batch_plan(arr, 2) == pd.OK
+    need = L.pdelta_linear_batch_workspace_bytes(arr, 2, M, pd.F16)
+    assert need == L.pdelta_linear_workspace_bytes(M, 4096, 4096, pd.F16) > 0
+    assert L.pdelta_linear_batch_workspace_bytes(arr, 2, 16, pd.F16) == 0            # decode
+    assert L.pdelta_linear_batch_workspace_bytes(None, 2, M, pd.F16) == 0
+
+    def call(ws, n):
+        return L.pdelta_linear_batch_ws(arr, A + 32 * GB, 2, M, pd.F16, pd.F16, ws, n, None)
+
+    assert call(A + 33 * GB, need - 1) == pd.EWORKSPACE
+    assert call(A + 33 * GB + 8, need) == pd.EALIGN
+    assert call(None, need) == pd.EINVAL
+    for k in range(5):
+        assert call(A + 8 * GB + k * GB, need) == pd.EINVAL                          # on a tensor of the second layer

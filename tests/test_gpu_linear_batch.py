@@ -70,6 +70,22 @@ def test_layer_by_layer_fallback_gives_the_same_results(M, shapes):
     check_batch(cases, plan, Ys, f"fallback M={M}", torch.float32)
 
 
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_prefill_layers_are_computed_as_single_calls_are(dtype):
+    """Shapes whose single call is computed in parts of d_in (1024 x 4096 x 4096: 4) and one that is not."""
+    lib, M = pd.lib(), 1024
+    shapes = [(4096, 4096, orc.ROW), (264, 640, orc.COL), (512, 8192, orc.COL)]
+    need = [lib.pdelta_linear_workspace_bytes(M, o, k, pd.F16 if dtype == synth.F16 else pd.BF16) for o, k, _ in shapes]
+    assert need[0] > 0 and need[1] == 0 and need[2] > 0
+    cases, plan = build_batch(shapes, M, dtype, synth.seed_for(3, 640), torch.float32)
+    assert lib.pdelta_linear_batch_workspace_bytes(plan.host, 3, M, plan.x_dtype) == max(need)
+    for Y in plan.Y:
+        Y.fill_(float("nan"))
+    Ys = pd.pdelta_linear_batch(plan)
+    torch.cuda.synchronize()
+    check_batch(cases, plan, Ys, f"prefill dt={dtype}", torch.float32)
+
+
 def test_one_block_of_the_7b_stack_batch1():
     # q, k, v, o, gate, up, down of one block with the benchmark's axis mix, each with its own X and Y
     shapes = [(4096, 4096, orc.ROW)] * 2 + [(4096, 4096, orc.COL)] * 2 + \
