@@ -217,8 +217,9 @@ def _prefill_workspace(need: int):
 
 def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
     M, d_in = X.shape
-    d_out = W_b.shape[0]
-    if W_b.shape[1] != d_in or X.dtype != W_b.dtype:
+    w_shape = W_b.shape                    # read once: a small decode call is host time only, and this is 0.1 us of it
+    d_out = w_shape[0]
+    if w_shape[1] != d_in or X.dtype != W_b.dtype:
         raise ValueError("X and W_b must agree in d_in and dtype")
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)

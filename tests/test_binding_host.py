@@ -40,3 +40,36 @@ def test_batch_workspace_rules():
     assert call(None, need) == pd.EINVAL
     for k in range(5):
         assert call(A + 8 * GB + k * GB, need) == pd.EINVAL                          # on a tensor of the second layer
+
+
+def test_a_decode_call_is_one_library_call(monkeypatch):
+    """The smallest decode call is host time only: one call into the library and one look at each shape, whatever
+    the prefill path needs beside that."""
+    class FakeTensor:
+        def __init__(self, *shape):
+            self.size, self.dtype, self.is_cuda, self.reads = shape, torch.float16, True, 0
+
+        @property
+        def shape(self):
+            self.reads += 1
+            return self.size
+
+        def is_contiguous(self):
+            return True
+
+        def data_ptr(self):
+            return 16
+
+    calls = []
+
+    class FakeLibrary:
+        def __getattr__(self, name):
+            return lambda *args: calls.append(name) or pd.OK
+
+    monkeypatch.setattr(pd, "_lib", FakeLibrary())
+    monkeypatch.setattr(pd, "_stream", lambda: 0)
+    for fn in (pd.pdelta_linear_row, pd.pdelta_linear_col):
+        X, W_b, Y = FakeTensor(4, 512), FakeTensor(256, 512), FakeTensor(4, 256)
+        assert fn(X, W_b, FakeTensor(256, 16), FakeTensor(256), out=Y) is Y
+        assert X.reads == 1 and W_b.reads == 1
+    assert calls == ["pdelta_linear_row", "pdelta_linear_col"]
