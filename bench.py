@@ -431,7 +431,7 @@ def main() -> int:
         Bg = torch.randint(-2 ** 31, 2 ** 31 - 1, (Ng, Kg // 32), dtype=torch.int32, device=dev)
         res = {"workload": "dL/dv from dY: 2048 tokens, 4096 x 4096 layer, bf16 X and dY, fp32 gradient"}
         for name, axis in (("row", pd.ROW), ("col", pd.COL)):
-            ws = torch.empty(pd.pdelta_grad_v_workspace_bytes(Mg, Ng, Kg, axis), dtype=torch.uint8, device=dev)
+            ws = torch.empty(pd.pdelta_grad_v_split_workspace_bytes(Mg, Ng, Kg, axis), dtype=torch.uint8, device=dev)
             outg = torch.empty(Ng if axis == pd.ROW else Kg, dtype=torch.float32, device=dev)
             fn = lambda: pd.pdelta_grad_v(Xg, dYg, Bg, axis, out=outg, workspace=ws)
             timed(fn, 3)

@@ -204,9 +204,16 @@ _DTYPE_CODE = {torch.float16: F16, torch.bfloat16: BF16, torch.float32: F32}
 _DECODE_MAX_TOKENS = 64
 
 
-def _prefill_workspace(need: int):
-    """Workspace of a prefill call that uses ``need`` bytes, or None when that is 0 or the memory for it is not
-    there (the result is the same without, bit for bit, and takes longer)."""
+def pdelta_linear_workspace_bytes(M: int, d_out: int, d_in: int, dtype: torch.dtype) -> int:
+    """Bytes of the ``workspace`` that a linear call of this shape uses (0: none)."""
+    return int(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, dtype_code(dtype)))
+
+
+def _prefill_workspace(need: int, given: torch.Tensor | None = None):
+    """Workspace of a prefill call that uses ``need`` bytes: the caller's own (empty: none), else one of this call's.
+    None when none is used or the memory is not there: the result is the same, bit for bit, and takes longer."""
+    if given is not None:
+        return given if given.numel() > 0 else None
     if need == 0:
         return None
     try:                                   # on the device whose stream runs the call: it is released when the call returns
@@ -215,7 +222,11 @@ def _prefill_workspace(need: int):
         return None
 
 
-def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
+def _workspace_args(ws):
+    return (None, 0) if ws is None else (_dev(ws, "workspace"), ws.numel() * ws.element_size())
+
+
+def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype, workspace):
     M, d_in = X.shape
     w_shape = W_b.shape                    # read once: a small decode call is host time only, and this is 0.1 us of it
     d_out = w_shape[0]
@@ -224,11 +235,10 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
-        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[X.dtype]))
+        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[X.dtype]), workspace)
         rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                     ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
-                                    _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], ws.data_ptr() if ws is not None else None,
-                                    ws.numel() if ws is not None else 0, _stream())
+                                    _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], *_workspace_args(ws), _stream())
         _check(rc, fn_name)
         return out
     fn = getattr(_lib, fn_name) if _lib is not None else getattr(lib(), fn_name)
@@ -239,14 +249,17 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype):
     return out
 
 
-def pdelta_linear_row(X, W_b, B_packed, v_row, out=None, out_dtype=None):
-    """Y = X W_b^T + v_row (.) (X B^T), v_row fp16 [d_out]."""
-    return _linear("pdelta_linear_row", X, W_b, B_packed, v_row, out, out_dtype)
+def pdelta_linear_row(X, W_b, B_packed, v_row, out=None, out_dtype=None, workspace=None):
+    """Y = X W_b^T + v_row (.) (X B^T), v_row fp16 [d_out].
+
+    Above 64 tokens a call may use up to 64 MiB of scratch memory (``pdelta_linear_workspace_bytes``), allocated for the
+    call unless ``workspace`` gives it; an empty tensor there, or no free memory, means the same result more slowly."""
+    return _linear("pdelta_linear_row", X, W_b, B_packed, v_row, out, out_dtype, workspace)
 
 
-def pdelta_linear_col(X, W_b, B_packed, v_col, out=None, out_dtype=None):
-    """Y = X W_b^T + (X (.) v_col) B^T, v_col fp16 [d_in]."""
-    return _linear("pdelta_linear_col", X, W_b, B_packed, v_col, out, out_dtype)
+def pdelta_linear_col(X, W_b, B_packed, v_col, out=None, out_dtype=None, workspace=None):
+    """Y = X W_b^T + (X (.) v_col) B^T, v_col fp16 [d_in]; ``workspace`` as in ``pdelta_linear_row``."""
+    return _linear("pdelta_linear_col", X, W_b, B_packed, v_col, out, out_dtype, workspace)
 
 
 def pdelta_patch(W_b, B_packed, v, axis: int, out=None):
@@ -305,13 +318,18 @@ def pdelta_linear_batch_plan(layers, out_dtype=None) -> BatchPlan:
     return BatchPlan(host, device, tensors, M, dtype_code(x_dtype), dtype_code(y_dtype))
 
 
-def pdelta_linear_batch(plan: BatchPlan):
-    """Run every layer of the plan (one launch when the layers fit the batched decode kernel)."""
+def pdelta_linear_batch_workspace_bytes(plan: BatchPlan) -> int:
+    """Bytes of the ``workspace`` that ``pdelta_linear_batch`` uses for this plan (0: none)."""
+    return int(lib().pdelta_linear_batch_workspace_bytes(plan.host, len(plan), plan.M, plan.x_dtype))
+
+
+def pdelta_linear_batch(plan: BatchPlan, workspace=None):
+    """Run every layer of the plan (one launch when the layers fit the batched decode kernel); ``workspace`` as in
+    ``pdelta_linear_row``, shared by the layers."""
     if plan.M > _DECODE_MAX_TOKENS:
-        ws = _prefill_workspace(lib().pdelta_linear_batch_workspace_bytes(plan.host, len(plan), plan.M, plan.x_dtype))
+        ws = _prefill_workspace(pdelta_linear_batch_workspace_bytes(plan), workspace)
         rc = lib().pdelta_linear_batch_ws(plan.host, plan.device.data_ptr(), len(plan), plan.M, plan.x_dtype, plan.y_dtype,
-                                          ws.data_ptr() if ws is not None else None, ws.numel() if ws is not None else 0,
-                                          _stream())
+                                          *_workspace_args(ws), _stream())
     else:
         rc = lib().pdelta_linear_batch(plan.host, plan.device.data_ptr(), len(plan), plan.M, plan.x_dtype,
                                        plan.y_dtype, _stream())
@@ -453,6 +471,11 @@ def pdelta_grad_v_workspace_bytes(M: int, d_out: int, d_in: int, axis: int) -> i
     return int(lib().pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis))
 
 
+def pdelta_grad_v_split_workspace_bytes(M: int, d_out: int, d_in: int, axis: int) -> int:
+    """Bytes with which calls of few tokens run fast (what ``pdelta_grad_v`` allocates); the size above also works."""
+    return int(lib().pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis))
+
+
 def pdelta_grad_v(X, dY, B_packed, axis: int, out=None, workspace: torch.Tensor | None = None):
     """dL/dv (fp32) for upstream gradient dY: [d_out] in row mode, [d_in] in column mode."""
     M, d_in = X.shape
@@ -462,7 +485,7 @@ def pdelta_grad_v(X, dY, B_packed, axis: int, out=None, workspace: torch.Tensor 
     if out is None:
         out = torch.empty(d_out if axis == ROW else d_in, dtype=torch.float32, device=X.device)
     if workspace is None:
-        workspace = torch.empty(max(lib().pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis), 16),
+        workspace = torch.empty(max(pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis), 16),
                                 dtype=torch.uint8, device=X.device)
     rc = lib().pdelta_grad_v(_dev(X, "X") or None, _dev(dY, "dY") or None, _dev(B_packed, "B_packed"), axis,
                              _dev(out, "grad_v"), M, d_out, d_in, dtype_code(X.dtype), _dev(workspace, "workspace"),
@@ -499,8 +522,8 @@ def pdelta_pack_group(W_f: torch.Tensor, W_b: torch.Tensor, group: int, shared_r
     return B, v
 
 
-def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=None):
-    """Y = X W_hat^T with W_hat = W_b + scale(o, i) B and blockwise scales v."""
+def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=None, workspace=None):
+    """Y = X W_hat^T with W_hat = W_b + scale(o, i) B and blockwise scales v; ``workspace`` as in ``pdelta_linear_row``."""
     M, d_in = X.shape
     d_out, _, shared = _group_args(W_b, v, group)
     if W_b.shape[1] != d_in or X.dtype != W_b.dtype:
@@ -510,11 +533,10 @@ def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=Non
     x_dtype = dtype_code(X.dtype)
     ws = None
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
-        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype))
+        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype), workspace)
     rc = lib().pdelta_linear_group_ws(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                       group, shared, _dev(out, "Y") or None, M, d_out, d_in, x_dtype,
-                                      dtype_code(out.dtype), ws.data_ptr() if ws is not None else None,
-                                      ws.numel() if ws is not None else 0, _stream())
+                                      dtype_code(out.dtype), *_workspace_args(ws), _stream())
     _check(rc, "pdelta_linear_group")
     return out
 

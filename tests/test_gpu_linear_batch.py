@@ -78,7 +78,7 @@ def test_prefill_layers_are_computed_as_single_calls_are(dtype):
     need = [lib.pdelta_linear_workspace_bytes(M, o, k, pd.F16 if dtype == synth.F16 else pd.BF16) for o, k, _ in shapes]
     assert need[0] > 0 and need[1] == 0 and need[2] > 0
     cases, plan = build_batch(shapes, M, dtype, synth.seed_for(3, 640), torch.float32)
-    assert lib.pdelta_linear_batch_workspace_bytes(plan.host, 3, M, plan.x_dtype) == max(need)
+    assert pd.pdelta_linear_batch_workspace_bytes(plan) == max(need)
     for Y in plan.Y:
         Y.fill_(float("nan"))
     Ys = pd.pdelta_linear_batch(plan)

@@ -69,3 +69,29 @@ def test_whole_round_and_split_rest(dtype, monkeypatch):
         check_y(want, ref, f"289 tiles, kind {k}, dt={dtype}")
         got, refused = without_memory(monkeypatch, call)
         assert refused == 1 and torch.equal(got, want), f"kind {k} dt={dtype}"
+
+
+def test_a_callers_workspace(monkeypatch):
+    """The caller's workspace is the one that is used, nothing is allocated beside it, and an empty one asks for none."""
+    M, d_out, d_in = 1024, 4096, 4096
+    L = make_case(d_out, d_in, M, synth.F16, "row", 99)
+    d = L["d"]
+    vg = torch.full((d_out, d_in // 128), 1e-3, dtype=torch.float16, device=DEV)
+    need = pd.pdelta_linear_workspace_bytes(M, d_out, d_in, torch.float16)
+    own, none = torch.empty(need, dtype=torch.uint8, device=DEV), torch.empty(0, dtype=torch.uint8, device=DEV)
+    plan = pd.pdelta_linear_batch_plan([(d["X"], d["W_b"], d["B"], d["v_row"], pd.ROW)])
+    assert pd.pdelta_linear_batch_workspace_bytes(plan) == need
+    Y = torch.empty((M, d_out), dtype=torch.float16, device=DEV)
+    for call in (lambda ws: pd.pdelta_linear_row(d["X"], d["W_b"], d["B"], d["v_row"], out=Y, workspace=ws),
+                 lambda ws: pd.pdelta_linear_col(d["X"], d["W_b"], d["B"], d["v_col"], out=Y, workspace=ws),
+                 lambda ws: pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], vg, 128, out=Y, workspace=ws),
+                 lambda ws: pd.pdelta_linear_batch(plan, workspace=ws)[0]):
+        want = call(None).clone()
+        for ws in (own, none):
+            own.zero_()
+            got, refused = without_memory(monkeypatch, lambda: call(ws))
+            assert refused == 0 and torch.equal(got, want)
+            assert bool(own.any()) == (ws is own)
+        with pytest.raises(pd.PdeltaError) as e:
+            call(own[:need - 16])
+        assert e.value.status == pd.EWORKSPACE
