@@ -83,6 +83,34 @@ def test_pack_patch_and_gradient_in_a_graph():
     replay_and_compare(capture(run), outputs, expected)
 
 
+def test_calls_that_allocate_a_workspace_in_a_graph():
+    """Prefill in 16 parts of d_in, the same in a batch, and gradients in parts; every workspace is the call's own."""
+    M, d_out, d_in = 200, 512, 8192
+    assert pd.pdelta_linear_workspace_bytes(M, d_out, d_in, torch.float16) > 0
+    assert pd.pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, pd.ROW) > pd.pdelta_grad_v_workspace_bytes(M, d_out, d_in, pd.ROW)
+    L = make_case(d_out, d_in, M, synth.F16, "row", 321)
+    d = L["d"]
+    dY = synth.x_device(M, d_out, synth.F16, 322, DEV)
+    vg = torch.full((d_out, d_in // 128), 1e-3, dtype=torch.float16, device=DEV)
+    Y = [torch.empty((M, d_out), dtype=torch.float16, device=DEV) for _ in range(3)]
+    plan = pd.pdelta_linear_batch_plan([(d["X"], d["W_b"], d["B"], d["v_row"], pd.ROW), (d["X"], d["W_b"], d["B"], d["v_col"], pd.COL)])
+    g = [torch.empty(d_out, dtype=torch.float32, device=DEV), torch.empty(d_in, dtype=torch.float32, device=DEV)]
+
+    def run():
+        pd.pdelta_linear_row(d["X"], d["W_b"], d["B"], d["v_row"], out=Y[0])
+        pd.pdelta_linear_col(d["X"], d["W_b"], d["B"], d["v_col"], out=Y[1])
+        pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], vg, 128, out=Y[2])
+        pd.pdelta_linear_batch(plan)
+        pd.pdelta_grad_v(d["X"], dY, d["B"], pd.ROW, out=g[0])
+        pd.pdelta_grad_v(d["X"], dY, d["B"], pd.COL, out=g[1])
+
+    run()
+    torch.cuda.synchronize()
+    outputs = Y + list(plan.Y) + g
+    expected = [o.clone() for o in outputs]
+    replay_and_compare(capture(run), outputs, expected)
+
+
 def test_batched_entry_points_in_a_graph():
     layers = []
     for k, (d_out, d_in, axis) in enumerate([(96, 256, orc.ROW), (40, 1152, orc.COL), (256, 512, orc.ROW)]):

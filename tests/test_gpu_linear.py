@@ -98,8 +98,9 @@ def test_empty_batch_is_a_no_op():
 @pytest.mark.parametrize("shape", synth.PREFILL_SHAPES)
 @pytest.mark.parametrize("kernel", ["default", "two_per_cu"])
 def test_config2_prefill_full_size_sampled_outputs(shape, kernel, monkeypatch):
-    """bf16, M = 2048, the benchmark's launch configuration (the library's own choice of kernel,
-    which is the pipelined one, and the two-per-CU kernel forced); 600 sampled outputs, each an fp64 dot product by the
+    """bf16, M = 2048, the benchmark's launch configuration (the library's own choice of kernel: 256 x 256 tiles for
+    11008 x 4096 and 14336 x 4096, the pipelined 256 x 128 one for 4096 x 11008; and the two-per-CU kernel forced);
+    600 sampled outputs, each an fp64 dot product by the
     oracle, plus whole rows and columns of the output tile grid's corners."""
     if kernel == "two_per_cu":
         monkeypatch.setenv("PDELTA_TUNE", "gemm_pipe=0")

@@ -6,7 +6,7 @@ import torch
 from oracle import pdelta_oracle as orc
 from paper_2512_19720_amd import binding as pd
 from paper_2512_19720_amd import synth
-from parity_util import check_y, f16_dev, gpu_linear, make_case
+from parity_util import DEV, check_y, f16_dev, gpu_linear, make_case
 
 GB = 1 << 30
 
@@ -41,6 +41,26 @@ def test_blockwise_scales(group, shared, dtype, monkeypatch):
         monkeypatch.setenv("PDELTA_TUNE", f"gemm_big={parts}")
         Y = pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], v_dev, group, out_dtype=torch.float32)
         check_y(Y, ref, f"big group={group} shared={shared} dt={dtype} parts={parts}")
+
+
+# parts that begin inside a group of scales: 1280 inputs in 3 parts begin at 384 and 768, 768 in 2 at 384, 1536 in 5 at
+# 256, 512, 896 and 1152; at the groups' own ends: 1536 in 3 at 512 and 1024; and groups of 128, which no part cuts
+@pytest.mark.gpu
+@pytest.mark.parametrize("group,d_in,parts", [(256, 1280, 3), (256, 768, 2), (512, 1536, 5), (512, 1536, 3), (128, 640, 3)])
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_parts_that_begin_inside_a_group(group, d_in, parts, shared, dtype, monkeypatch):
+    M, d_out = 130, 264
+    monkeypatch.setenv("PDELTA_TUNE", f"gemm_big={parts}")
+    L = make_case(d_out, d_in, M, dtype, "row", 19 + group + d_in)
+    d = L["d"]
+    v_bits = orc.pack_group(L["dW"], L["dW"] * 0, group, shared, dtype)[1]
+    # scales that differ from group to group by more than the tolerance: one taken from a neighbour shows
+    v_dev = f16_dev(v_bits) * (1 + torch.arange(d_in // group, device=DEV) % 3).to(torch.float16)
+    v_bits = synth.torch_to_bits(v_dev)
+    Y = torch.full((M, d_out), float("nan"), dtype=torch.float32, device=DEV)
+    pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], v_dev, group, out=Y)
+    check_y(Y, orc.linear_group(L["X"], L["W_b"], L["B"], v_bits, group, dtype), f"group={group} d_in={d_in} parts={parts} shared={shared}")
 
 
 def test_workspace_rules_without_a_gpu():
