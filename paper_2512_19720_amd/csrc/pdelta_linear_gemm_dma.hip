@@ -47,6 +47,19 @@ constexpr int kBigXB = kBigTile * kBigBK * 2, kBigStage = 2 * kBigXB;   // bytes
 constexpr int kBigSigns = 2 * kBigStage, kBigScales = kBigSigns + 8 * 1024, kBigTouch = kBigScales + 8 * 1024, kBigLds = kBigTouch + 8 * 256;
 constexpr size_t kPartBytes = (size_t)kBigTile * kBigTile * 4;      // fp32 partial sums of one tile
 
+// Rows of a W_b tile that each of the workgroups sharing it touches ahead of its loads, and the lanes of a wave that
+// do so.  All rows are covered, except by a workgroup that has the tile to itself: each line is then loaded only
+// once anyway, and 64 of the rows are better than all (256 x 14336 x 4096 bf16 63 against 65 us).  With 64 rows also
+// for two and three sharers, 500 x 4096 x 11008 took 81 instead of 79.5 us and 700 x 11008 x 4096 139 instead of 133.5.
+constexpr __host__ __device__ int touch_rows(int sharers) { return (kBigTile + sharers - 1) / sharers; }
+constexpr __host__ __device__ int touch_lanes(int sharers) { return sharers == 1 ? 8 : (touch_rows(sharers) + 7) / 8; }
+constexpr bool touch_covers_the_tile(int sharers)
+{
+    return sharers > 8 || (8 * touch_lanes(sharers) >= touch_rows(sharers) && sharers * touch_rows(sharers) >= kBigTile &&
+                           touch_lanes(sharers) <= 64 && touch_covers_the_tile(sharers + 1));
+}
+static_assert(touch_covers_the_tile(2), "a line that is not touched is waited for by its first reader");
+
 // x ^ C.  HERE: computed where it stands.  As ordinary expressions the LDS addresses of the loop are all kept in
 // registers, up to 20 of them, and for fp16 with column or blockwise scales there are not enough (accumulators, two
 // sets of fragments and raw weights take 200 of the 256): 5 and 11 were spilled and reloaded between the MFMAs, each
@@ -143,9 +156,10 @@ linear_gemm_big_kernel(const uint16_t* __restrict__ X, const uint16_t* __restric
     };
 
     // L2 prefetch of W_b, kBigFar steps ahead: the workgroups of one output-row tile on an XCD share its 256
-    // rows, 4 to 8 lanes of each wave touch one 128-byte line each.  (The data goes to LDS that nobody reads.)
-    const int sharers = min(m_tiles, 8), lanes = min(32 / sharers, 8);
-    const uint32_t poff = (uint32_t)(min(n0 + (tile % m_tiles % sharers) * (256 / sharers) + wave * lanes + lane, d_out - 1) - n0) * (uint32_t)K * 2u;
+    // rows, the first lanes of each wave touch one 128-byte line each.  (The data goes to LDS that nobody reads.)
+    const int sharers = min(m_tiles, 8), lanes = touch_lanes(sharers);
+    const int trow = min((tile % m_tiles % sharers) * touch_rows(sharers) + wave * lanes + lane, kBigTile - 1);
+    const uint32_t poff = (uint32_t)(min(n0 + trow, d_out - 1) - n0) * (uint32_t)K * 2u;
     auto prefetch = [&](int s) {
         if (lane < lanes) load_lds_4(lds0 + kBigTouch + wave * 256, poff, wbase + (int64_t)min(s + kBigFar, n_steps - 1) * (kBigBK * 2));
     };
