@@ -390,8 +390,8 @@ def main() -> int:
             tot_flop += flop
             tot_ms += ms
             if (d_out, d_in) == synth.PREFILL_SHAPES[0]:
-                # where the launch spends its time: the same kernel with parts of its loop compiled out
-                # (pdelta_probe_prefill_parts; mask 15 is the product kernel)
+                # where the 256 x 128 kernel spends its time on this shape: its loop with parts compiled out
+                # (pdelta_probe_prefill_parts; mask 15 is the whole kernel).  The call timed above runs 256 x 256 tiles.
                 parts = {}
                 for mask in pd.PREFILL_PARTS_BUILT:
                     fp = lambda: pd.pdelta_probe_prefill_parts(mask, X, W_b, B, v_row, Y)
@@ -399,8 +399,8 @@ def main() -> int:
                     msp = sorted(timed(fp, 20) / 20 for _ in range(3))[1]
                     kept = [name for name, bit in pd.PREFILL_PARTS.items() if mask & bit]
                     parts[str(mask)] = {"kept": kept or ["nothing (barriers and epilogue only)"], "us": round(msp * 1e3, 1)}
-                prefill_parts = {"workload": f"{d_out}x{d_in}, bf16, M = {M}, row scales; linear_gemm_pipe_kernel "
-                                             "with parts of its loop compiled out", "masks": parts}
+                prefill_parts = {"workload": f"{d_out}x{d_in}, bf16, M = {M}, row scales; linear_gemm_pipe_kernel (256 x 128 tiles; "
+                                             "not the kernel of this shape's call) with parts of its loop compiled out", "masks": parts}
             if (d_out, d_in) == synth.PREFILL_SHAPES[0] and "group" not in skip:
                 # the same layer with one scale per (row, block of 128 inputs): reported, not in the aggregate
                 vg = torch.full((d_out, d_in // 128), 1e-3, dtype=torch.float16, device=dev)

@@ -44,12 +44,13 @@ int pdelta_probe_read_stream(const void* src, size_t bytes, void* sink, void* st
 int pdelta_probe_mfma(int waves_per_simd, int random_operands, int iters, void* sink, void* stream);
 
 /*
- * Where a prefill launch spends its time: the product's prefill kernel for more than 128 tokens
+ * Where a prefill launch spends its time: the 256 x 128-tile prefill kernel for more than 128 tokens
  * (bf16 X and W_b, row scales; the operation is the delta linear layer of paper Eq. 1, arguments as
  * pdelta_linear_row) built with parts of its inner loop compiled out.  `parts` is a bit mask of
  * what stays: 1 the global loads of the steady loop, 2 the bf16 -> fp16 conversion, sign / scale
- * add and LDS writes, 4 the fragment reads from LDS, 8 the MFMAs.  15 is the product kernel itself
- * and writes the same Y as pdelta_linear_row, bit for bit; with any other mask Y is written with
+ * add and LDS writes, 4 the fragment reads from LDS, 8 the MFMAs.  15 is the whole kernel
+ * and writes the same Y as pdelta_linear_row, bit for bit, also for the shapes that call computes on
+ * 256 x 256 tiles; with any other mask Y is written with
  * meaningless values (all accesses stay in bounds).  Built masks: 0, 1, 2, 3, 4, 8, 12, 13, 14, 15.
  *   M > 128 (PDELTA_ESHAPE otherwise); other checks and status values as pdelta_linear_row;
  *   PDELTA_EINVAL for a mask that is not built.

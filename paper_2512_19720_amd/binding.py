@@ -573,7 +573,7 @@ PREFILL_PARTS_BUILT = (0, 1, 2, 3, 4, 8, 12, 13, 14, 15)
 
 def pdelta_probe_prefill_parts(parts: int, X, W_b, B_packed, v_row, out):
     """Enqueue the prefill kernel (bf16, row scales, more than 128 tokens) with only the parts of
-    its loop named by the bit mask ``parts``; 15 is the product kernel."""
+    its loop named by the bit mask ``parts``; 15 is the whole kernel."""
     M, d_in = X.shape
     d_out = W_b.shape[0]
     rc = lib().pdelta_probe_prefill_parts(parts, _dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"),

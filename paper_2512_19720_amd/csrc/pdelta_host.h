@@ -101,7 +101,8 @@ int launch_linear_gemm_big(int x_dtype, int y_dtype, int axis, const void* X, co
 
 // Measurement builds of the pipelined prefill kernel (bf16 operands, row scales): bit 0 of `parts`
 // keeps the steady loop's global loads, bit 1 conversion and LDS writes, bit 2 fragment reads,
-// bit 3 the MFMAs; 15 is the product kernel.  Returns -2 for a combination that is not built.
+// bit 3 the MFMAs; 15 is that kernel whole (a library call of the same shape may run another, see
+// linear_gemm_big_split).  Returns -2 for a combination that is not built.
 int launch_linear_gemm_parts(int parts, int y_dtype, const void* X, const void* W_b, const uint32_t* B_packed,
                              const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in,
                              hipStream_t stream);

@@ -239,7 +239,7 @@ struct GemmRegs {                         // one step of one thread: 4 x 16 B of
     uint32_t sb[2], vg[2];                // sign bytes; blockwise mode: the step's scale per W row
 };
 
-// PARTS (measurement builds only; 15 = the product kernel): bit 0 the global loads of the steady
+// PARTS (measurement builds only; 15 = the whole kernel): bit 0 the global loads of the steady
 // loop, bit 1 conversion and LDS writes, bit 2 fragment reads, bit 3 the MFMAs.  A part that is
 // switched off is compiled out with its inputs kept alive (loads are still waited for where the
 // conversion would use them, fragments where the MFMAs would), every access stays in bounds and
@@ -762,7 +762,7 @@ static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_pack
         return launch_gemm_small<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
     if (M <= 128 || tune_value("gemm_bm", 256) == 128)
         return launch_gemm<XDT, AXIS, 128, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-    // The pipelined kernel (one workgroup per CU) is the default: measured 6 % faster on
+    // Of the 256 x 128 kernels the pipelined one (one workgroup per CU) is taken: measured 6 % faster on
     // 11008 x 4096, 2 % on 14336 x 4096 and 27 % on 4096 x 11008 (M = 2048) than the two-per-CU
     // kernel, whose finer granularity does not make up for its second barrier per step, and it
     // writes exactly Y (no register spills).  gemm_pipe=0 selects the two-per-CU kernel.
@@ -816,7 +816,7 @@ int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const 
 }
 
 // Measurement builds of the pipelined kernel (bf16 operands, row scales) with parts of its loop
-// compiled out; parts = 15 is the product kernel.
+// compiled out; parts = 15 is the whole kernel.
 int launch_linear_gemm_parts(int parts, int y_dtype, const void* X, const void* W_b, const uint32_t* B_packed,
                              const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in,
                              hipStream_t stream)

@@ -27,6 +27,28 @@ def test_whole_and_split_tiles(M, d_out, d_in, dtype, parts, monkeypatch):
             check_y(gpu_linear(axis, d["X"], d["W_b"], d["B"], v_dev, y), ref, f"big M={M} {d_out}x{d_in} dt={dtype} axis={axis} parts={parts}")
 
 
+# an output of a whole tile is the same sum in the same order in every prefill kernel, and it is what the entry points
+# without a workspace compute
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("M,d_out,d_in", [(300, 264, 640), (1024, 4096, 4096)])
+def test_whole_tiles_have_the_bits_of_the_other_kernels(M, d_out, d_in, dtype, monkeypatch):
+    L = make_case(d_out, d_in, M, dtype, "row", 31 * M + d_out)
+    d = L["d"]
+    for axis, v in ((orc.ROW, d["v_row"]), (orc.COL, d["v_col"])):
+        got = []
+        for tune in ("gemm_big=1", "gemm_big=0,gemm_small=0", "gemm_big=0,gemm_small=1"):
+            monkeypatch.setenv("PDELTA_TUNE", tune)
+            got.append(gpu_linear(axis, d["X"], d["W_b"], d["B"], v, torch.float32))
+        monkeypatch.delenv("PDELTA_TUNE")
+        Y = torch.full((M, d_out), float("nan"), dtype=torch.float32, device=DEV)
+        fn = pd.lib().pdelta_linear_row if axis == orc.ROW else pd.lib().pdelta_linear_col
+        assert fn(d["X"].data_ptr(), d["W_b"].data_ptr(), d["B"].data_ptr(), v.data_ptr(), Y.data_ptr(), M, d_out, d_in,
+                  pd.F16 if dtype == synth.F16 else pd.BF16, pd.F32, torch.cuda.current_stream().cuda_stream) == pd.OK
+        for other in got[1:] + [Y]:
+            assert torch.equal(other, got[0]), f"axis={axis}"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("group,shared", [(32, False), (64, False), (128, True), (640, False), (640, True)])
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
