@@ -533,9 +533,11 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
 
 // Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel.  That one takes 7 us
 // and 0.8 us per step of 64 inputs when it has few tiles, however few they are; this one 24 us (its epilogue
-// reads G for every part) and 1.05 per step with at most 128 workgroups.  Above 64 tiles, or where the
-// workgroups would be more than 128, the epilogues cost what the shorter loops give.  256 tokens, 4096 x
-// 4096 fp16 row 60 -> 31 us, 512 tokens bf16 row 60 -> 41, col 73 -> 60, 128 tokens on 4096 x 11008 145 -> 49; 2048 tokens, 4096 x
+// reads G for every part, one 2-byte load after another: the compiler puts each behind a branch on its token and waits
+// for it) and 1.05 per step with at most 128 workgroups.  Above 64 tiles, or where the
+// workgroups would be more than 128, the epilogues cost what the shorter loops give.  Repeated inputs, 256 tokens, 4096 x
+// 4096 fp16 row 60 -> 31 us (changing inputs 66 -> 42), 512 tokens bf16 row 60 -> 41, col 73 -> 60, 128 tokens on 4096 x
+// 11008 145 -> 49; 2048 tokens, 4096 x
 // 4096 in two parts 84-91 us against 71-78; 512 tokens in 8 parts 54 instead of 41.
 static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
 {

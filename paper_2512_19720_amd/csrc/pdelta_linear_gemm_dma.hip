@@ -2,7 +2,7 @@
 // (W_hat = fp16(W_b +- v), X as fp16, fp32 sums in the order of d_in) on tiles of 256 tokens x 256 output
 // rows x 64 inputs, 8 waves of 128 x 64 outputs, with all global traffic as direct loads into LDS.
 //
-// What bounds it, found by taking parts out (2048 x 8192 x 4096 fp16, one full round of 256 tiles, 131 us
+// What bounds it, found by taking parts out in working builds (2048 x 8192 x 4096 fp16, one full round of 256 tiles, 131 us
 // against 152 for the 256 x 128 register-staged kernel): MFMAs, fragment reads and conversion alone 114 us
 // (the matrix cores' own ceiling with random operands is 81), everything but the MFMAs 91.  The
 // latter is the L1's request rate, about one request every two cycles whether it is for 64 or 128 bytes;
@@ -17,7 +17,7 @@
 // last quarter's MFMAs run while the first fragments of step s+1 are read.
 //
 // With W_b in HBM (a program's other layers ran in between) two stages are too little lead for the first
-// reader of a line, so each workgroup also touches its share of the W_b lines kBigFar steps ahead: 2048 x
+// reader of a line, so each workgroup also touches its share of the W_b lines kBigFar steps ahead (touch_rows): 2048 x
 // 11008 x 4096 bf16 on changing inputs 237 -> 227 us (236 for the 256 x 128 kernel), 777 x 4096 x 11008
 // blockwise 131 -> 126 (253); on inputs that stay cached it is within 2 %.  Touching the lines of both
 // operands from every workgroup costs more than it gives (the L1's request rate again).
@@ -365,9 +365,9 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // steps, a split 8 more for its second launch and 0.06 per part for the sums that it writes and reads;
 // the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernel 0.34 a step for each of its
 // workgroups on a CU (0.42 / 0.47 at least) and 3 a call.  Against the latter a split pays 0.4 more per part: it
-// has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, this
-// kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 213 against 224-229, 777 x 4096 x
-// 11008 blockwise (64 tiles in 4 parts) 117 against 236, 1024 x 4096 x 4096 58 against 82; 256 x 512 x 8192 (2 tiles
+// has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, changing
+// inputs, this kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 223-230 against 230-237, 777 x
+// 4096 x 11008 blockwise (64 tiles in 4 parts) 127 against 254, 1024 x 4096 x 4096 60 against 87, 256 x 512 x 8192 (2 tiles
 // in 16 parts) 36 against 58.  Below the line: 256 x 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 26, 512 x 300 x
 // 3968 32 against 26, 251 x 4096 x 4096 32 against 30.
 BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed)

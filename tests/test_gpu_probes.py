@@ -1,5 +1,5 @@
 """The measurement build of the prefill kernel (pdelta_probe_prefill_parts): with every part of
-the loop switched on it IS the product kernel, so its output must equal pdelta_linear_row's bit
+the loop switched on it IS the 256 x 128 kernel, so its output must equal pdelta_linear_row's bit
 for bit; every other built mask must run to completion (its output is meaningless by contract)."""
 import pytest
 import torch
