@@ -73,3 +73,24 @@ def test_a_decode_call_is_one_library_call(monkeypatch):
         assert fn(X, W_b, FakeTensor(256, 16), FakeTensor(256), out=Y) is Y
         assert X.reads == 1 and W_b.reads == 1
     assert calls == ["pdelta_linear_row", "pdelta_linear_col"]
+
+
+def test_group_workspace_rules():
+    L, A, GB = pd.lib(), 1 << 40, 1 << 30
+    M, d_out, d_in = 1024, 4096, 4096
+    need = L.pdelta_linear_workspace_bytes(M, d_out, d_in, pd.BF16)
+
+    def call(ws=A + 5 * GB, n=need, group=128, shared=0, M=M):
+        return L.pdelta_linear_group_ws(A, A + GB, A + 2 * GB, A + 3 * GB, group, shared, A + 4 * GB, M, d_out, d_in, pd.BF16, pd.F32,
+                                        ws, n, None)
+
+    assert call(n=need - 1) == pd.EWORKSPACE
+    assert call(ws=A + 5 * GB + 4) == pd.EALIGN
+    assert call(ws=None) == pd.EINVAL
+    for k in range(5):
+        assert call(ws=A + k * GB) == pd.EINVAL                          # on X, W_b, B_packed, v, Y
+    # the last bytes of the tensors, whose sizes depend on the call: 4 bytes an output, 2 a scale
+    assert call(ws=A + 4 * GB + M * d_out * 4 - 16) == pd.EINVAL
+    assert call(ws=A + 3 * GB + d_out * (d_in // 128) * 2 - 16) == pd.EINVAL
+    assert call(group=100) != pd.OK and call(group=3) != pd.OK           # refused with a workspace as without
+    assert call(M=0) == pd.OK
