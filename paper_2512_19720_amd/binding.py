@@ -525,18 +525,21 @@ def pdelta_pack_group(W_f: torch.Tensor, W_b: torch.Tensor, group: int, shared_r
 def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=None, workspace=None):
     """Y = X W_hat^T with W_hat = W_b + scale(o, i) B and blockwise scales v; ``workspace`` as in ``pdelta_linear_row``."""
     M, d_in = X.shape
-    d_out, _, shared = _group_args(W_b, v, group)
-    if W_b.shape[1] != d_in or X.dtype != W_b.dtype:
+    d_out, w_in, shared = _group_args(W_b, v, group)
+    if w_in != d_in or X.dtype != W_b.dtype:
         raise ValueError("X and W_b must agree in d_in and dtype")
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     x_dtype = dtype_code(X.dtype)
-    ws = None
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
         ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype), workspace)
-    rc = lib().pdelta_linear_group_ws(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
-                                      group, shared, _dev(out, "Y") or None, M, d_out, d_in, x_dtype,
-                                      dtype_code(out.dtype), *_workspace_args(ws), _stream())
+        rc = lib().pdelta_linear_group_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+                                          group, shared, _dev(out, "Y"), M, d_out, d_in, x_dtype,
+                                          dtype_code(out.dtype), *_workspace_args(ws), _stream())
+    else:
+        rc = lib().pdelta_linear_group(_dev(X, "X") or None, _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+                                       group, shared, _dev(out, "Y") or None, M, d_out, d_in, x_dtype,
+                                       dtype_code(out.dtype), _stream())
     _check(rc, "pdelta_linear_group")
     return out
 

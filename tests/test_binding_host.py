@@ -54,6 +54,9 @@ def test_a_decode_call_is_one_library_call(monkeypatch):
             self.reads += 1
             return self.size
 
+        def dim(self):
+            return len(self.size)
+
         def is_contiguous(self):
             return True
 
@@ -72,7 +75,10 @@ def test_a_decode_call_is_one_library_call(monkeypatch):
         X, W_b, Y = FakeTensor(4, 512), FakeTensor(256, 512), FakeTensor(4, 256)
         assert fn(X, W_b, FakeTensor(256, 16), FakeTensor(256), out=Y) is Y
         assert X.reads == 1 and W_b.reads == 1
-    assert calls == ["pdelta_linear_row", "pdelta_linear_col"]
+    X, W_b, Y = FakeTensor(4, 512), FakeTensor(256, 512), FakeTensor(4, 256)
+    assert pd.pdelta_linear_group(X, W_b, FakeTensor(256, 16), FakeTensor(256, 4), 128, out=Y) is Y
+    assert X.reads == 1 and W_b.reads == 1
+    assert calls == ["pdelta_linear_row", "pdelta_linear_col", "pdelta_linear_group"]
 
 
 def test_group_workspace_rules():
