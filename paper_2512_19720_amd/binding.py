@@ -234,16 +234,18 @@ def _linear(fn_name: str, X, W_b, B_packed, v, out, out_dtype, workspace):
         raise ValueError("X and W_b must agree in d_in and dtype")
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
+    L = _lib if _lib is not None else lib()
     if M > _DECODE_MAX_TOKENS and X.is_cuda:
-        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[X.dtype]), workspace)
-        rc = lib().pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
+        need = L.pdelta_linear_workspace_bytes(M, d_out, d_in, _DTYPE_CODE[X.dtype])
+        if need != 0:
+            ws = _prefill_workspace(need, workspace)
+            rc = L.pdelta_linear_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                     ROW if fn_name == "pdelta_linear_row" else COL, _dev(out, "Y"), M, d_out, d_in,
                                     _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], *_workspace_args(ws), _stream())
-        _check(rc, fn_name)
-        return out
-    fn = getattr(_lib, fn_name) if _lib is not None else getattr(lib(), fn_name)
-    rc = fn(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"), _dev(out, "Y"),
-            M, d_out, d_in, _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], _stream())
+            _check(rc, fn_name)
+            return out
+    rc = getattr(L, fn_name)(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"), _dev(out, "Y"),
+                             M, d_out, d_in, _DTYPE_CODE[X.dtype], _DTYPE_CODE[out.dtype], _stream())
     if rc != OK:
         raise PdeltaError(rc, fn_name)
     return out
@@ -531,8 +533,9 @@ def pdelta_linear_group(X, W_b, B_packed, v, group: int, out=None, out_dtype=Non
     if out is None:
         out = torch.empty((M, d_out), dtype=out_dtype or X.dtype, device=X.device)
     x_dtype = dtype_code(X.dtype)
-    if M > _DECODE_MAX_TOKENS and X.is_cuda:
-        ws = _prefill_workspace(lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype), workspace)
+    need = lib().pdelta_linear_workspace_bytes(M, d_out, d_in, x_dtype) if M > _DECODE_MAX_TOKENS and X.is_cuda else 0
+    if need != 0:
+        ws = _prefill_workspace(need, workspace)
         rc = lib().pdelta_linear_group_ws(_dev(X, "X"), _dev(W_b, "W_b"), _dev(B_packed, "B_packed"), _dev(v, "v"),
                                           group, shared, _dev(out, "Y"), M, d_out, d_in, x_dtype,
                                           dtype_code(out.dtype), *_workspace_args(ws), _stream())

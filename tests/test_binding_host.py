@@ -79,6 +79,10 @@ def test_a_decode_call_is_one_library_call(monkeypatch):
     assert pd.pdelta_linear_group(X, W_b, FakeTensor(256, 16), FakeTensor(256, 4), 128, out=Y) is Y
     assert X.reads == 1 and W_b.reads == 1
     assert calls == ["pdelta_linear_row", "pdelta_linear_col", "pdelta_linear_group"]
+    del calls[:]                                              # a short prompt that uses no workspace: its size, then the same call
+    pd.pdelta_linear_row(FakeTensor(65, 512), W_b, FakeTensor(256, 16), FakeTensor(256), out=FakeTensor(65, 256))
+    pd.pdelta_linear_group(FakeTensor(65, 512), W_b, FakeTensor(256, 16), FakeTensor(256, 4), 128, out=FakeTensor(65, 256))
+    assert calls == ["pdelta_linear_workspace_bytes", "pdelta_linear_row", "pdelta_linear_workspace_bytes", "pdelta_linear_group"]
 
 
 def test_group_workspace_rules():
