@@ -364,7 +364,8 @@ static int launch_grad_tile_pipe(const uint16_t* A, const uint16_t* G, const uin
 // partials and nothing else.  2048 tokens, 4096 x 4096 bf16: see grad_big_parts.
 constexpr int kGbTile = 256, kGbBK = 64, kGbUnitK = 128;
 constexpr int kGbAB = kGbTile * kGbBK * 2, kGbStage = 2 * kGbAB;      // bytes of A (of the signs) and of a stage
-constexpr int kGbSigns = 2 * kGbStage, kGbLds = kGbSigns + 8 * 1024;  // + sign words: 1 KB per wave
+// behind the stages, per wave: sign words (1 KB), and where touched lines of G end up (256 B)
+constexpr int kGbSigns = 2 * kGbStage, kGbTouch = kGbSigns + 8 * 1024, kGbLds = kGbTouch + 8 * 256;
 
 template <int DT>
 __global__ void __launch_bounds__(512, 2)
@@ -468,6 +469,16 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
     request(1, kGbStage);
     read_frags(0, 0);
 
+    // The tile's lines of G, on their way to L2 during the last two steps (two 128-byte lines per thread; the data goes
+    // to LDS that nobody reads): the epilogue would wait for memory eight times otherwise.
+    const char* gbase = (const char*)(G + (int64_t)m0 * Nc);
+    auto touch_g = [&]() {
+        const uint32_t row = (uint32_t)(min(m0 + (int)threadIdx.x / 2, M - 1) - m0) * (uint32_t)Nc;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            load_lds_2(lds0 + kGbTouch + wave * 256, (row + (uint32_t)min(n0 + ((int)threadIdx.x % 2 * 2 + q) * 64, Nc - 1)) * 2u, gbase);
+    };
+
     // Step s; REQ: request step s + 2, MORE: there is a step s + 1.  The fences keep the LDS reads above
     // the MFMAs and the expansion between them.
     auto step = [&](int s, uint32_t cur, uint32_t nxt, auto req, auto more) {
@@ -480,7 +491,8 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
         __builtin_amdgcn_sched_barrier(0);
         multiply(1);
         __builtin_amdgcn_sched_barrier(0);
-        wait_loads<0>();
+        if constexpr (REQ) wait_loads<0>();
+        else if constexpr (MORE) wait_loads<2>();     // (all but touch_g)
         if constexpr (MORE) fetch_signs(s + 1);
         read_frags(cur, 3);
         __builtin_amdgcn_sched_barrier(0);
@@ -499,56 +511,84 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
         step(s, 0, kGbStage, std::true_type{}, std::true_type{});
         step(s + 1, kGbStage, 0, std::true_type{}, std::true_type{});
     }
+    touch_g();
     step(s, 0, kGbStage, std::false_type{}, std::true_type{});
     step(s + 1, kGbStage, 0, std::false_type{}, std::false_type{});
 
     // epilogue as in grad_tile_kernel, a sum of its own for each 32 tokens (the last barrier came after the
-    // last fragment read: the stages are free)
+    // last fragment read: the stages are free).  The 128 entries of G that a lane needs are asked for 16 at a time, one
+    // group ahead of the sums, from uniform row addresses; rows past the end repeat the last one and count as zero.
+    // Left to itself the compiler puts every 2-byte load behind a branch on its token and waits for it, 20 us a tile.
     float* red = (float*)gb_smem;                      // [2 wm][256]
+    const int tok0 = m0 + wm * 128, half4 = (lane >> 5) * 4;
+    uint32_t gbits[2][16], goff[FN];
 #pragma unroll
-    for (int h = 0; h < FN; ++h) {
-        const int n = n0 + wn * 64 + h * 32 + (lane & 31);
-        const int nc = min(n, Nc - 1);
-        float sum[FM];
-#pragma unroll
-        for (int f = 0; f < FM; ++f) {
-            sum[f] = 0.f;
+    for (int h = 0; h < FN; ++h) goff[h] = (uint32_t)min(n0 + wn * 64 + h * 32 + (lane & 31), Nc - 1) * 2u;
+    const uint32_t gstep = (uint32_t)half4 * (uint32_t)Nc * 2u;
+    auto weighted_sums = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;  // all of the tile's tokens exist
+        auto load_g = [&](int i) {
+            const int h = i / FM, f = i % FM;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int tok = m0 + wm * 128 + f * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const uint32_t gbits = G[(int64_t)min(tok, M - 1) * Nc + nc];
-                const float gval = tok < M ? bits_to_f32<DT>(gbits) : 0.f;
-                sum[f] += gval * acc[f][h][r];
+                const int row = wm * 128 + f * 32 + (r >> 2) * 8 + (r & 3);
+                if constexpr (FULL)
+                    gbits[i & 1][r] = *(const uint16_t*)(gbase + (int64_t)row * Nc * 2 + (goff[h] + gstep));
+                else
+                    gbits[i & 1][r] = *(const uint16_t*)(gbase + ((uint32_t)(min(m0 + row + half4, M - 1) - m0) * (uint32_t)Nc * 2u + goff[h]));
+            }
+        };
+        load_g(0);
+        float t = 0.f, first = 0.f;
+#pragma unroll
+        for (int i = 0; i < FN * FM; ++i) {
+            const int h = i / FM, f = i % FM;
+            if (i + 1 < FN * FM) load_g(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                uint32_t g = gbits[i & 1][r];
+                if constexpr (!FULL) g = tok0 + f * 32 + (r >> 2) * 8 + half4 + (r & 3) < M ? g : 0u;
+                sum += bits_to_f32<DT>(g) * acc[f][h][r];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if ((f & 1) == 0) first = sum;
+            else t = f == 1 ? first + sum : t + (first + sum);
+            if (f == FM - 1) {
+                t += __shfl_xor(t, 32, kWave);
+                if (lane < 32) red[wm * kGbTile + wn * 64 + h * 32 + lane] = t;
             }
         }
-        float t = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-        t += __shfl_xor(t, 32, kWave);
-        if (lane < 32) red[wm * kGbTile + wn * 64 + h * 32 + lane] = t;
-    }
+    };
+    if (m0 + kGbTile <= M) weighted_sums(std::true_type{});       // uniform
+    else weighted_sums(std::false_type{});
     __syncthreads();
     const int tid = threadIdx.x;
     if (tid < kGbTile && n0 + tid < Nc)
         partial[(int64_t)(part * m_tiles + tile_m) * Nc + n0 + tid] = red[tid] + red[kGbTile + tid];
 }
 
-// Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel.  That one takes 7 us
-// and 0.8 us per step of 64 inputs when it has few tiles, however few they are; this one 24 us (its epilogue
-// reads G for every part, one 2-byte load after another: the compiler puts each behind a branch on its token and waits
-// for it) and 1.05 per step with at most 128 workgroups.  Above 64 tiles, or where the
-// workgroups would be more than 128, the epilogues cost what the shorter loops give.  Repeated inputs, 256 tokens, 4096 x
-// 4096 fp16 row 60 -> 31 us (changing inputs 66 -> 42), 512 tokens bf16 row 60 -> 41, col 73 -> 60, 128 tokens on 4096 x
-// 11008 145 -> 49; 2048 tokens, 4096 x
-// 4096 in two parts 84-91 us against 71-78; 512 tokens in 8 parts 54 instead of 41.
+// Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel, which is only taken where the
+// contraction is not a multiple of 128 or the caller's workspace has no room for the parts.  A round of up to 256
+// workgroups takes 4 us and 1.12 us per step of 64 inputs (1.44 when all CUs multiply and the clock falls); a part more
+// is one more row of partial sums for the second launch, and 16 parts would double the workspace for 3 us.  Changing
+// inputs, bf16 row, the 256 x 128 kernel or the earlier epilogue, then now: 64 tokens, 11008 x 4096 65 -> 26 us; 256 tokens, 4096 x 4096 41 ->
+// 19; 1024 65 -> 33; 2048 80 -> 58 (col 88 -> 65); 2048 tokens, 11008 x 4096 221 -> 157; 4000 tokens, 2048 x 2048 53 -> 34.
 static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
 {
     const int forced = tune_value("grad_big", -1);     // 0: never; n > 0: in n parts
     if (Kc % kGbUnitK != 0 || M <= 0 || forced == 0 || (forced < 0 && tune_value("grad_pipe", -1) >= 0)) return 0;
-    const int64_t tiles = (M + kGbTile - 1) / kGbTile * ((Nc + kGbTile - 1) / kGbTile), units = Kc / kGbUnitK;
+    const int64_t m_tiles = (M + kGbTile - 1) / kGbTile, tiles = m_tiles * ((Nc + kGbTile - 1) / kGbTile), units = Kc / kGbUnitK;
     if (tiles > (1 << 24)) return 0;
     if (forced > 0) return (int)std::min<int64_t>(forced, units);
-    if (tiles > 64) return 0;
-    const int64_t p = std::min<int64_t>(std::min<int64_t>(128 / tiles, units), 16);
-    return 24 + 1.05 * 2 * (double)((units + p - 1) / p) < 0.9 * (7 + 0.8 * 2 * (double)units) ? (int)p : 0;
+    double best = 0;
+    int parts = 0;
+    for (int64_t p = 1; p <= std::min<int64_t>(8, units); ++p) {
+        const double t = (double)((tiles * p + 255) / 256) * (4 + 1.12 * 2 * (double)((units + p - 1) / p));
+        if (parts == 0 || t < best) { best = t; parts = (int)p; }
+    }
+    return parts;
 }
 
 template <int DT>
@@ -564,40 +604,66 @@ static int launch_grad_big(const uint16_t* A, const uint16_t* G, const uint32_t*
     return 0;
 }
 
+// Sums of the partial rows (up to 8 parts times the token tiles) in fp64: a block takes 64 outputs, its wave w the
+// rows w, w + 4, ..., so that every load of a thread is in flight at once and 4096 outputs spread over 64 CUs.
 __global__ void __launch_bounds__(256)
-grad_reduce_kernel(const float* __restrict__ partial, float* __restrict__ grad, int n, int m_tiles)
+grad_reduce_kernel(const float* __restrict__ partial, float* __restrict__ grad, int n, int rows)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    double s = 0.0;                                    // (up to 16 parts times the token tiles)
-#pragma unroll 4
-    for (int t = 0; t < m_tiles; ++t) s += (double)partial[(int64_t)t * n + i];
-    grad[i] = (float)s;
+    __shared__ double part[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane, ic = min(i, n - 1);
+    double s = 0.0;
+#pragma unroll 8
+    for (int t = w; t < rows; t += 4) s += (double)partial[(int64_t)t * n + ic];
+    part[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && i < n) grad[i] = (float)((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
 }
 
-// Bt[i][o / 32] bit (o % 32) = B[o][i / 32] bit (i % 32); d_out % 32 == 0.  A wave takes 64 rows
-// o and one word column: 32 ballots turn the lanes' words into the 64-bit columns.
+// Bt[i][o / 32] bit (o % 32) = B[o][i / 32] bit (i % 32); d_out % 32 == 0.  A lane transposes one block of 32 x 32 bits
+// in registers (five rounds of masked swaps, 10 instructions for each of its words; ballots took eight times that); the
+// lanes of a wave take 64 consecutive words of each row, the four waves 128 rows, whose 16 bytes per row of Bt leave
+// through LDS as one store.  4096 x 4096: 5.4 us a launch (7.1 with ballots and 4-byte loads down the columns).
 __global__ void __launch_bounds__(256)
 transpose_bits_kernel(const uint32_t* __restrict__ B, uint32_t* __restrict__ Bt, int d_out, int d_in)
 {
-    const int lane = threadIdx.x & 63;
-    const int wcol = blockIdx.x * 4 + (threadIdx.x >> 6);            // word column of B
-    const int wpr = d_in >> 5;
-    if (wcol >= wpr) return;                                        // whole wave
-    const int o = blockIdx.y * 64 + lane;
-    const uint32_t word = o < d_out ? B[(int64_t)o * wpr + wcol] : 0u;
-    unsigned long long mine = 0;
+    constexpr int COL = 32 * 4 + 4;                   // words per word column: [bit][row block], padded
+    __shared__ __attribute__((aligned(16))) uint32_t out[64 * COL];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int wpr = d_in >> 5, wpr_t = d_out >> 5;
+    const int wcol0 = blockIdx.x * 64, rblock0 = blockIdx.y * 4;
+    const int wcol = min(wcol0 + lane, wpr - 1), rblock = min(rblock0 + w, wpr_t - 1);    // (repeats are not stored)
+    const uint32_t* src = B + (int64_t)rblock * 32 * wpr + wcol;
+    uint32_t a[32];
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
-        const unsigned long long m = __ballot((word >> b) & 1u);
-        if (lane == b) mine = m;
-    }
-    if (lane < 32) {
-        const int i = wcol * 32 + lane;
-        const int wpr_t = d_out >> 5;
-        const int w0 = blockIdx.y * 2;
-        Bt[(int64_t)i * wpr_t + w0] = (uint32_t)mine;
-        if (w0 + 1 < wpr_t) Bt[(int64_t)i * wpr_t + w0 + 1] = (uint32_t)(mine >> 32);
+    for (int r = 0; r < 32; ++r) a[r] = src[(int64_t)r * wpr];
+    auto trade = [&](auto width) {                    // rows r and r + J trade the halves of their fields of 2 J bits
+        constexpr int J = decltype(width)::value;
+        constexpr uint32_t low = J == 16 ? 0x0000FFFFu : J == 8 ? 0x00FF00FFu : J == 4 ? 0x0F0F0F0Fu : J == 2 ? 0x33333333u : 0x55555555u;
+#pragma unroll
+        for (int r = 0; r < 32; ++r) {
+            if (r & J) continue;
+            const uint32_t x = a[r], y = a[r + J];
+            a[r] = (x & low) | ((y << J) & ~low);
+            a[r + J] = ((x >> J) & low) | (y & ~low);
+        }
+    };
+    trade(std::integral_constant<int, 16>{});
+    trade(std::integral_constant<int, 8>{});
+    trade(std::integral_constant<int, 4>{});
+    trade(std::integral_constant<int, 2>{});
+    trade(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int b = 0; b < 32; ++b) out[lane * COL + b * 4 + w] = a[b];
+    __syncthreads();
+    const bool whole = rblock0 + 4 <= wpr_t && (wpr_t & 3) == 0;              // 16-byte aligned pieces
+    for (int k = threadIdx.x; k < 64 * 32; k += 256) {
+        if (wcol0 + (k >> 5) >= wpr) break;
+        uint32_t* dst = Bt + ((int64_t)wcol0 * 32 + k) * wpr_t + rblock0;
+        const uint32_t* from = out + (k >> 5) * COL + (k & 31) * 4;
+        if (whole) *(uint4v*)dst = *(const uint4v*)from;
+        else
+            for (int q = 0; q < 4 && rblock0 + q < wpr_t; ++q) dst[q] = from[q];
     }
 }
 
@@ -631,7 +697,7 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
         size_t off = (size_t)m_tiles * std::max(1, parts) * Nc * sizeof(float);
         off = (off + 255) & ~(size_t)255;
         uint32_t* Bt = (uint32_t*)((char*)workspace + off);
-        const dim3 grid((unsigned)((d_in / 32 + 3) / 4), (unsigned)((d_out + 63) / 64));
+        const dim3 grid((unsigned)((d_in / 32 + 63) / 64), (unsigned)((d_out + 127) / 128));
         hipLaunchKernelGGL(transpose_bits_kernel, grid, dim3(256), 0, stream, B_packed, Bt, (int)d_out, (int)d_in);
         bits = Bt;
     }
@@ -656,7 +722,7 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
     else
         hipLaunchKernelGGL(grad_tile_kernel<kF16>, grid, dim3(512), 0, stream, A, G, bits, partial, (int)M, (int)Nc,
                            (int)Kc, (int)m_tiles);
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((Nc + 255) / 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((Nc + 63) / 64)), dim3(256), 0, stream,
                        (const float*)partial, grad, (int)Nc, (int)m_tiles * std::max(1, parts));
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

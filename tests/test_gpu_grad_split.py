@@ -23,6 +23,18 @@ def test_whole_and_split_contraction(M, d_out, d_in, dtype, axis, parts, monkeyp
     check_grad(got, ref, f"grad big M={M} {d_out}x{d_in} dt={dtype} axis={axis} parts={parts}")
 
 
+# the transposition of the signs at the edges of its 128 x 2048 tiles (d_out % 128 != 0: rows of the result that are not
+# 16-byte aligned), and sums over many partial rows (9 token tiles in 5 parts; 64 x 9 outputs of a reduction block)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,d_out,d_in", [(2, 32, 2080), (3, 160, 4128), (2, 128, 2048), (5, 288, 64), (2304, 640, 576)])
+@pytest.mark.parametrize("axis", [orc.ROW, orc.COL])
+def test_transposed_signs_and_many_partial_rows(M, d_out, d_in, axis):
+    X, dY, B = make(M, d_out, d_in, synth.BF16, 5 * M + d_out + d_in)
+    ref = orc.grad_v(X, dY, B, axis, synth.BF16)
+    got = pd.pdelta_grad_v(to_dev(X, synth.BF16), to_dev(dY, synth.BF16), words_dev(B), axis)
+    check_grad(got, ref, f"M={M} {d_out}x{d_in} axis={axis}")
+
+
 def test_split_workspace_sizes():
     L = pd.lib()
     assert L.pdelta_grad_v_split_workspace_bytes(256, 4096, 4096, pd.ROW) == 8 * 4096 * 4        # 16 tiles in 8 parts
