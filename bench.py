@@ -214,7 +214,7 @@ def main() -> int:
                                   "of this same command, committed as profiles/decode_4096x4096_pmc_traffic.md")
     launches = args.steps * len(cases)
     avg_launch_us = ms_total * 1e3 / launches
-    roofline = {"bound": "hbm", "kernel": "linear_skinny_kernel / linear_skinny_staged_kernel (decode, 4096x4096 fp16)",
+    roofline = {"bound": "hbm", "kernel": "linear_skinny_dma_kernel (decode, 4096x4096 fp16)",
                 "achieved": round(value, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(value / HBM_PEAK_GBS, 4),
                 "bytes_per_launch": step_bytes // len(cases),

@@ -23,68 +23,9 @@
 #include "pdelta.h"
 #include "pdelta_device.h"
 #include "pdelta_host.h"
+#include "pdelta_skinny_tile.h"
 
 namespace pdelta {
-
-template <int DT>
-__device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
-    if constexpr (DT == kBF16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                       __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a),
-                                                      __builtin_bit_cast(half8, b), c, 0, 0, 0);
-}
-
-// Eight sign bits (bit e <-> element e, 1 = +1) to eight +-1.0 values of dtype DT.
-template <int DT>
-__device__ __forceinline__ uint4v expand_signs(uint32_t byte) {
-    constexpr uint32_t one2 = DT == kBF16 ? 0x3F803F80u : 0x3C003C00u;
-    const uint32_t neg = ~byte;
-    uint4v r;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t t = neg >> (2 * p);
-        r[p] = one2 | ((t & 1u) << 15) | ((t & 2u) << 30);
-    }
-    return r;
-}
-
-// Column mode: the sign-part operand is fp16(X * v_col), whatever the dtype of X.
-template <int XDT>
-__device__ __forceinline__ uint4v scale_x(uint4v x, uint4v v) {
-    uint4v r;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        if constexpr (XDT == kF16) {
-            const uint32_t xp = x[p], vp = v[p];
-            r[p] = as_u32(as_half2(xp) * as_half2(vp));                        // v_pk_mul_f16
-        } else {
-            const float lo = bf16_bits_to_f32(x[p] & 0xFFFFu) * f16_bits_to_f32(v[p] & 0xFFFFu);
-            const float hi = bf16_bits_to_f32(x[p] >> 16) * f16_bits_to_f32(v[p] >> 16);
-            r[p] = f32_to_f16_bits(lo) | (f32_to_f16_bits(hi) << 16);
-        }
-    }
-    return r;
-}
-
-// Grouped scales: the sign-part operands are fp16 whatever the dtype of X: A = fp16(X) and
-// B = +-v (the exact product of the +-1 pattern and the group's scale).
-template <int XDT>
-__device__ __forceinline__ uint4v x_as_f16(uint4v x) {
-    if constexpr (XDT == kF16) return x;
-    else return scale_x<XDT>(x, (uint4v){0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u});
-}
-__device__ __forceinline__ uint4v signs_times_scale(uint4v pm, uint32_t v_half) {
-    const uint32_t vv = v_half | (v_half << 16);
-    uint4v r;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t sp = pm[p];
-        r[p] = as_u32(as_half2(sp) * as_half2(vv));                              // v_pk_mul_f16, exact
-    }
-    return r;
-}
 
 template <int MT, int AXIS>
 struct SkinnyStep {
@@ -167,6 +108,7 @@ __device__ __forceinline__ void skinny_compute(const SkinnyStep<MT, AXIS>& r, in
     }
 }
 
+// For what pdelta_linear_skinny_dma.hip leaves: see launch_plain.
 // grid.x = ceil(d_out / 16); block = WAVES * 64; dynamic LDS = WAVES * MT * 256 floats.
 // DEPTH steps per wave are kept in flight (a ring of register buffers).
 template <int XDT, int AXIS, int MT, int WAVES, int DEPTH, bool K128>
@@ -266,7 +208,7 @@ linear_skinny_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict_
     }
 }
 
-// ---- staged variant (M <= 16, d_in % 128 == 0, slabs fit in LDS) ---------------------------
+// ---- staged workgroup of the batched launch (M <= 16, d_in % 128 == 0, slabs fit in LDS) ----
 // What the plain kernel above loads besides W_b is small but awkward: the sign words of a step
 // are a 16-byte piece from each of 16 rows, and at one token X is 64 useful bytes per load
 // instruction.  Here the workgroup copies its whole sign slab (16 rows x d_in/8 bytes, one
@@ -286,8 +228,7 @@ template <int XDT, int AXIS, int WAVES, int DEPTH, bool STAGE_X>
 __device__ __forceinline__ void
 staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             const uint32_t* __restrict__ B_packed, const uint16_t* __restrict__ v,
-            void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int block,
-            int v_stride = 0, int g_shift = 31)
+            void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int block)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // nibble -> four +-1.0 values (of the sign operand's dtype): two conflict-free 8-byte LDS
@@ -300,11 +241,8 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
     float* red = (float*)smem;                                        // [WAVES][4][64]
     uint32_t* s_sign = (uint32_t*)(smem + WAVES * 1024);              // [16][spr]
     uint16_t* s_x = (uint16_t*)(s_sign + 16 * spr);                   // [M][xpr]      (STAGE_X)
-    uint16_t* s_xv = s_x + (STAGE_X ? M * xpr : 0);                   // [M][xpr]      (STAGE_X: col, or grouped with bf16 X)
-    // grouped mode: the scales of the workgroup's 16 rows, [16][ngrp] fp16, behind the X copies
-    constexpr bool XV = STAGE_X && (AXIS == 1 || (AXIS == 2 && XDT == kBF16));
-    const int ngrp = g_shift >= 31 ? 1 : (K >> g_shift);
-    uint16_t* s_v = s_xv + (XV ? M * xpr : 0);
+    uint16_t* s_xv = s_x + (STAGE_X ? M * xpr : 0);                   // [M][xpr]      (STAGE_X: col)
+    constexpr bool XV = STAGE_X && AXIS == 1;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -382,14 +320,6 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
                 *(uint4v*)(s_x + t * xpr + u * 8) = xv;
                 if constexpr (AXIS == 1)
                     *(uint4v*)(s_xv + t * xpr + u * 8) = scale_x<XDT>(xv, *(const uint4v*)(v + u * 8));
-                if constexpr (AXIS == 2 && XDT == kBF16)
-                    *(uint4v*)(s_xv + t * xpr + u * 8) = x_as_f16<XDT>(xv);
-            }
-        }
-        if constexpr (AXIS == 2) {
-            for (int i = tid; i < 16 * ngrp; i += WAVES * 64) {
-                const int row = i / ngrp, c = i - row * ngrp;
-                s_v[i] = v[(int64_t)min(n0 + row, d_out - 1) * v_stride + c];
             }
         }
     }
@@ -399,7 +329,6 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
     const uint32_t* my_sign = s_sign + n * spr;
     const uint16_t* my_x = s_x + tok * xpr + g * 8;
     const uint16_t* my_xv = s_xv + tok * xpr + g * 8;
-    const uint16_t* my_v = s_v + n * ngrp;
 
     auto compute = [&](const StagedStep<AXIS, STAGE_X>& r, int kb) {
         const uint4v sw = *(const uint4v*)(my_sign + (kb >> 5));
@@ -410,11 +339,9 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             if constexpr (STAGE_X) {
                 xa = *(const uint4v*)(my_x + kb + j * 32);
                 if constexpr (XV) xs = *(const uint4v*)(my_xv + kb + j * 32);
-                else if constexpr (AXIS == 2) xs = xa;
             } else {
                 xa = to_mfma_layout(r.x[j]);
                 if constexpr (AXIS == 1) xs = scale_x<XDT>(xa, r.vc[j]);
-                if constexpr (AXIS == 2) xs = x_as_f16<XDT>(xa);
             }
             const uint4v wj = to_mfma_layout(r.w[j]);
             uint4v sg;
@@ -427,7 +354,6 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             } else {
                 sg = expand_signs<(AXIS == 0 ? XDT : kF16)>(byte);
             }
-            if constexpr (AXIS == 2) sg = signs_times_scale(sg, my_v[(kb + j * 32) >> g_shift]);
             accb = mfma16<XDT>(xa, wj, accb);
             if constexpr (AXIS == 0) accs = mfma16<XDT>(xa, sg, accs);
             else accs = mfma16<kF16>(xs, sg, accs);
@@ -478,17 +404,6 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
     }
 }
 
-template <int XDT, int AXIS, int WAVES, int DEPTH, bool STAGE_X>
-__global__ void __launch_bounds__(WAVES * 64)
-linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
-                            const uint32_t* __restrict__ B_packed, const uint16_t* __restrict__ v,
-                            void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int v_stride,
-                            int g_shift)
-{
-    staged_body<XDT, AXIS, WAVES, DEPTH, STAGE_X>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype,
-                                                  (int)blockIdx.x, v_stride, g_shift);
-}
-
 // Many layers in one launch (all with the same batch M and dtypes; shapes and axis per layer).
 // Workgroup b belongs to the last layer whose first_block is <= b.  One launch instead of one
 // per layer removes the per-kernel ramp-up and drain (about 2.4 us each on MI355X, a third of a
@@ -517,81 +432,14 @@ linear_skinny_batch_kernel(const pdelta_layer* __restrict__ layers, int n_layers
 
 constexpr size_t kStagedLdsLimit = 96 * 1024;
 
-// LDS bytes of the staged kernel, or 0 when the slabs do not fit.
-// `x_copies`: LDS copies of X (2 when the sign part needs its own fp16 operand: column mode, or
-// grouped mode with bf16 X); `scale_halves`: grouped mode's 16 rows of scales.
-static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M, int64_t K, int64_t scale_halves = 0)
+// LDS bytes of a staged workgroup, or 0 when the slabs do not fit.
+// `x_copies`: LDS copies of X (column mode: 2, the sign part has its own fp16 operand).
+static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M, int64_t K)
 {
-    size_t bytes = (size_t)waves * 1024 + (size_t)16 * (K / 32 + 4) * 4 + (size_t)scale_halves * 2 + 16;
+    size_t bytes = (size_t)waves * 1024 + (size_t)16 * (K / 32 + 4) * 4 + 16;
     if (stage_x) bytes += (size_t)M * (K + 8) * 2 * x_copies;
     return bytes <= kStagedLdsLimit ? bytes : 0;
 }
-static int x_copies_of(int axis, int x_dtype) { return axis == 1 || (axis == 2 && x_dtype == kBF16) ? 2 : 1; }
-
-template <int XDT, int AXIS, int WAVES, int DEPTH, bool STAGE_X>
-static int launch_staged(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
-                         void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype, size_t lds,
-                         hipStream_t stream, int v_stride = 0, int g_shift = 31)
-{
-    const dim3 grid((unsigned)((d_out + 15) / 16));
-    auto kernel = linear_skinny_staged_kernel<XDT, AXIS, WAVES, DEPTH, STAGE_X>;
-    static unsigned lds_opted_in = 0;                 // per template instance: one kernel
-    if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0)
-        return -1;           // above the default dynamic-LDS limit the kernel has to opt in (once)
-    hipLaunchKernelGGL(kernel, grid, dim3(WAVES * 64), lds, stream, (const uint16_t*)X,
-                       (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype, v_stride,
-                       g_shift);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-// Returns 1 if the staged kernel does not apply, else the launch result (0 / -1).
-template <int XDT, int AXIS>
-static int try_staged(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
-                      void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
-                      hipStream_t stream)
-{
-    if (M > 16 || d_in % 128 != 0) return 1;
-    // Measured on MI355X (4096 x 4096, 11008 x 4096, 4096 x 11008; 1 and 16 tokens): with the plain
-    // kernel's loads in the coalesced lane mapping the staged kernel only wins where it saves real
-    // work, in column mode with X small enough for LDS (fp16(X * v_col) is then formed once per
-    // workgroup instead of once per step: 18.8 against 22.1 us on 11008 x 4096).  Everywhere else
-    // the plain kernel is as fast or up to 6 % faster (no staging phase before the first MFMA).
-    const bool staged_pays = AXIS == 1 && M * d_in <= 24576;
-    if (tune_value("skinny_staged", staged_pays ? 1 : 0) == 0) return 1;
-    // Measured on MI355X: 8 waves with 2 steps in flight each is the best general choice; when a
-    // layer is wide (d_in >= 8192) but has few workgroups (<= 2 per CU) 16 waves fill the CU better.
-    const bool wide_few = d_in >= 8192 && (d_out + 15) / 16 <= 512;
-    // (not in column mode with X read through L2: that variant needs more than the 128 registers
-    // a 16-wave workgroup leaves per lane and spills - measured 37 us against 24 us with 8 waves)
-    const bool x_small = M * d_in <= 24576;
-    constexpr int XC = AXIS == 1 ? 2 : 1;             // LDS copies of X
-    const bool col16_ok = x_small && staged_lds_bytes(16, XC, true, M, d_in) != 0;   // X fits LDS at 16 waves
-    const int waves = tune_value("stg_waves", wide_few && (AXIS == 0 || col16_ok) ? 16 : 8);
-    const bool want_x = tune_value("stg_x", 1) != 0;
-    size_t lds = want_x ? staged_lds_bytes(waves, XC, true, M, d_in) : 0;
-    const bool stage_x = lds != 0 && x_small;
-    if (!stage_x) lds = staged_lds_bytes(waves, XC, false, M, d_in);
-    // Row mode, small batch, exactly four steps per wave (d_in = 4096 at 8 waves): all four in
-    // flight from the start is 3 % faster than a ring of two (same-run A/B); elsewhere it makes no
-    // difference or loses (column mode and larger batches carry more registers per step).
-    const int depth = tune_value("stg_depth", (AXIS == 0 && stage_x && d_in / 128 == 4 * waves) ? 4 : 2);
-    if (lds == 0) return 1;
-#define PDELTA_STG(WAVES, DEPTH)                                                                        \
-    return stage_x ? launch_staged<XDT, AXIS, WAVES, DEPTH, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, \
-                                                                   y_dtype, lds, stream)                  \
-                   : launch_staged<XDT, AXIS, WAVES, DEPTH, false>(X, W_b, B_packed, v, Y, M, d_out, d_in, \
-                                                                    y_dtype, lds, stream)
-    if (waves == 4) {
-        if (depth == 8) PDELTA_STG(4, 8);
-        PDELTA_STG(4, 4);
-    }
-    if (waves == 16) PDELTA_STG(16, 2);
-    if (depth == 2) PDELTA_STG(8, 2);
-    if (depth == 6) PDELTA_STG(8, 6);
-    PDELTA_STG(8, 4);
-#undef PDELTA_STG
-}
-
 template <int XDT, int AXIS, int MT, int WAVES, int DEPTH, bool K128>
 static int launch_one(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                       void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
@@ -605,40 +453,11 @@ static int launch_one(const void* X, const void* W_b, const uint32_t* B_packed, 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int XDT, int AXIS, bool K128>
-static int launch_by_tokens(const void* X, const void* W_b, const uint32_t* B_packed,
-                            const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in,
-                            int y_dtype, hipStream_t stream)
-{
-#define PDELTA_GO(MT, WAVES, DEPTH) \
-    return launch_one<XDT, AXIS, MT, WAVES, DEPTH, K128>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-    const int waves = tune_value("skinny_waves", 8);
-    // steps in flight per wave: two, except row mode at more than 8 tokens, where one is 3-4 %
-    // faster (measured; the X loads double the bytes in flight per step)
-    const int depth = tune_value("skinny_depth", (AXIS == 0 && M > 8) ? 1 : 2);
-    if (M <= 16) {
-        if (waves == 4) {
-            if (depth == 4) PDELTA_GO(1, 4, 4);
-            if (depth == 6) PDELTA_GO(1, 4, 6);
-            PDELTA_GO(1, 4, 2);
-        }
-        if (waves == 16) PDELTA_GO(1, 16, 2);
-        if (depth == 1) PDELTA_GO(1, 8, 1);
-        if (depth == 3) PDELTA_GO(1, 8, 3);
-        if (depth == 4) PDELTA_GO(1, 8, 4);
-        PDELTA_GO(1, 8, 2);
-    }
-    if (M <= 32) PDELTA_GO(2, 8, 2);
-    if (M <= 48) PDELTA_GO(3, 8, 1);
-    PDELTA_GO(4, 8, 1);
-#undef PDELTA_GO
-}
-
 int launch_linear_skinny_batch(int x_dtype, int y_dtype, const pdelta_layer* layers_host,
                                const pdelta_layer* layers_device, int n_layers, int64_t M,
                                hipStream_t stream)
 {
-    // applicable when every layer can use the staged kernel (sign slab in LDS); X goes to LDS too
+    // applicable when every layer's workgroups can be staged (sign slab in LDS); X goes to LDS too
     // when it is small enough in every layer, else all layers read it through L2
     if (M > 16 || tune_value("skinny_batch", 1) == 0) return 1;
     bool stage_x = true;
@@ -668,72 +487,49 @@ int launch_linear_skinny_batch(int x_dtype, int y_dtype, const pdelta_layer* lay
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Grouped (blockwise / scalar) scales, M <= kSkinnyMaxM: the staged kernel when it applies (up to
-// 16 tokens, d_in a multiple of 128, slabs fit LDS), else the plain kernel.
-template <int XDT>
-static int launch_group(int y_dtype, const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
-                        void* Y, int64_t M, int64_t d_out, int64_t d_in, int v_stride, int g_shift,
-                        hipStream_t stream)
+// What linear_skinny_dma_kernel leaves: one or two tokens on many rows with row scales, and d_in that is
+// not a multiple of 128.  Two steps in flight per wave, except row mode above 8 tokens, where one is 3-4 % faster (the X
+// loads double the bytes in flight per step), and above 32 tokens (registers).
+template <int XDT, int AXIS>
+static int launch_plain(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                        int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
-    if (M <= 16 && d_in % 128 == 0 && tune_value("skinny_staged", 1) != 0) {
-        const int64_t scale_halves = 16 * (g_shift >= 31 ? 1 : (d_in >> g_shift));
-        const int xc = x_copies_of(2, XDT);
-        size_t lds = M * d_in <= 24576 ? staged_lds_bytes(8, xc, true, M, d_in, scale_halves) : 0;
-        const bool stage_x = lds != 0;
-        if (!stage_x) lds = staged_lds_bytes(8, xc, false, M, d_in, scale_halves);
-        if (lds != 0)
-            return stage_x ? launch_staged<XDT, 2, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, lds,
-                                                               stream, v_stride, g_shift)
-                           : launch_staged<XDT, 2, 8, 2, false>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, lds,
-                                                                stream, v_stride, g_shift);
-    }
-#define PDELTA_GO(MT, DEPTH)                                                                                   \
-    return d_in % 128 == 0                                                                                     \
-               ? launch_one<XDT, 2, MT, 8, DEPTH, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, \
-                                                        v_stride, g_shift)                                     \
-               : launch_one<XDT, 2, MT, 8, DEPTH, false>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, \
-                                                         v_stride, g_shift)
-    if (M <= 16) PDELTA_GO(1, 2);
-    if (M <= 32) PDELTA_GO(2, 2);
-    if (M <= 48) PDELTA_GO(3, 1);
-    PDELTA_GO(4, 1);
+#define PDELTA_GO(MT, DEPTH, K128) \
+    return launch_one<XDT, AXIS, MT, 8, DEPTH, K128>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift)
+    if (AXIS == 0 && M <= 2 && d_in % 128 == 0) PDELTA_GO(1, 2, true);
+    if (AXIS == 0 && M > 8 && M <= 16) PDELTA_GO(1, 1, false);
+    if (M <= 16) PDELTA_GO(1, 2, false);
+    if (M <= 32) PDELTA_GO(2, 2, false);
+    if (M <= 48) PDELTA_GO(3, 1, false);
+    PDELTA_GO(4, 1, false);
 #undef PDELTA_GO
+}
+
+template <int XDT>
+static int launch_axis(int axis, const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                       int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
+{
+    const int rc = launch_linear_skinny_dma(XDT, y_dtype, axis, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
+    if (rc != 1) return rc;
+    if (axis == 0) return launch_plain<XDT, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
+    if (axis == 1) return launch_plain<XDT, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
+    return launch_plain<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
 }
 
 int launch_linear_skinny_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                                const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                                int64_t d_out, int64_t d_in, int v_stride, int g_shift, hipStream_t stream)
 {
-    if (x_dtype == kBF16)
-        return launch_group<kBF16>(y_dtype, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
-    return launch_group<kF16>(y_dtype, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
+    return x_dtype == kBF16 ? launch_axis<kBF16>(2, X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
+                            : launch_axis<kF16>(2, X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
 }
 
 int launch_linear_skinny(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                          const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                          int64_t d_out, int64_t d_in, hipStream_t stream)
 {
-    const bool k128 = d_in % 128 == 0;
-    {
-        int rc = 1;
-        if (x_dtype == kBF16)
-            rc = axis == 0 ? try_staged<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-                           : try_staged<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-        else
-            rc = axis == 0 ? try_staged<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-                           : try_staged<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-        if (rc != 1) return rc;
-    }
-#define PDELTA_SEL(XDT, AXIS)                                                                      \
-    return k128 ? launch_by_tokens<XDT, AXIS, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream) \
-                : launch_by_tokens<XDT, AXIS, false>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream)
-    if (x_dtype == kBF16) {
-        if (axis == 0) PDELTA_SEL(kBF16, 0);
-        PDELTA_SEL(kBF16, 1);
-    }
-    if (axis == 0) PDELTA_SEL(kF16, 0);
-    PDELTA_SEL(kF16, 1);
-#undef PDELTA_SEL
+    return x_dtype == kBF16 ? launch_axis<kBF16>(axis, X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, stream)
+                            : launch_axis<kF16>(axis, X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, stream);
 }
 
 }  // namespace pdelta

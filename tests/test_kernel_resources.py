@@ -33,3 +33,10 @@ def test_prefill_kernels_do_not_spill(tmp_path):
     assert sum("linear_gemm_big_kernel" in n for n in found) == 6            # two operand types, three kinds of scales
     for name, entry in found.items():
         assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
+
+
+def test_decode_kernels_with_direct_loads_do_not_spill(tmp_path):
+    found = {n: e for n, e in kernels(tmp_path).items() if "linear_skinny_dma_kernel" in n}
+    assert len(found) == 72                                          # two operand types, three kinds of scales, 4 x 3 tiles
+    for name, entry in found.items():
+        assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
