@@ -95,6 +95,11 @@ int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const 
                        const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                        int64_t d_out, int64_t d_in, PrefillSplit ps, hipStream_t stream);
 
+// The same on 64 x 64 tiles with the work of a workgroup split by role; d_in a multiple of 128.  axis 2: blockwise scales.
+int launch_linear_gemm_roles(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b, const uint32_t* B_packed,
+                             const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in, int v_stride, int g_shift,
+                             hipStream_t stream);
+
 // The same on 256 x 256 tiles with direct loads into LDS; axis 2: blockwise scales.  The first `whole`
 // tiles are computed in one go, the other `split` ones in `parts` pieces of d_in each, whose fp32
 // sums go through the workspace.  parts = 0: another kernel is the better one, or the only one.

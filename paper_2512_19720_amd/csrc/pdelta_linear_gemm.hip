@@ -18,7 +18,8 @@
 //                             other multiplies: short batches (BM = 128) and the second
 //                             implementation behind the gemm_pipe=0 switch;
 //   linear_gemm_small_kernel  64 x 64 tiles with a ring of steps in flight, for grids that the
-//                             big tile cannot fill.
+//                             big tile cannot fill; with at most one tile per CU (and d_in a multiple of 128) the
+//                             kernel of pdelta_linear_gemm_roles.hip takes those.
 //
 // Workgroup -> tile map.  Hardware deals consecutive workgroups round-robin to the 8 XCDs, each
 // with its own L2.  Workgroup w therefore belongs to XCD x = w % 8; its x-local index j = w / 8
@@ -703,6 +704,11 @@ static int launch_gemm_small(const void* X, const void* W_b, const uint32_t* B_p
                              hipStream_t stream, int v_stride = 0, int g_shift = 31)
 {
     const int m_tiles = (int)((M + 63) / 64), n_tiles = (int)((d_out + 63) / 64);
+    // At most one tile per CU: the kernel with roles, of which a CU holds one workgroup (251 x 4096 x 4096 bf16 32.5 -> 25.2
+    // us); more tiles: several workgroups per CU overlap better (70 x 11008 x 4096, 344 tiles: 47 us here, 51 there).
+    const int roles = tune_value("gemm_roles", -1);
+    if (d_in % 128 == 0 && roles != 0 && (roles == 1 || (int64_t)m_tiles * n_tiles <= 256))
+        return launch_linear_gemm_roles(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
     const int n_groups = (n_tiles + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)((int64_t)n_groups * kXcds * m_tiles));
     // four steps in flight (eight were measured too: 3-10 % slower, they halve the occupancy)

@@ -363,13 +363,13 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // Which calls run here, and how many tiles are split.  Both sides are priced with what was measured
 // (us, 256 CUs, steps of 64 inputs): here a step takes 1.75 (fp16) or 1.95 (bf16), a call 8 beside its
 // steps, a split 8 more for its second launch and 0.06 per part for the sums that it writes and reads;
-// the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernel 0.34 a step for each of its
-// workgroups on a CU (0.42 / 0.47 at least) and 3 a call.  Against the latter a split pays 0.4 more per part: it
+// the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernels 3 a call and 0.29 / 0.31 a step (0.045 more
+// when every CU has a tile), above one tile per CU 0.34 for each.  Against the latter a split pays 0.1 more per part: it
 // has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, changing
 // inputs, this kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 223-230 against 230-237, 777 x
 // 4096 x 11008 blockwise (64 tiles in 4 parts) 127 against 254, 1024 x 4096 x 4096 60 against 87, 256 x 512 x 8192 (2 tiles
-// in 16 parts) 36 against 58.  Below the line: 256 x 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 26, 512 x 300 x
-// 3968 32 against 26, 251 x 4096 x 4096 32 against 30.
+// in 16 parts) 36 against 43, 448 x 960 x 8192 fp16 blockwise (8 tiles in 16 parts) 38 against 45.5.  Below the line: 256 x
+// 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 23, 402 x 384 x 5760 fp16 31 against 23, 251 x 4096 x 4096 32 against 25.
 BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed)
 {
     const BigSplit none{0, 0, 0};
@@ -393,8 +393,9 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     const int64_t tiles128 = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int64_t tiles64 = ((M + 63) / 64) * ((d_out + 63) / 64);
     if (tiles128 <= 128) {
-        const double small = 3 + n * std::max(x_dtype == kBF16 ? 0.47 : 0.42, 0.34 * (double)tiles64 / 256);
-        return best + (sp.split > 0 ? 0.4 * sp.parts : 0) < small ? sp : none;
+        const double small = tiles64 <= 256 ? 3 + n * ((x_dtype == kBF16 ? 0.31 : 0.29) + 0.045 * (double)tiles64 / 256)
+                                            : 3 + n * 0.34 * (double)tiles64 / 256;
+        return best + (sp.split > 0 ? 0.1 * sp.parts : 0) < small ? sp : none;
     }
     const double pipe = 15 + n * (double)((tiles128 + 255) / 256) * (x_dtype == kBF16 ? 1.08 : 1.0);
     return best < 0.97 * pipe ? sp : none;

@@ -49,6 +49,31 @@ def test_whole_tiles_have_the_bits_of_the_other_kernels(M, d_out, d_in, dtype, m
             assert torch.equal(other, got[0]), f"axis={axis}"
 
 
+# the 64 x 64 kernel with roles: one pair of steps, as many as are held in registers and in LDS, one more, and many; tiles
+# cut in both directions.  Bit for bit the 256 x 256 kernel's whole tiles
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("M,d_out,d_in", [(65, 63, 128), (66, 65, 256), (128, 64, 384), (97, 130, 512), (129, 72, 640), (70, 200, 4224)])
+def test_roles_kernel(M, d_out, d_in, dtype, monkeypatch):
+    L = make_case(d_out, d_in, M, dtype, "row", 11 * M + d_out + d_in)
+    d = L["d"]
+    v_bits = orc.pack_group(L["dW"], L["dW"] * 0, 32, False, dtype)[1]
+    vg = f16_dev(v_bits)
+    calls = [(lambda y: pd.pdelta_linear_row(d["X"], d["W_b"], d["B"], d["v_row"], out=y), lambda: orc.linear(L["X"], L["W_b"], L["B"], L["v_row"], orc.ROW, L["dtype"])),
+             (lambda y: pd.pdelta_linear_col(d["X"], d["W_b"], d["B"], d["v_col"], out=y), lambda: orc.linear(L["X"], L["W_b"], L["B"], L["v_col"], orc.COL, L["dtype"])),
+             (lambda y: pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], vg, 32, out=y), lambda: orc.linear_group(L["X"], L["W_b"], L["B"], v_bits, 32, dtype))]
+    for k, (call, oracle) in enumerate(calls):
+        ref = oracle()
+        for y_dtype in (torch.float32, d["X"].dtype):
+            got = []
+            for tune in ("gemm_big=0,gemm_small=1,gemm_roles=1", "gemm_big=1"):
+                monkeypatch.setenv("PDELTA_TUNE", tune)
+                got.append(torch.full((M, d_out), float("nan"), dtype=y_dtype, device=DEV))
+                call(got[-1])
+            check_y(got[0], ref, f"roles kind {k} M={M} {d_out}x{d_in} dt={dtype}")
+            assert torch.equal(got[0].view(torch.uint8), got[1].view(torch.uint8)), f"kind {k} M={M} {d_out}x{d_in} dt={dtype}"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("group,shared", [(32, False), (64, False), (128, True), (640, False), (640, True)])
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])

@@ -35,8 +35,8 @@ def test_prefill_kernels_do_not_spill(tmp_path):
         assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
 
 
-def test_decode_kernels_with_direct_loads_do_not_spill(tmp_path):
-    found = {n: e for n, e in kernels(tmp_path).items() if "linear_skinny_dma_kernel" in n}
-    assert len(found) == 72                                          # two operand types, three kinds of scales, 4 x 3 tiles
+def test_kernels_with_direct_loads_do_not_spill(tmp_path):
+    found = {n: e for n, e in kernels(tmp_path).items() if "linear_skinny_dma_kernel" in n or "linear_gemm_roles_kernel" in n}
+    assert len(found) == 72 + 6                                      # two operand types, three kinds of scales; 4 x 3 decode tiles
     for name, entry in found.items():
         assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
