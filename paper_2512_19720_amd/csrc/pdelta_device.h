@@ -105,6 +105,19 @@ __device__ __forceinline__ T* as_global_per_lane(T* p) {
     return (T*)g;
 }
 
+// Weights that a call reads (writes) once, NT: marked as non-temporal.  That pays where they do not come out of a cache
+// anyway: see streams_weights() on the host side.
+template <bool NT, typename T>
+__device__ __forceinline__ T load_weights(const T* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void store_weights(T* p, T x) {
+    if constexpr (NT) __builtin_nontemporal_store(x, p);
+    else *p = x;
+}
+
 // ---- wavefront reductions -------------------------------------------------------------------
 
 __device__ __forceinline__ float wave_sum(float x) {

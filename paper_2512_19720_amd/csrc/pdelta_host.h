@@ -9,6 +9,11 @@
 
 namespace pdelta {
 
+// Whether pack and patch read (and write) the weights of a call, this many in each matrix, as non-temporal: from 16 MiB on.
+// Seven layers of 704 x 640 packed at once (6 MiB, in the caches) take 17.6 us without and 19.2 with; two of 1024 x 4096
+// (16 MiB) 21.8 and 20.1; one of 2048 x 4096 patched (16 MiB) 8.7 and 7.8, and above it is 3 to 18 % everywhere.
+inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)16 << 20; }
+
 // Bytes of fp64 partial sums pdelta_pack writes for these dimensions.
 size_t pack_workspace_bytes(int64_t d_out, int64_t d_in);
 

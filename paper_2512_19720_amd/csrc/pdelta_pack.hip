@@ -32,7 +32,7 @@ constexpr int kPackSignWords = kPackTileCols / 32;           // 32 words per til
 // ahead a wave loads (1, 2 or 4 rows: 4.4-4.8, 4.3-4.8, 3.7-3.9 TB/s, the last at 3 waves per SIMD),
 // on the tile width (512 or 1024 columns at 4-7 waves per SIMD), on the tile height (64 to 512
 // rows) or on the arithmetic (with the sums and compares taken out it streams at the same
-// 4.5 TB/s; the vector ALUs are 36-42 % busy).  Two rows ahead at 4 waves per SIMD it is.
+// 4.5 TB/s; the vector ALUs are 36-42 % busy; all before the loads were non-temporal).  Two rows ahead at 4 waves per SIMD it is.
 constexpr int kPackAhead = 2;                                // rows in flight per wave
 constexpr int kPackOcc = 4;                                  // waves per SIMD the registers allow
 constexpr int kPackBatchWaves = 4;                           // waves per workgroup of the batched kernel
@@ -60,10 +60,12 @@ struct PackRow {          // both matrices' 16 bytes per lane for the two chunks
 // Work of one workgroup of WAVES waves: a tile of WAVES * 8 * blocks rows x 1024 columns.
 // Wave w owns 8 * blocks consecutive rows and walks them in blocks of 8; lane l owns columns
 // chunk*512 + 8l .. 8l+7 of each chunk: one 16-byte load per matrix, one sign byte.  Loads are
-// unconditional, two rows ahead of the arithmetic, across block boundaries.  After each block
+// unconditional, two rows ahead of the arithmetic, across block boundaries, NT: non-temporal (a weight is
+// read once: a block of seven layers fp16 182.7 -> 167.5 us, 5.0 TB/s; with the sign words stored so as well 172.3; four
+// rows ahead spills: 252.6).  After each block
 // the wave writes its 8 x 128 bytes of sign words and its 8 row sums; column sums stay in
 // registers until the end of the tile, where the waves meet once in LDS.
-template <int DT, int WAVES>
+template <int DT, int WAVES, bool NT>
 __device__ __forceinline__ void
 pack_tile(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ W_b, int d_out, int d_in,
           uint32_t* __restrict__ B_packed,
@@ -98,8 +100,8 @@ pack_tile(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ W_b, in
         const int64_t base = (int64_t)min(row, d_out - 1) * d_in;
 #pragma unroll
         for (int c = 0; c < kPackChunks; ++c) {
-            R.a[c] = *(const uint4v*)((row_live ? lane_f[c] : lane_b[c]) + base);
-            R.b[c] = *(const uint4v*)(lane_b[c] + base);
+            R.a[c] = load_weights<NT>((const uint4v*)((row_live ? lane_f[c] : lane_b[c]) + base));
+            R.b[c] = load_weights<NT>((const uint4v*)(lane_b[c] + base));
         }
     };
 
@@ -229,7 +231,7 @@ pack_tile(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ W_b, in
     }
 }
 
-template <int DT, int WAVES>
+template <int DT, int WAVES, bool NT>
 __global__ void __launch_bounds__(WAVES * kWave, kPackOcc)
 pack_main_kernel(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ W_b,
                  int d_out, int d_in, uint32_t* __restrict__ B_packed,
@@ -238,12 +240,12 @@ pack_main_kernel(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ 
 {
     // consecutive workgroups take the column tiles of one row tile: rows are read end to end
     const int id = (int)blockIdx.x;
-    pack_tile<DT, WAVES>(W_f, W_b, d_out, d_in, B_packed, row_part, col_part, id / n_col_tiles,
+    pack_tile<DT, WAVES, NT>(W_f, W_b, d_out, d_in, B_packed, row_part, col_part, id / n_col_tiles,
                          id % n_col_tiles, blocks);
 }
 
 // Many layers in one launch: workgroup b works on the last job whose first_tile is <= b.
-template <int DT>
+template <int DT, bool NT>
 __global__ void __launch_bounds__(kPackBatchWaves * kWave, kPackOcc)
 pack_main_batch_kernel(const pdelta_pack_job* __restrict__ jobs, int n_jobs)
 {
@@ -259,7 +261,7 @@ pack_main_batch_kernel(const pdelta_pack_job* __restrict__ jobs, int n_jobs)
     const int n_ct = (d_in + kPackTileCols - 1) / kPackTileCols;
     double* row_part = as_global((double*)J.workspace);
     double* col_part = row_part + (int64_t)n_ct * d_out;
-    pack_tile<DT, kPackBatchWaves>(as_global((const uint16_t*)J.W_f), as_global((const uint16_t*)J.W_b), d_out, d_in,
+    pack_tile<DT, kPackBatchWaves, NT>(as_global((const uint16_t*)J.W_f), as_global((const uint16_t*)J.W_b), d_out, d_in,
                      as_global(J.B_packed),
                      J.v_row ? row_part : (double*)nullptr, J.v_col ? col_part : (double*)nullptr,
                      id / n_ct, id % n_ct, J.tile_blocks);
@@ -370,7 +372,9 @@ static int launch_pack(const void* W_f, const void* W_b, int64_t d_out, int64_t 
     double* row_part = (double*)workspace;
     double* col_part = row_part + n_ct * d_out;
     const bool want_any = v_row != nullptr || v_col != nullptr;
-    auto main_kernel = waves == 4 ? pack_main_kernel<DT, 4> : pack_main_kernel<DT, 8>;
+    const bool nt = streams_weights(d_out * d_in);
+    auto main_kernel = waves == 4 ? (nt ? pack_main_kernel<DT, 4, true> : pack_main_kernel<DT, 4, false>)
+                                  : (nt ? pack_main_kernel<DT, 8, true> : pack_main_kernel<DT, 8, false>);
     hipLaunchKernelGGL(main_kernel, dim3((unsigned)(n_rt * n_ct)), dim3(waves * kWave), 0,
                        stream, (const uint16_t*)W_f, (const uint16_t*)W_b, (int)d_out, (int)d_in, B_packed,
                        v_row ? row_part : (double*)nullptr, v_col ? col_part : (double*)nullptr, blocks,
@@ -406,13 +410,15 @@ int launch_pack_batch(int w_dtype, const pdelta_pack_job* jobs_host, const pdelt
     const int64_t tiles = last.first_tile + pack_batch_tiles(last.d_out, last.d_in, last.tile_blocks);
     const int64_t fin = last.first_fin_block + pack_batch_fin_blocks(last.d_out, last.d_in);
     bool want_any = false;
-    for (int j = 0; j < n_jobs; ++j) want_any = want_any || jobs_host[j].v_row || jobs_host[j].v_col;
-    if (w_dtype == kBF16)
-        hipLaunchKernelGGL(pack_main_batch_kernel<kBF16>, dim3((unsigned)tiles), dim3(kPackBatchWaves * kWave), 0, stream,
-                           jobs_device, n_jobs);
-    else
-        hipLaunchKernelGGL(pack_main_batch_kernel<kF16>, dim3((unsigned)tiles), dim3(kPackBatchWaves * kWave), 0, stream,
-                           jobs_device, n_jobs);
+    int64_t weights = 0;
+    for (int j = 0; j < n_jobs; ++j) {
+        want_any = want_any || jobs_host[j].v_row || jobs_host[j].v_col;
+        weights += jobs_host[j].d_out * jobs_host[j].d_in;
+    }
+    const bool nt = streams_weights(weights);
+    auto main_kernel = w_dtype == kBF16 ? (nt ? pack_main_batch_kernel<kBF16, true> : pack_main_batch_kernel<kBF16, false>)
+                                        : (nt ? pack_main_batch_kernel<kF16, true> : pack_main_batch_kernel<kF16, false>);
+    hipLaunchKernelGGL(main_kernel, dim3((unsigned)tiles), dim3(kPackBatchWaves * kWave), 0, stream, jobs_device, n_jobs);
     if (want_any) {
         if (w_dtype == kBF16)
             hipLaunchKernelGGL(pack_finalize_batch_kernel<kBF16>, dim3((unsigned)fin), dim3(64 * kFinGroups), 0,

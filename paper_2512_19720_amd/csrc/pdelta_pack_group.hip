@@ -23,7 +23,7 @@ namespace pdelta {
 
 constexpr int kPgWaves = 4;
 
-template <int DT>
+template <int DT, bool NT>
 __global__ void __launch_bounds__(kPgWaves * kWave)
 pack_group_kernel(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__ W_b, int d_out, int d_in,
                   uint32_t* __restrict__ B_packed, uint16_t* __restrict__ v, double* __restrict__ partial,
@@ -41,13 +41,14 @@ pack_group_kernel(const uint16_t* __restrict__ W_f, const uint16_t* __restrict__
     const bool inside_chunk = group <= 512 && (group & (group - 1)) == 0;   // wave-uniform; else: a whole short row
 
     // a lane past the end of the row reads a clamped address of W_b for both operands: its
-    // differences are exactly zero and nothing of it is stored (loads stay unconditional)
+    // differences are exactly zero and nothing of it is stored (loads stay unconditional).  NT: 11008 x 4096 bf16,
+    // groups of 128, 40.3 -> 37.2 us
     auto load = [&](uint4v& a, uint4v& b, int chunk) {
         const int col = (chunk << 9) + lane * 8;
         const int cc = min(col, d_in - 8);
         const uint16_t* f_or_b = col < d_in ? f_row : b_row;
-        b = *(const uint4v*)(b_row + cc);
-        a = *(const uint4v*)(f_or_b + cc);
+        b = load_weights<NT>((const uint4v*)(b_row + cc));
+        a = load_weights<NT>((const uint4v*)(f_or_b + cc));
     };
     uint4v a0, b0, a1, b1;
     load(a0, b0, 0);
@@ -133,7 +134,8 @@ static int launch_pack_group_dt(const void* W_f, const void* W_b, int64_t d_out,
 {
     const int n_groups = (int)(d_in / group);
     double* partial = shared_rows ? (double*)workspace : nullptr;
-    hipLaunchKernelGGL(pack_group_kernel<DT>, dim3((unsigned)((d_out + kPgWaves - 1) / kPgWaves)),
+    auto kernel = streams_weights(d_out * d_in) ? pack_group_kernel<DT, true> : pack_group_kernel<DT, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + kPgWaves - 1) / kPgWaves)),
                        dim3(kPgWaves * kWave), 0, stream, (const uint16_t*)W_f, (const uint16_t*)W_b, (int)d_out,
                        (int)d_in, B_packed, v, partial, (int)group, n_groups);
     if (shared_rows)

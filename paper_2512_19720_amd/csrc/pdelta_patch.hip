@@ -141,13 +141,15 @@ __device__ __forceinline__ void patch_values(const PatchUnits<N>& S, uint4v (&ou
 // by u).  Units are counted from the start of row `row_base`: the passes that start at first_rel,
 // first_rel + stride, ... below last_rel, each clipped at last_rel.  A pass covers 1024
 // consecutive units: thread t takes units t, t + 256, t + 512, t + 768 of it, issues all its loads,
-// sums, stores.  Measured on MI355X this plain shape (what a library elementwise kernel does)
+// sums, stores.  Every weight is read once and written once, so both are marked as non-temporal (NT): a block of seven layers
+// bf16 151.6 -> 133.3 us (6.3 TB/s), 4096 x 4096 bf16 15.8 -> 13.6, 1024 x 4096 5.1 -> 4.8 (signs, of which a 128-byte line
+// serves four waves, are not: 134.8).  Measured on MI355X this plain shape (what a library elementwise kernel does)
 // streams 5-8 % faster than walking rows with the next step's loads in flight, and equals the
 // box's in-place update rate.  Loads are unconditional (unit index clamped to last_rel - 1); only
 // stores are guarded.
 // AXIS 2: blockwise scales v[row * v_stride + (col >> g_shift)] (groups are multiples of 8 inputs,
 // so the eight weights of a unit share one scale).
-template <int DT, int AXIS>
+template <int DT, int AXIS, bool NT>
 __device__ __forceinline__ void
 patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint16_t* __restrict__ v,
             uint16_t* W_out, int d_in, int row_base, int first_rel, int last_rel, int stride, int v_stride = 0,
@@ -168,7 +170,7 @@ patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint
             const int r = rc / upr;
             const int col = (rc - r * upr) * 8;
             const int row = row_base + r;
-            S.w[j] = *(const uint4v*)(w_base + (int64_t)rc * 8);
+            S.w[j] = load_weights<NT>((const uint4v*)(w_base + (int64_t)rc * 8));
             S.byte[j] = b_base[rc];
             S.v16[j] = AXIS == 0   ? (uint32_t)v[row]
                        : AXIS == 2 ? (uint32_t)v[(int64_t)row * v_stride + (col >> g_shift)]
@@ -179,12 +181,12 @@ patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint
         patch_values<DT, AXIS, kPatchUnits>(S, out);
 #pragma unroll
         for (int j = 0; j < kPatchUnits; ++j)
-            if (rel[j] < last_rel) *(uint4v*)(out_base + (int64_t)rel[j] * 8) = out[j];
+            if (rel[j] < last_rel) store_weights<NT>((uint4v*)(out_base + (int64_t)rel[j] * 8), out[j]);
     }
 }
 
 // One layer: workgroup b patches units 1024 b .. 1024 b + 1023.
-template <int DT, int AXIS>
+template <int DT, int AXIS, bool NT>
 __global__ void __launch_bounds__(kPatchThreads)
 patch_kernel(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint16_t* __restrict__ v,
              uint16_t* W_out, int d_in, int64_t total_units, int v_stride, int g_shift)
@@ -194,7 +196,7 @@ patch_kernel(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uin
     const int64_t last = min(first + kPatchChunk, total_units);
     const int row_base = (int)(first / upr);
     const int64_t unit0 = (int64_t)row_base * upr;
-    patch_units<DT, AXIS>(W_b, B_bytes, v, W_out, d_in, row_base, (int)(first - unit0), (int)(last - unit0),
+    patch_units<DT, AXIS, NT>(W_b, B_bytes, v, W_out, d_in, row_base, (int)(first - unit0), (int)(last - unit0),
                           kPatchChunk, v_stride, g_shift);
 }
 
@@ -202,7 +204,7 @@ patch_kernel(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uin
 // first_block is <= b, and kPatchBatchParts workgroups share its units in equal contiguous parts
 // (at d_in = 4096 a part is exactly one pass; dealing the passes out round-robin instead was
 // measured slower, 5.15 against 5.33 TB/s on a 7B-shaped stack).  The layer's Y field is W_out.
-template <int DT>
+template <int DT, bool NT>
 __global__ void __launch_bounds__(kPatchThreads)
 patch_batch_kernel(const pdelta_layer* __restrict__ layers, int n_layers)
 {
@@ -222,8 +224,8 @@ patch_batch_kernel(const pdelta_layer* __restrict__ layers, int n_layers)
     uint16_t* W_out = as_global((uint16_t*)L.Y);
     const int per_part = (block_units + kPatchBatchParts - 1) / kPatchBatchParts;
     const int first = part * per_part, last = min(first + per_part, block_units);
-    if (L.axis == 0) patch_units<DT, 0>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
-    else patch_units<DT, 1>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
+    if (L.axis == 0) patch_units<DT, 0, NT>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
+    else patch_units<DT, 1, NT>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
 }
 
 // Returns 1 when the batch has too many blocks for one grid (the caller then patches layer by layer).
@@ -234,10 +236,12 @@ int launch_patch_batch(int w_dtype, const pdelta_layer* layers_host, const pdelt
     const int64_t total = last.first_block + (last.d_out + kPatchBatchRows - 1) / kPatchBatchRows;
     if (total * kPatchBatchParts > 0x7FFFFFFF) return 1;
     const dim3 grid((unsigned)(total * kPatchBatchParts));
-    if (w_dtype == kBF16)
-        hipLaunchKernelGGL(patch_batch_kernel<kBF16>, grid, dim3(kPatchThreads), 0, stream, layers_device, n_layers);
-    else
-        hipLaunchKernelGGL(patch_batch_kernel<kF16>, grid, dim3(kPatchThreads), 0, stream, layers_device, n_layers);
+    int64_t weights = 0;
+    for (int l = 0; l < n_layers; ++l) weights += layers_host[l].d_out * layers_host[l].d_in;
+    const bool nt = streams_weights(weights);
+    auto kernel = w_dtype == kBF16 ? (nt ? patch_batch_kernel<kBF16, true> : patch_batch_kernel<kBF16, false>)
+                                   : (nt ? patch_batch_kernel<kF16, true> : patch_batch_kernel<kF16, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kPatchThreads), 0, stream, layers_device, n_layers);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -248,7 +252,8 @@ static int launch_patch(const void* W_b, const uint32_t* B_packed, const uint16_
     const int64_t total_units = d_out * (d_in / 8);
     const int64_t n_blocks = (total_units + kPatchChunk - 1) / kPatchChunk;
     if (n_blocks > 0x7FFFFFFF) return -1;             // 2^41 weights and more: not a layer
-    hipLaunchKernelGGL((patch_kernel<DT, AXIS>), dim3((unsigned)n_blocks), dim3(kPatchThreads), 0, stream,
+    auto kernel = streams_weights(d_out * d_in) ? patch_kernel<DT, AXIS, true> : patch_kernel<DT, AXIS, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(kPatchThreads), 0, stream,
                        (const uint16_t*)W_b, (const uint8_t*)B_packed, v, (uint16_t*)W_out, (int)d_in, total_units,
                        v_stride, g_shift);
     return hipGetLastError() == hipSuccess ? 0 : -1;
