@@ -243,14 +243,16 @@ int pdelta_pack_batch_plan(pdelta_pack_job* jobs_host, int32_t n_jobs)
 {
     using namespace pdelta;
     if (n_jobs < 0 || (n_jobs > 0 && jobs_host == nullptr)) return PDELTA_EINVAL;
+    for (int32_t j = 0; j < n_jobs; ++j)
+        if (const int rc = check_dims(jobs_host[j].d_out, jobs_host[j].d_in)) return rc;
+    const int tallest = pack_batch_tallest(jobs_host, n_jobs);
     int64_t tile = 0, fin = 0;
     for (int32_t j = 0; j < n_jobs; ++j) {
         pdelta_pack_job& J = jobs_host[j];
-        if (const int rc = check_dims(J.d_out, J.d_in)) return rc;
         if (tile > 0x7FFFFFFF || fin > 0x7FFFFFFF) return PDELTA_ESHAPE;
         J.first_tile = (int32_t)tile;
         J.first_fin_block = (int32_t)fin;
-        J.tile_blocks = pack_batch_tile_blocks(J.d_out);
+        J.tile_blocks = pack_batch_tile_blocks(J.d_out, tallest);
         J.reserved = 0;
         tile += pack_batch_tiles(J.d_out, J.d_in, J.tile_blocks);
         fin += pack_batch_fin_blocks(J.d_out, J.d_in);
@@ -274,8 +276,9 @@ int pdelta_pack_batch(const pdelta_pack_job* jobs_host, const pdelta_pack_job* j
         if (const int rc = pack_check(J.W_f, J.W_b, J.d_out, J.d_in, w_dtype, J.B_packed, J.v_row, J.v_col,
                                       J.workspace, J.workspace_bytes))
             return rc;
-        if (J.first_tile != (int32_t)tile || J.first_fin_block != (int32_t)fin ||
-            J.tile_blocks != pack_batch_tile_blocks(J.d_out))
+        bool planned = false;                                           // in a batch of any length (a part of one may be run)
+        for (int tallest = 16; tallest >= 4; tallest /= 2) planned = planned || J.tile_blocks == pack_batch_tile_blocks(J.d_out, tallest);
+        if (J.first_tile != (int32_t)tile || J.first_fin_block != (int32_t)fin || !planned)
             return PDELTA_EINVAL;                                       // not planned, or edited
         tile += pack_batch_tiles(J.d_out, J.d_in, J.tile_blocks);
         fin += pack_batch_fin_blocks(J.d_out, J.d_in);

@@ -27,7 +27,8 @@ constexpr size_t kPackScratchBytes = (size_t)16 << 20;
 int pack_static_scratch(void** ptr);
 
 // Batched pack: geometry helpers shared by the plan (host) and the launcher.
-int pack_batch_tile_blocks(int64_t d_out);
+int pack_batch_tile_blocks(int64_t d_out, int tallest);
+int pack_batch_tallest(const ::pdelta_pack_job* jobs, int n_jobs);
 int64_t pack_batch_tiles(int64_t d_out, int64_t d_in, int tile_blocks);
 int64_t pack_batch_fin_blocks(int64_t d_out, int64_t d_in);
 int launch_pack_batch(int w_dtype, const ::pdelta_pack_job* jobs_host, const ::pdelta_pack_job* jobs_device,

@@ -388,13 +388,24 @@ static int launch_pack(const void* W_f, const void* W_b, int64_t d_out, int64_t 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Tiles of a job in the batched kernels: 4 waves x tile_blocks blocks of 8 rows, 1024 columns
-// (512-row tiles for tall layers: fewest column partials, measured 5 % faster than 128 rows).
-int pack_batch_tile_blocks(int64_t d_out)
+// Tiles of a job in the batched kernels: 4 waves x tile_blocks blocks of 8 rows, 1024 columns.  Tall layers take 512 rows
+// (fewest column partials, measured 5 % faster than 128 on 224 layers), or 256 or 128 where the batch would otherwise have
+// fewer tiles than the chip has CUs (`tallest`, in blocks): two of 4096 x 4096 65.5 -> 26.7 us, six of 3000 x 1056 67 -> 34.
+int pack_batch_tile_blocks(int64_t d_out, int tallest)
 {
-    const int blocks = tune_value("pack_batch_blocks", d_out >= 2048 ? 16 : (d_out >= 512 ? 4 : 2));
+    const int blocks = tune_value("pack_batch_blocks", d_out >= 2048 ? tallest : (d_out >= 512 ? 4 : 2));
     const int least = kPackTileRows / (kPackBatchWaves * 8);        // 64-row tiles at least: the workspace is sized for them
     return blocks < least ? least : blocks;
+}
+int pack_batch_tallest(const pdelta_pack_job* jobs, int n_jobs)
+{
+    for (int tallest = 16; tallest > 4; tallest /= 2) {
+        int64_t tiles = 0;
+        for (int j = 0; j < n_jobs && tiles < 256; ++j)
+            tiles += pack_batch_tiles(jobs[j].d_out, jobs[j].d_in, pack_batch_tile_blocks(jobs[j].d_out, tallest));
+        if (tiles >= 256) return tallest;
+    }
+    return 4;
 }
 int64_t pack_batch_tiles(int64_t d_out, int64_t d_in, int tile_blocks)
 {

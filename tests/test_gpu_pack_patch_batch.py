@@ -111,3 +111,22 @@ def test_patch_batch_un_patch_restores_the_base_when_nothing_was_rounded():
     torch.cuda.synchronize()
     for it, b in zip(items, bases):
         assert torch.equal(it[0], b)
+
+
+# tile heights of tall layers: 512 rows where the batch fills the chip, else 256, else 128 (2100 x 64: 5, 9 and 17 tiles each)
+@pytest.mark.parametrize("n,blocks", [(52, 16), (29, 8), (15, 4)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_tile_heights_of_tall_layers(n, blocks, dtype):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n)
+    pairs = [tuple(torch.randn((2100, 64), generator=g, device="cuda:0").to(dtype) for _ in range(2)) for _ in range(n)]
+    plan = pd.pdelta_pack_batch_plan(pairs)
+    assert {plan.host[k].tile_blocks for k in range(n)} == {blocks}
+    want = [pd.pdelta_pack(f, b) for f, b in pairs]
+    for first in (n, 1):                              # all of the plan, then its first job alone
+        for t in plan.out:
+            for x in t:
+                x.zero_()
+        assert pd.lib().pdelta_pack_batch(plan.host, plan.device.data_ptr(), first, plan.w_dtype, torch.cuda.current_stream().cuda_stream) == pd.OK
+        for got, ref in zip(plan.out[:first], want):
+            assert all(torch.equal(a, b) for a, b in zip(got, ref))
