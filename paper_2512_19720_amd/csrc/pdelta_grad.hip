@@ -620,12 +620,38 @@ grad_reduce_kernel(const float* __restrict__ partial, float* __restrict__ grad, 
     if (w == 0 && i < n) grad[i] = (float)((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
 }
 
-// Bt[i][o / 32] bit (o % 32) = B[o][i / 32] bit (i % 32); d_out % 32 == 0.  A lane transposes one block of 32 x 32 bits
-// in registers (five rounds of masked swaps, 10 instructions for each of its words; ballots took eight times that); the
-// lanes of a wave take 64 consecutive words of each row, the four waves 128 rows, whose 16 bytes per row of Bt leave
-// through LDS as one store.  4096 x 4096: 5.4 us a launch (7.1 with ballots and 4-byte loads down the columns).
+// Bt[i][o / 32] bit (o % 32) = B[o][i / 32] bit (i % 32); d_out % 32 == 0.  A wave takes 64 rows
+// o and one word column: 32 ballots turn the lanes' words into the 64-bit columns.
 __global__ void __launch_bounds__(256)
 transpose_bits_kernel(const uint32_t* __restrict__ B, uint32_t* __restrict__ Bt, int d_out, int d_in)
+{
+    const int lane = threadIdx.x & 63;
+    const int wcol = blockIdx.x * 4 + (threadIdx.x >> 6);            // word column of B
+    const int wpr = d_in >> 5;
+    if (wcol >= wpr) return;                                        // whole wave
+    const int o = blockIdx.y * 64 + lane;
+    const uint32_t word = o < d_out ? B[(int64_t)o * wpr + wcol] : 0u;
+    unsigned long long mine = 0;
+#pragma unroll
+    for (int b = 0; b < 32; ++b) {
+        const unsigned long long m = __ballot((word >> b) & 1u);
+        if (lane == b) mine = m;
+    }
+    if (lane < 32) {
+        const int i = wcol * 32 + lane;
+        const int wpr_t = d_out >> 5;
+        const int w0 = blockIdx.y * 2;
+        Bt[(int64_t)i * wpr_t + w0] = (uint32_t)mine;
+        if (w0 + 1 < wpr_t) Bt[(int64_t)i * wpr_t + w0 + 1] = (uint32_t)(mine >> 32);
+    }
+}
+
+// The same for large matrices.  A lane transposes one block of 32 x 32 bits
+// in registers (five rounds of masked swaps, 10 instructions for each of its words; ballots took eight times that); the
+// lanes of a wave take 64 consecutive words of each row, the four waves 128 rows, whose 16 bytes per row of Bt leave
+// through LDS as one store.  4096 x 4096: 5.4 us a launch, 7.1 with ballots and 4-byte loads down the columns.
+__global__ void __launch_bounds__(256)
+transpose_bits_blocks_kernel(const uint32_t* __restrict__ B, uint32_t* __restrict__ Bt, int d_out, int d_in)
 {
     constexpr int COL = 32 * 4 + 4;                   // words per word column: [bit][row block], padded
     __shared__ __attribute__((aligned(16))) uint32_t out[64 * COL];
@@ -697,8 +723,15 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
         size_t off = (size_t)m_tiles * std::max(1, parts) * Nc * sizeof(float);
         off = (off + 255) & ~(size_t)255;
         uint32_t* Bt = (uint32_t*)((char*)workspace + off);
-        const dim3 grid((unsigned)((d_in / 32 + 63) / 64), (unsigned)((d_out + 127) / 128));
-        hipLaunchKernelGGL(transpose_bits_kernel, grid, dim3(256), 0, stream, B_packed, Bt, (int)d_out, (int)d_in);
+        // Above 2^23 signs by blocks in registers, whose few waves each take longer (col gradient of 256 tokens, ballots /
+        // blocks: 1024 x 1024 13.9 / 15.0 us, 2048 x 4096 18.7 / 18.9, 4096 x 4096 25.7 / 24.7, 4096 x 11008 41.5 / 34.6).
+        if (d_out * d_in > (int64_t)1 << 23) {
+            const dim3 grid((unsigned)((d_in / 32 + 63) / 64), (unsigned)((d_out + 127) / 128));
+            hipLaunchKernelGGL(transpose_bits_blocks_kernel, grid, dim3(256), 0, stream, B_packed, Bt, (int)d_out, (int)d_in);
+        } else {
+            const dim3 grid((unsigned)((d_in / 32 + 3) / 4), (unsigned)((d_out + 63) / 64));
+            hipLaunchKernelGGL(transpose_bits_kernel, grid, dim3(256), 0, stream, B_packed, Bt, (int)d_out, (int)d_in);
+        }
         bits = Bt;
     }
     const int64_t n_tiles = (Nc + kGradBN - 1) / kGradBN;
