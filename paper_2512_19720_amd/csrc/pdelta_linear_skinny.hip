@@ -440,6 +440,28 @@ static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M,
     if (stage_x) bytes += (size_t)M * (K + 8) * 2 * x_copies;
     return bytes <= kStagedLdsLimit ? bytes : 0;
 }
+
+// One layer, column mode, X and fp16(X v) in LDS: for one or two tokens (see launch_plain).
+template <int XDT>
+__global__ void __launch_bounds__(512)
+linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
+                            const uint16_t* __restrict__ v, void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype)
+{
+    staged_body<XDT, 1, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x);
+}
+
+template <int XDT>
+static int launch_staged_col(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                             int64_t d_out, int64_t d_in, int y_dtype, size_t lds, hipStream_t stream)
+{
+    auto kernel = linear_skinny_staged_kernel<XDT>;
+    static unsigned lds_opted_in = 0;                 // per template instance: one kernel
+    if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0) return -1;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(512), lds, stream, (const uint16_t*)X,
+                       (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 template <int XDT, int AXIS, int MT, int WAVES, int DEPTH, bool K128>
 static int launch_one(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
                       void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
@@ -496,7 +518,12 @@ static int launch_plain(const void* X, const void* W_b, const uint32_t* B_packed
 {
 #define PDELTA_GO(MT, DEPTH, K128) \
     return launch_one<XDT, AXIS, MT, 8, DEPTH, K128>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift)
-    if (AXIS == 0 && M <= 2 && d_in % 128 == 0) PDELTA_GO(1, 2, true);
+    if (AXIS == 0 && M <= 8 && d_in % 128 == 0) PDELTA_GO(1, 2, true);
+    if (AXIS == 0 && M <= 16 && d_in % 128 == 0) PDELTA_GO(1, 1, true);
+    if (AXIS == 1 && M <= 2 && d_in % 128 == 0) {
+        const size_t lds = staged_lds_bytes(8, 2, true, M, d_in);
+        if (lds != 0) return launch_staged_col<XDT>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, lds, stream);
+    }
     if (AXIS == 0 && M > 8 && M <= 16) PDELTA_GO(1, 1, false);
     if (M <= 16) PDELTA_GO(1, 2, false);
     if (M <= 32) PDELTA_GO(2, 2, false);

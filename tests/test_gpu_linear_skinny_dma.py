@@ -54,3 +54,18 @@ def test_infinities_stay_in_their_outputs(M, monkeypatch):
     finite = torch.ones((M, d_out), dtype=torch.bool, device=DEV)
     finite[:, -1], finite[-1, :], finite[:, 3] = False, False, False
     assert torch.equal(torch.isfinite(got[0]), finite) and torch.equal(torch.nan_to_num(got[0]), torch.nan_to_num(got[1]))
+
+
+# a few tokens on more than 4096 outputs, and row scales on rows of 8 KB, run the register kernels: the same sums
+@pytest.mark.parametrize("M,d_out,d_in", [(1, 4097, 128), (2, 4112, 1152), (3, 4097, 640), (4, 4100, 256), (5, 4100, 256), (2, 4097, 8064), (9, 8190, 4096), (16, 5121, 4096)])
+@pytest.mark.parametrize("axis", ["row", "col"])
+def test_routes_of_few_tokens(M, d_out, d_in, axis, monkeypatch):
+    g = torch.Generator(device=DEV).manual_seed(M + d_out + d_in)
+    X = torch.randn((M, d_in), device=DEV, generator=g).half()
+    W = torch.randn((d_out, d_in), device=DEV, generator=g).half()
+    B = torch.randint(-2**31, 2**31, (d_out, d_in // 32), device=DEV, generator=g, dtype=torch.int64).to(torch.int32)
+    v = torch.rand(d_out if axis == "row" else d_in, device=DEV, generator=g).half()
+    call = pd.pdelta_linear_row if axis == "row" else pd.pdelta_linear_col
+    here = call(X, W, B, v, out_dtype=torch.float32)
+    monkeypatch.setenv("PDELTA_TUNE", "skinny_dma=1")
+    assert torch.equal(here, call(X, W, B, v, out_dtype=torch.float32))
