@@ -563,6 +563,21 @@ size_t pdelta_pack_group_workspace_bytes(int64_t d_out, int64_t d_in, int64_t gr
     return pdelta::pack_group_workspace_bytes(d_out, d_in, group, shared_rows);
 }
 
+int pdelta_probe_decode_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int64_t group)
+{
+    using namespace pdelta;
+    const TuneScope tune_scope;
+    int v_stride, g_shift;
+    size_t v_bytes;
+    if (M < 1 || axis < 0 || axis > 2) return PDELTA_EINVAL;
+    if (const int rc = group_layout(d_out, d_in, axis == 2 ? group : d_in, 0, &v_stride, &g_shift, &v_bytes)) return rc;
+    if (M > kSkinnyMaxM) return PDELTA_ESHAPE;
+    if (!is_w_dtype(x_dtype)) return PDELTA_EDTYPE;
+    const DecodeRoute route = linear_skinny_route(x_dtype, axis, M, d_out, d_in, g_shift);
+    if (route.kernel == kDecodeDirect) return route.rows;
+    return route.kernel == kDecodeStaged ? 8 : 0;
+}
+
 int pdelta_pack_group(const void* W_f, const void* W_b, int64_t d_out, int64_t d_in, int w_dtype, int64_t group,
                       int shared_rows, uint32_t* B_packed, uint16_t* v, void* workspace, size_t workspace_bytes,
                       void* stream)

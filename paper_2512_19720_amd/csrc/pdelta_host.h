@@ -52,11 +52,15 @@ int launch_linear_skinny(int x_dtype, int y_dtype, int axis, const void* X, cons
 int launch_linear_skinny_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
                                const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                                int64_t d_out, int64_t d_in, int v_stride, int g_shift, hipStream_t stream);
-// The same for batches with direct loads into LDS (axis 2: blockwise scales).  Returns 1 when it does not apply or the
-// kernels above are the better ones, else 0 / -1.
+// Which kernel takes a decode call (axis 2: blockwise scales), and of the one with direct loads how many tiles of 16 output
+// rows a workgroup takes.
+enum DecodeKernel { kDecodeRegisters, kDecodeStaged, kDecodeDirect };
+struct DecodeRoute { DecodeKernel kernel; int rows; };
+DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift);
+// The kernel with direct loads into LDS: d_in a multiple of 128, rows of 1 to 3 tiles.
 int launch_linear_skinny_dma(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b, const uint32_t* B_packed,
                              const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in, int v_stride, int g_shift,
-                             hipStream_t stream);
+                             int rows, hipStream_t stream);
 // Prefill: may tiles be computed in parts of d_in, and the memory for their sums (linear_gemm_workspace_bytes).
 // Without the memory the same sums are formed by one workgroup per tile.
 struct PrefillSplit { bool allowed; void* workspace; };

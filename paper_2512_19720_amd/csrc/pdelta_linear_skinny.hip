@@ -20,6 +20,8 @@
 // j = 0..3, the 16 bytes W_b[row n][k0 + 32 j + 8 g .. +7]: this is exactly the B-operand
 // layout of the MFMA (no shuffles), and the four 32-bit sign words of that row and step are
 // one 16-byte load from which the lane keeps byte g of word j.
+#include <algorithm>
+
 #include "pdelta.h"
 #include "pdelta_device.h"
 #include "pdelta_host.h"
@@ -441,7 +443,7 @@ static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M,
     return bytes <= kStagedLdsLimit ? bytes : 0;
 }
 
-// One layer, column mode, X and fp16(X v) in LDS: for one or two tokens (see launch_plain).
+// One layer, column mode, X and fp16(X v) in LDS: for one or two tokens (see linear_skinny_route).
 template <int XDT>
 __global__ void __launch_bounds__(512)
 linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
@@ -452,9 +454,10 @@ linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __re
 
 template <int XDT>
 static int launch_staged_col(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int y_dtype, size_t lds, hipStream_t stream)
+                             int64_t d_out, int64_t d_in, int y_dtype, hipStream_t stream)
 {
     auto kernel = linear_skinny_staged_kernel<XDT>;
+    const size_t lds = staged_lds_bytes(8, 2, true, M, d_in);
     static unsigned lds_opted_in = 0;                 // per template instance: one kernel
     if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0) return -1;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(512), lds, stream, (const uint16_t*)X,
@@ -509,21 +512,69 @@ int launch_linear_skinny_batch(int x_dtype, int y_dtype, const pdelta_layer* lay
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// What linear_skinny_dma_kernel leaves: one or two tokens on many rows with row scales, and d_in that is
-// not a multiple of 128.  Two steps in flight per wave, except row mode above 8 tokens, where one is 3-4 % faster (the X
+// Which kernel takes a decode call.  d_in not a multiple of 128: the register kernel.  Else the kernel with direct loads,
+// except up to 16 tokens where one of the older kernels was measured faster (us, changing weights, 24 calls in a row):
+// they hide one workgroup's start behind another's end, and a CU holds several of them.  That counts for rows of a multiple
+// of 4 KB (d_in a multiple of 2048) above all; the line was found by measuring, not derived (such rows begin at the same
+// few memory channels).
+
+// Row scales, up to 16 tokens: is the register kernel the better one?  `rows`, `rounds`: what the other one would take.
+static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int64_t rounds)
+{
+    if (d_out <= 256 * 16) return false;              // one round (4096 x 4096, one token: 8.7 there, 8.2 here)
+    if (M <= 4) return true;                          // 8192 x 4096 14.1 and 15.3, 14336 x 2048 13.4 and 14.4, 11008 x 4096 18.9 and 19.5
+    const bool thin = rounds > 2 && rounds * rows * 4096 * 8 > d_out * 9;      // a ninth or more of the last round is empty
+    // some waves have no unit: 10240 x 512, 12 tokens 4.7 and 5.3, 18432 x 512 6.8 and 7.5; 14336 x 512 6.3 and 5.6
+    if (d_in < 1024 && (d_out <= 8192 || (M > 8 && (d_out <= 12288 || thin)))) return true;
+    // 12288 x 4096, eight tokens 21.0 and 23.1, 16384 x 2048 15.3 and 16.4, 32000 x 4096 50.7 and 56.4; six, 6144 x 4096 13.1 and
+    // 13.7, 10240 x 6144 29.8 and 31.6; 9216 x 4096 even, 10240 x 8192, eight, 40.2 and 38.3
+    if (M <= 8 && d_in % 2048 == 0 && (d_out > (d_in % 4096 == 0 ? 10240 : 9216) || (d_out > (d_in % 4096 == 0 ? 5120 : 7168) && d_out <= 8192)))
+        return true;
+    if (M <= 8 && rows == 3 && d_out > 11264 && d_in >= 6144) return true;     // 12288 x 11008, six 59.4 and 62.7
+    // 12288 x 4096, ten tokens 22.1 and 23.2, 32000 x 4096 52.5 and 55-57, 18432 x 6144 52.4 and 55.6; 11008 x 4096 21.6 and 21.1
+    if (M <= 12 && d_out > 11264 && (d_in % 4096 == 0 || (d_in % 2048 == 0 && thin))) return true;
+    return d_in % 4096 == 0 && rows == 1;             // 8192 x 4096, twelve 16.1 and 16.9, 28672 x 8192, sixteen 100 and 99.6-102
+}
+
+DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift)
+{
+    const int forced = tune_value("skinny_dma", -1);
+    if (d_in % 128 != 0 || forced == 0) return DecodeRoute{kDecodeRegisters, 1};
+    if (forced > 0) return DecodeRoute{kDecodeDirect, std::min(forced, 3)};
+    const int mt = (int)((M + 15) / 16);
+    // Row tiles per workgroup: the least rounds of 256 workgroups times what a round weighs, 8, 13, 20 for one token tile
+    // (4096 inputs, 16 tokens: 9.0, 12.2, 12.6 us in one round; 18432 x 1024: 13.9, 10.1, 11.0 in five, three, two) and
+    // 3 mt + k (4 + mt) for more, which only ranks them (64 tokens: 15, 19, 22 in one round).  Two tiles on more than 6144
+    // rows of a multiple of 8 KB are left out: 11008 x 4096 24.9 against 21.1-22, 8192 x 8192 36 against 31-33.
+    // bf16 with column scales converts X in every workgroup, so three tiles weigh 18 there where two are left out (20480 x
+    // 4096, six tokens: 37.5 with three, 40.5 with one).
+    const bool no_two = mt == 1 && d_out > 6144 && d_in % 4096 == 0;
+    const int third = mt == 1 && !(no_two && axis == 1 && x_dtype == kBF16) ? 2 : 0;
+    int rows = 1;
+    int64_t best = 0, rounds = 0;
+    for (int k = 1; k <= 3; ++k) {
+        if (k == 2 && no_two) continue;
+        const int64_t r = ((d_out + k * 16 - 1) / (k * 16) + 255) / 256, cost = r * (3 * mt + k * (4 + mt) + (k == 3 ? third : 0));
+        if (k == 1 || cost < best) { best = cost; rows = k; rounds = r; }
+    }
+    if (mt > 1) return DecodeRoute{kDecodeDirect, rows};
+    if (axis == 0) return registers_pay(M, d_out, d_in, rows, rounds) ? DecodeRoute{kDecodeRegisters, 1} : DecodeRoute{kDecodeDirect, rows};
+    // Column scales, one or two tokens: the staged kernel forms fp16(X v) once per workgroup.  8192 x 4096 14.3 and 16.3,
+    // 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0.
+    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return DecodeRoute{kDecodeStaged, 1};
+    return DecodeRoute{kDecodeDirect, rows};
+}
+
+// The register kernel.  Two steps in flight per wave, except row mode above 8 tokens, where one is 3-4 % faster (the X
 // loads double the bytes in flight per step), and above 32 tokens (registers).
 template <int XDT, int AXIS>
-static int launch_plain(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                        int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
+static int launch_registers(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                            int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
 #define PDELTA_GO(MT, DEPTH, K128) \
     return launch_one<XDT, AXIS, MT, 8, DEPTH, K128>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift)
     if (AXIS == 0 && M <= 8 && d_in % 128 == 0) PDELTA_GO(1, 2, true);
     if (AXIS == 0 && M <= 16 && d_in % 128 == 0) PDELTA_GO(1, 1, true);
-    if (AXIS == 1 && M <= 2 && d_in % 128 == 0) {
-        const size_t lds = staged_lds_bytes(8, 2, true, M, d_in);
-        if (lds != 0) return launch_staged_col<XDT>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, lds, stream);
-    }
     if (AXIS == 0 && M > 8 && M <= 16) PDELTA_GO(1, 1, false);
     if (M <= 16) PDELTA_GO(1, 2, false);
     if (M <= 32) PDELTA_GO(2, 2, false);
@@ -536,11 +587,15 @@ template <int XDT>
 static int launch_axis(int axis, const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                        int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
-    const int rc = launch_linear_skinny_dma(XDT, y_dtype, axis, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
-    if (rc != 1) return rc;
-    if (axis == 0) return launch_plain<XDT, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
-    if (axis == 1) return launch_plain<XDT, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
-    return launch_plain<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream);
+    const DecodeRoute route = linear_skinny_route(XDT, axis, M, d_out, d_in, g_shift);
+    if (route.kernel == kDecodeDirect)
+        return launch_linear_skinny_dma(XDT, y_dtype, axis, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, route.rows, stream);
+#define PDELTA_GO(AXIS) return launch_registers<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
+    if (route.kernel == kDecodeStaged) return launch_staged_col<XDT>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
+    if (axis == 0) PDELTA_GO(0);
+    if (axis == 1) PDELTA_GO(1);
+    PDELTA_GO(2);
+#undef PDELTA_GO
 }
 
 int launch_linear_skinny_group(int x_dtype, int y_dtype, const void* X, const void* W_b,

@@ -262,31 +262,9 @@ static int launch_dma(const void* X, const void* W_b, const uint32_t* B_packed, 
 
 template <int XDT, int AXIS>
 static int launch_dma_tokens(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
+                             int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, int nt, hipStream_t stream)
 {
-    // Row tiles per workgroup: 256 workgroups are a round, and a round takes about 3 MT + NT (4 + MT) (64 tokens, 4096
-    // inputs: 15, 19, 22 us in one round with 1, 2, 3 tiles; in three, two and one for 11008 outputs: 39, 38, 27).
     const int mt = (int)((M + 15) / 16);
-    int nt = tune_value("skinny_dma", -1);
-    // A few tokens and more than one round of 16-row workgroups: the register kernels, which hide one workgroup's start
-    // behind another's end, and in column mode form fp16(X v) once per workgroup.  Changing inputs, there and here: row,
-    // four tokens, 8192 x 4096 14.1 and 15.3 us, 14336 x 2048 13.4 and 14.4, 11008 x 4096 18.9 and 19.5 (twelve: 22.0 and 19.7);
-    // col, one token, 8192 x 4096 14.1 and 15.7, 14336 x 2048 13.8 and 14.4 (four: 18.9 and 16.0, 15.2 and 14.8).  In one round
-    // they are behind (row, one token, 4096 x 4096: 8.7 and 8.2; 4096 x 11008: 21.4 and 19.5).
-    if (nt < 0 && d_out > 256 * 16 && (AXIS == 0 ? M <= 4 : AXIS == 1 && M <= 2 && d_in < 8192)) return 1;
-    if (nt < 0) {
-        // Two tiles of rows of a multiple of 8 KB start every workgroup 256 KB from the next, at the same memory channels:
-        // 8192 x 4096, up to 16 tokens, takes 19-20 us with two, 15.3-17 with one or three (5120 x 4096, 160 workgroups: 12.9,
-        // 13.7, 13.5).  The register kernel's row mode is the best there (twelve tokens 15.7).
-        const bool camps = mt == 1 && d_in % 4096 == 0 && d_out > 160 * 32;
-        int64_t best = 0;
-        for (int k = 1; k <= 3; ++k) {
-            if (k == 2 && camps) continue;
-            const int64_t rounds = ((d_out + k * 16 - 1) / (k * 16) + 255) / 256, cost = rounds * (3 * mt + k * (4 + mt));
-            if (k == 1 || cost < best) { best = cost; nt = k; }
-        }
-        if (AXIS == 0 && camps && nt == 1) return 1;
-    }
 #define PDELTA_GO(MT, NT) \
     return launch_dma<XDT, AXIS, MT, NT>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
 #define PDELTA_ROWS(MT)           \
@@ -305,10 +283,9 @@ static int launch_dma_tokens(const void* X, const void* W_b, const uint32_t* B_p
 
 int launch_linear_skinny_dma(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b, const uint32_t* B_packed,
                              const uint16_t* v, void* Y, int64_t M, int64_t d_out, int64_t d_in, int v_stride, int g_shift,
-                             hipStream_t stream)
+                             int rows, hipStream_t stream)
 {
-    if (d_in % kDmaUnitK != 0 || M <= 0 || M > kSkinnyMaxM || tune_value("skinny_dma", -1) == 0) return 1;
-#define PDELTA_GO(XDT, AXIS) return launch_dma_tokens<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
+#define PDELTA_GO(XDT, AXIS) return launch_dma_tokens<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, rows, stream)
     if (x_dtype == kBF16) {
         if (axis == 0) PDELTA_GO(kBF16, 0);
         if (axis == 1) PDELTA_GO(kBF16, 1);
