@@ -230,7 +230,7 @@ template <int XDT, int AXIS, int WAVES, int DEPTH, bool STAGE_X>
 __device__ __forceinline__ void
 staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             const uint32_t* __restrict__ B_packed, const uint16_t* __restrict__ v,
-            void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int block)
+            void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype, int block, int v_stride = 0, int g_shift = 31)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // nibble -> four +-1.0 values (of the sign operand's dtype): two conflict-free 8-byte LDS
@@ -243,8 +243,10 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
     float* red = (float*)smem;                                        // [WAVES][4][64]
     uint32_t* s_sign = (uint32_t*)(smem + WAVES * 1024);              // [16][spr]
     uint16_t* s_x = (uint16_t*)(s_sign + 16 * spr);                   // [M][xpr]      (STAGE_X)
-    uint16_t* s_xv = s_x + (STAGE_X ? M * xpr : 0);                   // [M][xpr]      (STAGE_X: col)
-    constexpr bool XV = STAGE_X && AXIS == 1;
+    uint16_t* s_xv = s_x + (STAGE_X ? M * xpr : 0);                   // [M][xpr]      (STAGE_X: col, or blockwise with bf16 X)
+    constexpr bool XV = STAGE_X && (AXIS == 1 || (AXIS == 2 && XDT == kBF16));
+    uint16_t* s_v = s_xv + (XV ? M * xpr : 0);                        // [16][groups]  (blockwise)
+    const int n_groups = AXIS == 2 && g_shift < 31 ? K >> g_shift : 1;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -322,8 +324,14 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
                 *(uint4v*)(s_x + t * xpr + u * 8) = xv;
                 if constexpr (AXIS == 1)
                     *(uint4v*)(s_xv + t * xpr + u * 8) = scale_x<XDT>(xv, *(const uint4v*)(v + u * 8));
+                if constexpr (AXIS == 2 && XV) *(uint4v*)(s_xv + t * xpr + u * 8) = x_as_f16<XDT>(xv);
             }
         }
+        if constexpr (AXIS == 2)
+            for (int i = tid; i < 16 * n_groups; i += WAVES * 64) {
+                const int row = i / n_groups, c = i - row * n_groups;
+                s_v[i] = v[(int64_t)min(n0 + row, d_out - 1) * v_stride + c];
+            }
     }
     __syncthreads();
 
@@ -331,6 +339,7 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
     const uint32_t* my_sign = s_sign + n * spr;
     const uint16_t* my_x = s_x + tok * xpr + g * 8;
     const uint16_t* my_xv = s_xv + tok * xpr + g * 8;
+    const uint16_t* my_v = s_v + n * n_groups;
 
     auto compute = [&](const StagedStep<AXIS, STAGE_X>& r, int kb) {
         const uint4v sw = *(const uint4v*)(my_sign + (kb >> 5));
@@ -341,6 +350,7 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             if constexpr (STAGE_X) {
                 xa = *(const uint4v*)(my_x + kb + j * 32);
                 if constexpr (XV) xs = *(const uint4v*)(my_xv + kb + j * 32);
+                else if constexpr (AXIS == 2) xs = xa;
             } else {
                 xa = to_mfma_layout(r.x[j]);
                 if constexpr (AXIS == 1) xs = scale_x<XDT>(xa, r.vc[j]);
@@ -356,6 +366,7 @@ staged_body(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b,
             } else {
                 sg = expand_signs<(AXIS == 0 ? XDT : kF16)>(byte);
             }
+            if constexpr (AXIS == 2) sg = signs_times_scale(sg, my_v[(kb + j * 32) >> g_shift]);
             accb = mfma16<XDT>(xa, wj, accb);
             if constexpr (AXIS == 0) accs = mfma16<XDT>(xa, sg, accs);
             else accs = mfma16<kF16>(xs, sg, accs);
@@ -443,25 +454,35 @@ static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M,
     return bytes <= kStagedLdsLimit ? bytes : 0;
 }
 
-// One layer, column mode, X and fp16(X v) in LDS: for one or two tokens (see linear_skinny_route).
-template <int XDT>
+// One layer with column or blockwise scales, its few tokens and their fp16 forms in LDS: see linear_skinny_route.
+template <int XDT, int AXIS>
 __global__ void __launch_bounds__(512)
 linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
-                            const uint16_t* __restrict__ v, void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype)
+                            const uint16_t* __restrict__ v, void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype,
+                            int v_stride, int g_shift)
 {
-    staged_body<XDT, 1, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x);
+    staged_body<XDT, AXIS, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x, v_stride, g_shift);
 }
 
-template <int XDT>
-static int launch_staged_col(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
-                             int64_t d_out, int64_t d_in, int y_dtype, hipStream_t stream)
+// LDS bytes of a workgroup of that kernel, or 0 when it does not apply.
+static size_t staged_layer_bytes(int x_dtype, int axis, int64_t M, int64_t K, int g_shift)
 {
-    auto kernel = linear_skinny_staged_kernel<XDT>;
-    const size_t lds = staged_lds_bytes(8, 2, true, M, d_in);
+    if (axis == 0 || K % 128 != 0 || M > 16) return 0;
+    const size_t bytes = staged_lds_bytes(8, axis == 1 || x_dtype == kBF16 ? 2 : 1, true, M, K);
+    const size_t scales = axis == 2 ? (size_t)16 * (g_shift < 31 ? K >> g_shift : 1) * 2 : 0;
+    return bytes != 0 && bytes + scales <= kStagedLdsLimit ? bytes + scales : 0;
+}
+
+template <int XDT, int AXIS>
+static int launch_staged(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                         int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
+{
+    auto kernel = linear_skinny_staged_kernel<XDT, AXIS>;
+    const size_t lds = staged_layer_bytes(XDT, AXIS, M, d_in, g_shift);
     static unsigned lds_opted_in = 0;                 // per template instance: one kernel
     if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0) return -1;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(512), lds, stream, (const uint16_t*)X,
-                       (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype);
+                       (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype, v_stride, g_shift);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -536,10 +557,34 @@ static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int6
     return d_in % 4096 == 0 && rows == 1;             // 8192 x 4096, twelve 16.1 and 16.9, 28672 x 8192, sixteen 100 and 99.6-102
 }
 
+// Column and blockwise scales, up to 16 tokens: is the staged kernel the better one?  It forms
+// fp16(X v) and fp16(X) once per workgroup.
+static bool staged_pays(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift, int rows, int64_t rounds)
+{
+    auto fits = [&](size_t lds) {
+        const size_t need = staged_layer_bytes(x_dtype, axis, M, d_in, g_shift);
+        return need != 0 && need + 128 <= lds;        // (128: the table of signs)
+    };
+    constexpr size_t half = 80 * 1024;                // two workgroups a CU
+    // col, one and two tokens: 8192 x 4096 14.3 and 16.3, 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0
+    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return fits(kStagedLdsLimit);
+    if (axis == 1) return false;
+    // Rows of 8 or 12 KB: blockwise, one token, 8192 x 4096 15.6 and 16.5, 14336 x 4096 26.4 and 28.4, 32000 x 4096 51.3 and
+    // 55.7; 8192 x 6144 21.3 and 24.1.  Three tokens with bf16 blocks are
+    // even (29.0 and 28.7), and in a single round of 48-row workgroups the other one is ahead earlier (10240 x 4096, one
+    // token 21.0 and 19.7; two, 12288 x 4096 23.6 and 23.3).  One token on rows of 16 KB: 6144 x 8192 24.8 and 26.3.
+    if (d_in == 8192) return M == 1 && d_out > 5120 && d_out <= 7168 && fits(half);
+    if (d_in % 2048 != 0 || d_in < 4096 || d_in > 8192 || d_out <= 6144) return false;
+    int64_t most = g_shift < 31 && x_dtype == kBF16 ? 2 : 3;
+    if (rows == 3 && rounds == 1) most = d_in != 4096 ? 2 : (d_out > 10240 ? 1 : 0);
+    return M <= most && fits(half);
+}
+
 DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift)
 {
-    const int forced = tune_value("skinny_dma", -1);
+    const int forced = tune_value("skinny_dma", -1), staged = tune_value("skinny_staged", -1);
     if (d_in % 128 != 0 || forced == 0) return DecodeRoute{kDecodeRegisters, 1};
+    if (staged > 0 && staged_layer_bytes(x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
     if (forced > 0) return DecodeRoute{kDecodeDirect, std::min(forced, 3)};
     const int mt = (int)((M + 15) / 16);
     // Row tiles per workgroup: the least rounds of 256 workgroups times what a round weighs, 8, 13, 20 for one token tile
@@ -559,9 +604,9 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
     }
     if (mt > 1) return DecodeRoute{kDecodeDirect, rows};
     if (axis == 0) return registers_pay(M, d_out, d_in, rows, rounds) ? DecodeRoute{kDecodeRegisters, 1} : DecodeRoute{kDecodeDirect, rows};
-    // Column scales, one or two tokens: the staged kernel forms fp16(X v) once per workgroup.  8192 x 4096 14.3 and 16.3,
-    // 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0.
-    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return DecodeRoute{kDecodeStaged, 1};
+    if (staged != 0 && staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds)) return DecodeRoute{kDecodeStaged, 1};
+    // Few tokens on long rows that fill their rounds: 12288 x 11008 blockwise, one token 59.0 with one tile, 64.0 with three
+    if (axis == 2 && M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288))) rows = 1;
     return DecodeRoute{kDecodeDirect, rows};
 }
 
@@ -590,11 +635,14 @@ static int launch_axis(int axis, const void* X, const void* W_b, const uint32_t*
     const DecodeRoute route = linear_skinny_route(XDT, axis, M, d_out, d_in, g_shift);
     if (route.kernel == kDecodeDirect)
         return launch_linear_skinny_dma(XDT, y_dtype, axis, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, route.rows, stream);
-#define PDELTA_GO(AXIS) return launch_registers<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
-    if (route.kernel == kDecodeStaged) return launch_staged_col<XDT>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-    if (axis == 0) PDELTA_GO(0);
-    if (axis == 1) PDELTA_GO(1);
-    PDELTA_GO(2);
+#define PDELTA_GO(LAUNCH) return LAUNCH(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
+    if (axis == 0) PDELTA_GO((launch_registers<XDT, 0>));
+    if (axis == 1) {
+        if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 1>));
+        PDELTA_GO((launch_registers<XDT, 1>));
+    }
+    if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 2>));
+    PDELTA_GO((launch_registers<XDT, 2>));
 #undef PDELTA_GO
 }
 

@@ -30,7 +30,18 @@ def test_column_scales(M, d_out, d_in, dtype, kernel):
     assert route(M, d_out, d_in, COL, dtype) == kernel
 
 
-def test_routes_that_do_not_fit_are_not_taken():
+# blockwise scales (0: one scale per row)
+@pytest.mark.parametrize("M,d_out,d_in,dtype,group,kernel", [
+    (1, 8192, 4096, pd.BF16, 128, 8), (1, 14336, 4096, pd.BF16, 128, 8), (2, 32000, 4096, pd.BF16, 128, 8), (3, 32000, 4096, pd.BF16, 0, 8),
+    (3, 14336, 4096, pd.F16, 128, 8), (2, 8192, 6144, pd.BF16, 128, 8), (1, 12288, 6144, pd.BF16, 0, 8), (1, 12288, 4096, pd.BF16, 128, 8),
+    (1, 6144, 8192, pd.BF16, 128, 8), (1, 12288, 11008, pd.BF16, 128, 1),
+    (3, 14336, 4096, pd.BF16, 128, 1), (1, 10240, 4096, pd.BF16, 128, 3), (2, 12288, 4096, pd.BF16, 128, 3), (1, 5120, 4096, pd.BF16, 128, 2),
+    (1, 8192, 8192, pd.BF16, 128, 1), (1, 14336, 2048, pd.BF16, 128, 2), (1, 4096, 4096, pd.F16, 128, 1), (1, 8192, 4096 + 32, pd.F16, 32, 0)])
+def test_blockwise_scales(M, d_out, d_in, dtype, group, kernel):
+    assert route(M, d_out, d_in, GROUP, dtype, group or d_in) == kernel
+
+
+def test_routes_that_do_not_fit_are_not_taken(monkeypatch):
     """A workgroup's LDS: a few long rows are never staged, and every route is one of the kernels."""
     for axis in (ROW, COL, GROUP):
         for dtype in (pd.F16, pd.BF16):
@@ -40,6 +51,8 @@ def test_routes_that_do_not_fit_are_not_taken():
                         assert route(M, d_out, d_in, axis, dtype, 32) in (0, 1, 2, 3, 8)
                         if d_in > 28672:
                             assert route(M, d_out, d_in, axis, dtype, 32) < 8
+    monkeypatch.setenv("PDELTA_TUNE", "skinny_staged=1")
+    assert route(16, 64, 28672, COL) in (1, 2, 3) and route(1, 64, 4096, COL) == 8
 
 
 def test_argument_errors():

@@ -69,3 +69,29 @@ def test_routes_of_few_tokens(M, d_out, d_in, axis, monkeypatch):
     here = call(X, W, B, v, out_dtype=torch.float32)
     monkeypatch.setenv("PDELTA_TUNE", "skinny_dma=1")
     assert torch.equal(here, call(X, W, B, v, out_dtype=torch.float32))
+
+
+# the staged kernel (column and blockwise scales): one unit, seven waves without work; rows past the end; the same sums in
+# the same order as the kernel with direct loads
+@pytest.mark.parametrize("M,d_out,d_in", [(1, 17, 128), (2, 49, 1152), (3, 33, 4096), (4, 16, 640), (1, 15, 8192)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_staged_kernel(M, d_out, d_in, dtype, monkeypatch):
+    L = make_case(d_out, d_in, M, dtype, "row", 5 * M + d_out + d_in)
+    d = L["d"]
+    calls = [("col", lambda y: pd.pdelta_linear_col(d["X"], d["W_b"], d["B"], d["v_col"], out=y),
+              lambda: orc.linear(L["X"], L["W_b"], L["B"], L["v_col"], orc.COL, L["dtype"]))]
+    for group, shared in ((32, False), (128, True), (d_in, False)):
+        v_bits = orc.pack_group(L["dW"], L["dW"] * 0, group, shared, dtype)[1]
+        v = f16_dev(v_bits)
+        calls.append((f"group {group}", lambda y, v=v, group=group: pd.pdelta_linear_group(d["X"], d["W_b"], d["B"], v, group, out=y),
+                      lambda v_bits=v_bits, group=group: orc.linear_group(L["X"], L["W_b"], L["B"], v_bits, group, dtype)))
+    for name, call, oracle in calls:
+        ref = oracle()
+        for y_dtype in (torch.float32, d["X"].dtype):
+            got = []
+            for tune in ("skinny_staged=1", "skinny_dma=1"):
+                monkeypatch.setenv("PDELTA_TUNE", tune)
+                got.append(torch.full((M, d_out), float("nan"), dtype=y_dtype, device=DEV))
+                call(got[-1])
+            check_y(got[0], ref, f"staged {name} M={M} {d_out}x{d_in} dt={dtype}")
+            assert torch.equal(got[0].view(torch.uint8), got[1].view(torch.uint8)), f"staged {name} M={M} {d_out}x{d_in} dt={dtype}"
