@@ -455,33 +455,33 @@ static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M,
 }
 
 // One layer with column or blockwise scales, its few tokens and their fp16 forms in LDS: see linear_skinny_route.
-template <int XDT, int AXIS>
-__global__ void __launch_bounds__(512)
+template <int XDT, int AXIS, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64)
 linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
                             const uint16_t* __restrict__ v, void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype,
                             int v_stride, int g_shift)
 {
-    staged_body<XDT, AXIS, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x, v_stride, g_shift);
+    staged_body<XDT, AXIS, WAVES, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x, v_stride, g_shift);
 }
 
 // LDS bytes of a workgroup of that kernel, or 0 when it does not apply.
-static size_t staged_layer_bytes(int x_dtype, int axis, int64_t M, int64_t K, int g_shift)
+static size_t staged_layer_bytes(int waves, int x_dtype, int axis, int64_t M, int64_t K, int g_shift)
 {
     if (axis == 0 || K % 128 != 0 || M > 16) return 0;
-    const size_t bytes = staged_lds_bytes(8, axis == 1 || x_dtype == kBF16 ? 2 : 1, true, M, K);
+    const size_t bytes = staged_lds_bytes(waves, axis == 1 || x_dtype == kBF16 ? 2 : 1, true, M, K);
     const size_t scales = axis == 2 ? (size_t)16 * (g_shift < 31 ? K >> g_shift : 1) * 2 : 0;
     return bytes != 0 && bytes + scales <= kStagedLdsLimit ? bytes + scales : 0;
 }
 
-template <int XDT, int AXIS>
+template <int XDT, int AXIS, int WAVES>
 static int launch_staged(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                          int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
-    auto kernel = linear_skinny_staged_kernel<XDT, AXIS>;
-    const size_t lds = staged_layer_bytes(XDT, AXIS, M, d_in, g_shift);
+    auto kernel = linear_skinny_staged_kernel<XDT, AXIS, WAVES>;
+    const size_t lds = staged_layer_bytes(WAVES, XDT, AXIS, M, d_in, g_shift);
     static unsigned lds_opted_in = 0;                 // per template instance: one kernel
     if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(512), lds, stream, (const uint16_t*)X,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(WAVES * 64), lds, stream, (const uint16_t*)X,
                        (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype, v_stride, g_shift);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -557,34 +557,39 @@ static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int6
     return d_in % 4096 == 0 && rows == 1;             // 8192 x 4096, twelve 16.1 and 16.9, 28672 x 8192, sixteen 100 and 99.6-102
 }
 
-// Column and blockwise scales, up to 16 tokens: is the staged kernel the better one?  It forms
+// Column and blockwise scales, up to 16 tokens: waves of the staged kernel where it is the better one, else 0.  It forms
 // fp16(X v) and fp16(X) once per workgroup.
-static bool staged_pays(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift, int rows, int64_t rounds)
+static int staged_pays(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift, int rows, int64_t rounds)
 {
-    auto fits = [&](size_t lds) {
-        const size_t need = staged_layer_bytes(x_dtype, axis, M, d_in, g_shift);
+    auto fits = [&](int waves, size_t lds) {
+        const size_t need = staged_layer_bytes(waves, x_dtype, axis, M, d_in, g_shift);
         return need != 0 && need + 128 <= lds;        // (128: the table of signs)
     };
     constexpr size_t half = 80 * 1024;                // two workgroups a CU
     // col, one and two tokens: 8192 x 4096 14.3 and 16.3, 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0
-    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return fits(kStagedLdsLimit);
-    if (axis == 1) return false;
+    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return fits(8, kStagedLdsLimit) ? 8 : 0;
+    // one bf16 token with column scales in one round, 2048 x 4096 7.9 and 8.3, 4096 x 6144 12.6 and 13.4; sixteen waves for
+    // long rows, 2048 x 8192 11.7 and 12.5, 4096 x 11008 21.9 and 22.7 (4096 x 8192 even)
+    if (axis == 1 && x_dtype == kBF16 && M == 1 && d_out <= 256 * 16) {
+        if (d_in >= 8192 && d_in < 14336 && d_out <= (d_in % 4096 == 0 ? 2048 : 4096)) return fits(16, kStagedLdsLimit) ? 16 : 0;
+        return d_in < 8192 && d_in % 2048 == 0 && d_out >= 2048 && fits(8, half) ? 8 : 0;
+    }
     // Rows of 8 or 12 KB: blockwise, one token, 8192 x 4096 15.6 and 16.5, 14336 x 4096 26.4 and 28.4, 32000 x 4096 51.3 and
-    // 55.7; 8192 x 6144 21.3 and 24.1.  Three tokens with bf16 blocks are
+    // 55.7; 8192 x 6144 21.3 and 24.1; col, three tokens, 8192 x 4096 15.8 and 17.7.  Three tokens with bf16 blocks are
     // even (29.0 and 28.7), and in a single round of 48-row workgroups the other one is ahead earlier (10240 x 4096, one
     // token 21.0 and 19.7; two, 12288 x 4096 23.6 and 23.3).  One token on rows of 16 KB: 6144 x 8192 24.8 and 26.3.
-    if (d_in == 8192) return M == 1 && d_out > 5120 && d_out <= 7168 && fits(half);
-    if (d_in % 2048 != 0 || d_in < 4096 || d_in > 8192 || d_out <= 6144) return false;
-    int64_t most = g_shift < 31 && x_dtype == kBF16 ? 2 : 3;
-    if (rows == 3 && rounds == 1) most = d_in != 4096 ? 2 : (d_out > 10240 ? 1 : 0);
-    return M <= most && fits(half);
+    if (d_in == 8192) return axis == 2 && M == 1 && d_out > 5120 && d_out <= 7168 && fits(8, half) ? 8 : 0;
+    if (d_in % 2048 != 0 || d_in < 4096 || d_in > 8192 || d_out <= 6144) return 0;
+    int64_t most = axis == 2 && g_shift < 31 && x_dtype == kBF16 ? 2 : 3;
+    if (rows == 3 && rounds == 1) most = axis == 1 || d_in != 4096 ? 2 : (d_out > 10240 ? 1 : 0);
+    return M <= most && fits(8, half) ? 8 : 0;
 }
 
 DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift)
 {
     const int forced = tune_value("skinny_dma", -1), staged = tune_value("skinny_staged", -1);
     if (d_in % 128 != 0 || forced == 0) return DecodeRoute{kDecodeRegisters, 1};
-    if (staged > 0 && staged_layer_bytes(x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
+    if (staged > 0 && staged_layer_bytes(8, x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
     if (forced > 0) return DecodeRoute{kDecodeDirect, std::min(forced, 3)};
     const int mt = (int)((M + 15) / 16);
     // Row tiles per workgroup: the least rounds of 256 workgroups times what a round weighs, 8, 13, 20 for one token tile
@@ -604,9 +609,10 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
     }
     if (mt > 1) return DecodeRoute{kDecodeDirect, rows};
     if (axis == 0) return registers_pay(M, d_out, d_in, rows, rounds) ? DecodeRoute{kDecodeRegisters, 1} : DecodeRoute{kDecodeDirect, rows};
-    if (staged != 0 && staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds)) return DecodeRoute{kDecodeStaged, 1};
+    const int waves = staged == 0 ? 0 : staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds);
+    if (waves != 0) return DecodeRoute{waves == 16 ? kDecodeStaged16 : kDecodeStaged, 1};
     // Few tokens on long rows that fill their rounds: 12288 x 11008 blockwise, one token 59.0 with one tile, 64.0 with three
-    if (axis == 2 && M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288))) rows = 1;
+    if (M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288))) rows = 1;
     return DecodeRoute{kDecodeDirect, rows};
 }
 
@@ -638,10 +644,12 @@ static int launch_axis(int axis, const void* X, const void* W_b, const uint32_t*
 #define PDELTA_GO(LAUNCH) return LAUNCH(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
     if (axis == 0) PDELTA_GO((launch_registers<XDT, 0>));
     if (axis == 1) {
-        if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 1>));
+        if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 1, 8>));
+        if constexpr (XDT == kBF16)
+            if (route.kernel == kDecodeStaged16) PDELTA_GO((launch_staged<XDT, 1, 16>));
         PDELTA_GO((launch_registers<XDT, 1>));
     }
-    if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 2>));
+    if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 2, 8>));
     PDELTA_GO((launch_registers<XDT, 2>));
 #undef PDELTA_GO
 }
