@@ -569,10 +569,12 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
         partial[(int64_t)(part * m_tiles + tile_m) * Nc + n0 + tid] = red[tid] + red[kGbTile + tid];
 }
 
-// Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel, which is only taken where the
-// contraction is not a multiple of 128 or the caller's workspace has no room for the parts.  A round of up to 256
+// Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel, which is taken where the
+// contraction is not a multiple of 128, the caller's workspace has no room for the parts, or a few tokens meet one or two
+// units (one token, 512 x 256 row 9.5 us and 10.9 here; 64: 13.8 and 10.9).  A round of up to 256
 // workgroups takes 4 us and 1.12 us per step of 64 inputs (1.44 when all CUs multiply and the clock falls); a part more
-// is one more row of partial sums for the second launch, and 16 parts would double the workspace for 3 us.  Changing
+// is one more row of partial sums for the second launch.  Up to 16 parts for at most 128 workgroups (one token, 8192 x 1024
+// col 24.9 us, 33.5 with eight; 2048 x 8192 row 20.8 and 29.4), else up to eight.  Changing
 // inputs, bf16 row, the 256 x 128 kernel or the earlier epilogue, then now: 64 tokens, 11008 x 4096 65 -> 26 us; 256 tokens, 4096 x 4096 41 ->
 // 19; 1024 65 -> 33; 2048 80 -> 58 (col 88 -> 65); 2048 tokens, 11008 x 4096 221 -> 157; 4000 tokens, 2048 x 2048 53 -> 34.
 static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
@@ -582,9 +584,11 @@ static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
     const int64_t m_tiles = (M + kGbTile - 1) / kGbTile, tiles = m_tiles * ((Nc + kGbTile - 1) / kGbTile), units = Kc / kGbUnitK;
     if (tiles > (1 << 24)) return 0;
     if (forced > 0) return (int)std::min<int64_t>(forced, units);
+    if (units <= 2 && M <= 16) return 0;
+    const int64_t most = std::max<int64_t>(8, std::min<int64_t>(16, 128 / tiles));
     double best = 0;
     int parts = 0;
-    for (int64_t p = 1; p <= std::min<int64_t>(8, units); ++p) {
+    for (int64_t p = 1; p <= std::min(most, units); ++p) {
         const double t = (double)((tiles * p + 255) / 256) * (4 + 1.12 * 2 * (double)((units + p - 1) / p));
         if (parts == 0 || t < best) { best = t; parts = (int)p; }
     }
@@ -604,7 +608,7 @@ static int launch_grad_big(const uint16_t* A, const uint16_t* G, const uint32_t*
     return 0;
 }
 
-// Sums of the partial rows (up to 8 parts times the token tiles) in fp64: a block takes 64 outputs, its wave w the
+// Sums of the partial rows (up to 16 parts times the token tiles) in fp64: a block takes 64 outputs, its wave w the
 // rows w, w + 4, ..., so that every load of a thread is in flight at once and 4096 outputs spread over 64 CUs.
 __global__ void __launch_bounds__(256)
 grad_reduce_kernel(const float* __restrict__ partial, float* __restrict__ grad, int n, int rows)
