@@ -490,8 +490,12 @@ def pdelta_grad_v(X, dY, B_packed, axis: int, out=None, workspace: torch.Tensor 
     if out is None:
         out = torch.empty(d_out if axis == ROW else d_in, dtype=torch.float32, device=X.device)
     if workspace is None:
-        workspace = torch.empty(max(pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis), 16),
-                                dtype=torch.uint8, device=X.device)
+        try:
+            workspace = torch.empty(max(pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis), 16),
+                                    dtype=torch.uint8, device=X.device)
+        except torch.cuda.OutOfMemoryError:                 # the least it works with: the sums are cut elsewhere, and slower
+            workspace = torch.empty(max(pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis), 16),
+                                    dtype=torch.uint8, device=X.device)
     rc = lib().pdelta_grad_v(_dev(X, "X") or None, _dev(dY, "dY") or None, _dev(B_packed, "B_packed"), axis,
                              _dev(out, "grad_v"), M, d_out, d_in, dtype_code(X.dtype), _dev(workspace, "workspace"),
                              workspace.numel(), _stream())

@@ -104,3 +104,32 @@ def test_group_workspace_rules():
     assert call(ws=A + 3 * GB + d_out * (d_in // 128) * 2 - 16) == pd.EINVAL
     assert call(group=100) != pd.OK and call(group=3) != pd.OK           # refused with a workspace as without
     assert call(M=0) == pd.OK
+
+
+def test_gradient_without_memory_for_the_parts(monkeypatch):
+    """A call whose parts' sums cannot be allocated runs with the least workspace, as it did before parts were used."""
+    M, d_out, d_in = 2048, 4096, 4096
+    least, parts = (f(M, d_out, d_in, pd.ROW) for f in (pd.pdelta_grad_v_workspace_bytes, pd.pdelta_grad_v_split_workspace_bytes))
+    assert parts > least
+    X, dY, B = torch.zeros((M, d_in), dtype=torch.bfloat16), torch.zeros((M, d_out), dtype=torch.bfloat16), torch.zeros((d_out, d_in // 32), dtype=torch.int32)
+    real, calls = torch.empty, []
+
+    def empty(n, *args, **kw):
+        if n == parts:
+            raise torch.cuda.OutOfMemoryError("no memory for the parts")
+        return real(n, *args, **kw)
+
+    class Lib:
+        def pdelta_grad_v_workspace_bytes(self, *args): return least
+        def pdelta_grad_v_split_workspace_bytes(self, *args): return parts
+
+        def pdelta_grad_v(self, *args):
+            calls.append(args[-2])
+            return pd.OK
+
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(pd, "lib", lambda: Lib())
+    monkeypatch.setattr(pd, "_dev", lambda t, name: t.data_ptr())
+    monkeypatch.setattr(pd, "_stream", lambda: None)
+    assert pd.pdelta_grad_v(X, dY, B, pd.ROW).shape == (d_out,)
+    assert calls == [least]
