@@ -165,7 +165,7 @@ int pdelta_linear_col(const void* X, const void* W_b, const uint32_t* B_packed,
  * leave part of the chip without a tile; here those tiles are computed in several parts of d_in whose
  * fp32 sums are added in the order of d_in (reproducible; the sums of one output differ from those of
  * pdelta_linear_row / _col only in where they are cut).  pdelta_linear_workspace_bytes: the bytes such a
- * call uses, at most 64 MiB, 0 when none is used (always for M <= 64).  workspace may be NULL with
+ * call may use with any kind of scales, at most 64 MiB, 0 when none is used (always for M <= 64).  workspace may be NULL with
  * workspace_bytes = 0: the same result, bit for bit, with the parts of a tile one after another, which
  * takes longer.  Otherwise PDELTA_EWORKSPACE if it is smaller than that, PDELTA_EALIGN unless 16-byte
  * aligned, PDELTA_EINVAL if it overlaps a tensor of the call.  Its contents on entry are ignored; it

@@ -68,6 +68,14 @@ int pdelta_probe_prefill_parts(int parts, const void* X, const void* W_b, const 
  */
 int pdelta_probe_decode_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int64_t group);
 
+/*
+ * The same for a prefill call (M > 64); may_split: 1 for the entry points that take a workspace (given or not), 0 for the
+ * others.  Returns 64 for the kernel of 64 x 64 tiles with a ring of steps in flight, 65 for the one with roles, 128 for
+ * 128 x 128 tiles, 256 and 257 for 256 x 128 tiles (pipelined, two workgroups per CU), and 1000 + parts for 256 x 256 tiles
+ * (1: none of them split).  PDELTA_ESHAPE up to 64 tokens.
+ */
+int pdelta_probe_prefill_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int may_split);
+
 #ifdef __cplusplus
 }
 #endif

@@ -117,6 +117,8 @@ def lib() -> ctypes.CDLL:
         L.pdelta_probe_prefill_parts.argtypes = [i32, vp, vp, vp, vp, vp, i64, i64, i64, i32, vp]
         L.pdelta_probe_decode_kernel.restype = i32
         L.pdelta_probe_decode_kernel.argtypes = [i64, i64, i64, i32, i32, i64]
+        L.pdelta_probe_prefill_kernel.restype = i32
+        L.pdelta_probe_prefill_kernel.argtypes = [i64, i64, i64, i32, i32, i32]
         L.pdelta_status_string.restype = ctypes.c_char_p
         L.pdelta_status_string.argtypes = [i32]
         _lib = L

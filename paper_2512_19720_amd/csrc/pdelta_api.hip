@@ -578,6 +578,19 @@ int pdelta_probe_decode_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     return route.kernel == kDecodeStaged ? 8 : route.kernel == kDecodeStaged16 ? 16 : 0;
 }
 
+int pdelta_probe_prefill_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int may_split)
+{
+    using namespace pdelta;
+    const TuneScope tune_scope;
+    if (M < 1 || axis < 0 || axis > 2 || may_split < 0 || may_split > 1) return PDELTA_EINVAL;
+    if (const int rc = check_dims(d_out, d_in)) return rc;
+    if (M <= kSkinnyMaxM || M > kMaxTokens) return PDELTA_ESHAPE;
+    if (!is_w_dtype(x_dtype)) return PDELTA_EDTYPE;
+    const PrefillRoute route = linear_gemm_route(x_dtype, axis, M, d_out, d_in, may_split != 0);
+    constexpr int number[] = {1000, 65, 64, 128, 256, 257};
+    return number[route.kernel] + (route.kernel == kPrefillTiles256 ? route.split.parts : 0);
+}
+
 int pdelta_pack_group(const void* W_f, const void* W_b, int64_t d_out, int64_t d_in, int w_dtype, int64_t group,
                       int shared_rows, uint32_t* B_packed, uint16_t* v, void* workspace, size_t workspace_bytes,
                       void* stream)

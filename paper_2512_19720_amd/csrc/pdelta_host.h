@@ -114,7 +114,12 @@ int launch_linear_gemm_roles(int x_dtype, int y_dtype, int axis, const void* X, 
 // tiles are computed in one go, the other `split` ones in `parts` pieces of d_in each, whose fp32
 // sums go through the workspace.  parts = 0: another kernel is the better one, or the only one.
 struct BigSplit { int whole, split, parts; };
-BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed);
+BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, bool split_allowed);
+// Which kernel takes a prefill call (axis 2: blockwise scales): 256 x 256 tiles as `split` says, 64 x 64 tiles with roles
+// or a ring of steps in flight, 128 x 128, or 256 x 128 pipelined or with two workgroups per CU.
+enum PrefillKernel { kPrefillTiles256, kPrefillRoles, kPrefillSmall, kPrefillShort, kPrefillPipelined, kPrefillTwoPerCu };
+struct PrefillRoute { PrefillKernel kernel; BigSplit split; };
+PrefillRoute linear_gemm_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, bool may_split);
 int launch_linear_gemm_big(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
                            const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M, int64_t d_out,
                            int64_t d_in, int v_stride, int g_shift, void* workspace, BigSplit sp, hipStream_t stream);

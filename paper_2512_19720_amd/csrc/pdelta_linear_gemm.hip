@@ -704,11 +704,6 @@ static int launch_gemm_small(const void* X, const void* W_b, const uint32_t* B_p
                              hipStream_t stream, int v_stride = 0, int g_shift = 31)
 {
     const int m_tiles = (int)((M + 63) / 64), n_tiles = (int)((d_out + 63) / 64);
-    // At most one tile per CU: the kernel with roles, of which a CU holds one workgroup (251 x 4096 x 4096 bf16 32.5 -> 25.2
-    // us); more tiles: several workgroups per CU overlap better (70 x 11008 x 4096, 344 tiles: 47 us here, 51 there).
-    const int roles = tune_value("gemm_roles", -1);
-    if (d_in % 128 == 0 && roles != 0 && (roles == 1 || (int64_t)m_tiles * n_tiles <= 256))
-        return launch_linear_gemm_roles(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
     const int n_groups = (n_tiles + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)((int64_t)n_groups * kXcds * m_tiles));
     // four steps in flight (eight were measured too: 3-10 % slower, they halve the occupancy)
@@ -750,54 +745,48 @@ static int launch_gemm(const void* X, const void* W_b, const uint32_t* B_packed,
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int XDT, int AXIS>
-static int launch_gemm_bm(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v,
-                          void* Y, int64_t M, int64_t d_out, int64_t d_in, int y_dtype,
-                          PrefillSplit ps, hipStream_t stream)
+PrefillRoute linear_gemm_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, bool may_split)
 {
     // 256 x 256 tiles with direct loads (and split tiles where the call may split) when they are
     // expected to be faster; see linear_gemm_big_split.
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, ps.allowed);
-    if (sp.parts > 0)
-        return launch_gemm_tiles256<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps.workspace, sp, stream);
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, x_dtype, axis, may_split);
+    if (sp.parts > 0) return PrefillRoute{kPrefillTiles256, sp};
     // Under-filled grids (at most 128 tiles of 256 x 128, i.e. a few hundred tokens): the
-    // small-tile kernel is 2-3x faster there; from about 1000 tokens on the big tiles win.
+    // small-tile kernels are 2-3x faster there; from about 1000 tokens on the big tiles win.
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
-    const int small = tune_value("gemm_small", -1);
-    if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128)))
-        return launch_gemm_small<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-    if (M <= 128 || tune_value("gemm_bm", 256) == 128)
-        return launch_gemm<XDT, AXIS, 128, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
+    const int small = tune_value("gemm_small", -1), roles = tune_value("gemm_roles", -1);
+    if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128))) {
+        // At most one tile per CU: the kernel with roles, of which a CU holds one workgroup (251 x 4096 x 4096 bf16 32.5 -> 25.2
+        // us); more tiles: several workgroups per CU overlap better (70 x 11008 x 4096, 344 tiles: 47 us there, 51 with roles).
+        const int64_t tiles = ((M + 63) / 64) * ((d_out + 63) / 64);
+        const bool one_each = d_in % 128 == 0 && roles != 0 && (roles == 1 || tiles <= 256);
+        return PrefillRoute{one_each ? kPrefillRoles : kPrefillSmall, sp};
+    }
+    if (M <= 128 || (axis != 2 && tune_value("gemm_bm", 256) == 128)) return PrefillRoute{kPrefillShort, sp};
     // Of the 256 x 128 kernels the pipelined one (one workgroup per CU) is taken: measured 6 % faster on
     // 11008 x 4096, 2 % on 14336 x 4096 and 27 % on 4096 x 11008 (M = 2048) than the two-per-CU
     // kernel, whose finer granularity does not make up for its second barrier per step, and it
     // writes exactly Y (no register spills).  gemm_pipe=0 selects the two-per-CU kernel.
-    if (tune_value("gemm_pipe", 1) != 0)
-        return launch_gemm_pipe<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
-    return launch_gemm<XDT, AXIS, 256, 4>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream);
+    return PrefillRoute{tune_value("gemm_pipe", 1) != 0 ? kPrefillPipelined : kPrefillTwoPerCu, sp};
 }
 
-// Blockwise scales: the small-tile kernel for under-filled grids, the 128 x 128 tile kernel for
-// short batches, else the pipelined 256 x 128 kernel (gemm_pipe=0: two workgroups per compute unit).
-template <int XDT>
-static int launch_gemm_group(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y,
-                             int64_t M, int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift,
-                             PrefillSplit ps, hipStream_t stream)
+template <int XDT, int AXIS>
+static int launch_prefill(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
+                          int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, PrefillSplit ps, hipStream_t stream)
 {
-    // 256 x 256 tiles with direct loads (and split tiles where the call may split) when they are
-    // expected to be faster; see linear_gemm_big_split.
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, XDT, ps.allowed);
-    if (sp.parts > 0)
-        return launch_gemm_tiles256<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps.workspace, sp, stream);
-    const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
-    const int small = tune_value("gemm_small", -1);
-    if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128)))
-        return launch_gemm_small<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift);
-    if (M <= 128)
-        return launch_gemm<XDT, 2, 128, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift);
-    if (tune_value("gemm_pipe", 1) != 0)
-        return launch_gemm_pipe<XDT, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift);
-    return launch_gemm<XDT, 2, 256, 4>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift);
+    const PrefillRoute route = linear_gemm_route(XDT, AXIS, M, d_out, d_in, ps.allowed);
+    switch (route.kernel) {
+        case kPrefillTiles256:
+            return launch_gemm_tiles256<XDT, AXIS>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps.workspace, route.split, stream);
+        case kPrefillRoles:
+            return launch_linear_gemm_roles(XDT, y_dtype, AXIS, X, W_b, B_packed, v, Y, M, d_out, d_in, v_stride, g_shift, stream);
+#define PDELTA_GO(LAUNCH) return LAUNCH(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift)
+        case kPrefillSmall: PDELTA_GO((launch_gemm_small<XDT, AXIS>));
+        case kPrefillShort: PDELTA_GO((launch_gemm<XDT, AXIS, 128, 2>));
+        case kPrefillPipelined: PDELTA_GO((launch_gemm_pipe<XDT, AXIS>));
+        default: PDELTA_GO((launch_gemm<XDT, AXIS, 256, 4>));
+#undef PDELTA_GO
+    }
 }
 
 int launch_linear_gemm_group(int x_dtype, int y_dtype, const void* X, const void* W_b,
@@ -805,9 +794,8 @@ int launch_linear_gemm_group(int x_dtype, int y_dtype, const void* X, const void
                              int64_t d_out, int64_t d_in, int v_stride, int g_shift, PrefillSplit ps,
                              hipStream_t stream)
 {
-    if (x_dtype == kBF16)
-        return launch_gemm_group<kBF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream);
-    return launch_gemm_group<kF16>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream);
+    return x_dtype == kBF16 ? launch_prefill<kBF16, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream)
+                            : launch_prefill<kF16, 2>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, ps, stream);
 }
 
 int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const void* W_b,
@@ -815,10 +803,10 @@ int launch_linear_gemm(int x_dtype, int y_dtype, int axis, const void* X, const 
                        int64_t d_out, int64_t d_in, PrefillSplit ps, hipStream_t stream)
 {
     if (x_dtype == kBF16)
-        return axis == 0 ? launch_gemm_bm<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream)
-                         : launch_gemm_bm<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream);
-    return axis == 0 ? launch_gemm_bm<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream)
-                     : launch_gemm_bm<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, ps, stream);
+        return axis == 0 ? launch_prefill<kBF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps, stream)
+                         : launch_prefill<kBF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps, stream);
+    return axis == 0 ? launch_prefill<kF16, 0>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps, stream)
+                     : launch_prefill<kF16, 1>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, 0, 31, ps, stream);
 }
 
 // Measurement builds of the pipelined kernel (bf16 operands, row scales) with parts of its loop

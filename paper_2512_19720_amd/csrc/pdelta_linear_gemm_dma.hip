@@ -363,14 +363,15 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // Which calls run here, and how many tiles are split.  Both sides are priced with what was measured
 // (us, 256 CUs, steps of 64 inputs): here a step takes 1.75 (fp16) or 1.95 (bf16), a call 8 beside its
 // steps, a split 8 more for its second launch and 0.06 per part for the sums that it writes and reads;
-// the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernels 3 a call and 0.29 / 0.31 a step (0.045 more
-// when every CU has a tile), above one tile per CU 0.34 for each.  Against the latter a split pays 0.1 more per part: it
+// the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernels 3 a call and 0.29 / 0.31 a step, 0.05
+// more with column or blockwise scales (128 x 3072 x 8192 fp16: 44, 48 and 51 there, 42-44 here in 16 parts) and 0.045 more
+// when every CU has a tile, above one tile per CU 0.34 for each.  Against the latter a split pays 0.1 more per part: it
 // has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, changing
 // inputs, this kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 223-230 against 230-237, 777 x
 // 4096 x 11008 blockwise (64 tiles in 4 parts) 127 against 254, 1024 x 4096 x 4096 60 against 87, 256 x 512 x 8192 (2 tiles
 // in 16 parts) 36 against 43, 448 x 960 x 8192 fp16 blockwise (8 tiles in 16 parts) 38 against 45.5.  Below the line: 256 x
 // 1024 x 4096 (4 tiles in 16 parts) fp16 35 against 23, 402 x 384 x 5760 fp16 31 against 23, 251 x 4096 x 4096 32 against 25.
-BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, bool split_allowed)
+BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, bool split_allowed)
 {
     const BigSplit none{0, 0, 0};
     const int forced = tune_value("gemm_big", -1);    // 0: never; n > 0: in n parts (1: whole tiles only)
@@ -393,7 +394,8 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     const int64_t tiles128 = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int64_t tiles64 = ((M + 63) / 64) * ((d_out + 63) / 64);
     if (tiles128 <= 128) {
-        const double small = tiles64 <= 256 ? 3 + n * ((x_dtype == kBF16 ? 0.31 : 0.29) + 0.045 * (double)tiles64 / 256)
+        const double row = x_dtype == kBF16 ? 0.31 : 0.29;
+        const double small = tiles64 <= 256 ? 3 + n * ((axis == 0 ? row : row + 0.05) + 0.045 * (double)tiles64 / 256)
                                             : 3 + n * 0.34 * (double)tiles64 / 256;
         return best + (sp.split > 0 ? 0.1 * sp.parts : 0) < small ? sp : none;
     }
@@ -403,7 +405,7 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
 
 size_t linear_gemm_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int x_dtype)
 {
-    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, x_dtype, true);
+    const BigSplit sp = linear_gemm_big_split(M, d_out, d_in, x_dtype, 2, true);       // row calls split in some of these cases only
     return (size_t)sp.split * sp.parts * kPartBytes;
 }
 
