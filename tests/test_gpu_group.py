@@ -1,7 +1,9 @@
 """GPU parity of the blockwise ("per-group") and scalar scale entry points pdelta_pack_group,
 pdelta_linear_group and pdelta_patch_group against the CPU oracle: packed words, scales and merged
-weights bit for bit, Y under the tolerance rule of parity_util.py.  Shapes cover every dispatch
-branch (staged / plain decode kernels, small-tile and big-tile prefill kernels), ragged d_out,
+weights bit for bit, Y under the tolerance rule of parity_util.py.  Shapes cover the decode
+kernels with direct loads and from registers and the prefill kernels of 64 x 64 (with roles, with a
+ring of steps), 128 x 128 and 256 x 128 tiles (the staged decode kernel and the 256 x 256 tiles have
+tests of their own), ragged d_out,
 d_in that is not a multiple of 128, groups inside one 32-input word up to the whole row, rows
 that share their scales, and the single scalar."""
 import numpy as np
@@ -61,9 +63,9 @@ def test_pack_group_scalar_of_a_full_size_layer():
 
 
 LINEAR_CASES = [  # (M, d_out, d_in, group)
-    (1, 64, 512, 32), (4, 100, 1152, 128), (16, 37, 4096, 64), (16, 48, 11008, 256),     # staged decode kernel
-    (3, 33, 160, 32), (17, 64, 512, 64), (40, 100, 1056, 1056), (64, 16, 256, 256),      # plain decode kernel
-    (65, 128, 256, 64), (130, 257, 1024, 128), (300, 384, 512, 512), (200, 100, 96, 32), # prefill kernels
+    (1, 64, 512, 32), (4, 100, 1152, 128), (16, 37, 4096, 64), (16, 48, 11008, 256),     # decode kernel with direct loads
+    (3, 33, 160, 32), (17, 64, 512, 64), (40, 100, 1056, 1056), (64, 16, 256, 256),      # register decode kernel (d_in % 128 != 0), and direct loads
+    (65, 128, 256, 64), (130, 257, 1024, 128), (300, 384, 512, 512), (200, 100, 96, 32), # prefill: 64 x 64 with roles, 256 x 128
 ]
 
 
@@ -79,6 +81,43 @@ def test_linear_group_matches_oracle(M, d_out, d_in, group, dtype, shared):
         pd.pdelta_linear_group(X, W_b, B, v, group, out=Y)
         torch.cuda.synchronize()
         check_y(Y, ref, f"group linear M={M} {d_out}x{d_in} g={group} shared={shared} dt={dtype} y={yd}")
+
+
+# the 64 x 64 kernel with a ring of steps: d_in an odd multiple of 64 (which the kernel with roles does not take), fewer steps
+# than the ring, as many, and more; tiles cut in both directions
+@pytest.mark.parametrize("M,d_out,d_in,group", [(65, 130, 192, 64), (70, 65, 64, 32), (100, 70, 448, 64), (300, 300, 320, 320), (129, 128, 1088, 32)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("shared", [False, True])
+def test_linear_group_small_tile_kernel(M, d_out, d_in, group, dtype, shared):
+    for dt in (pd.F16, pd.BF16):
+        assert pd.lib().pdelta_probe_prefill_kernel(M, d_out, d_in, dt, 2, 1) == 64
+    L = group_case(d_out, d_in, M, dtype, group, shared, synth.seed_for(1, 8400 + M + d_out + group))
+    ref = orc.linear_group(L["X"], L["W_b"], L["B"], L["v"], group, dtype)
+    X, W_b, B, v = to_dev(L["X"], dtype), to_dev(L["W_b"], dtype), words_dev(L["B"]), v_dev(L["v"])
+    for yd in (torch.float32, TORCH16[dtype]):
+        Y = torch.full((M, d_out), float("nan"), dtype=yd, device=DEV)
+        pd.pdelta_linear_group(X, W_b, B, v, group, out=Y)
+        torch.cuda.synchronize()
+        check_y(Y, ref, f"group linear (small tiles) M={M} {d_out}x{d_in} g={group} shared={shared} dt={dtype} y={yd}")
+
+
+# the same kernel forced on shapes that the kernel with roles takes: the same sums in the same order
+@pytest.mark.parametrize("M,d_out,d_in,group", [(65, 128, 256, 64), (130, 257, 1024, 128), (300, 384, 512, 512)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_linear_group_small_tile_kernel_forced(M, d_out, d_in, group, dtype, monkeypatch):
+    L = group_case(d_out, d_in, M, dtype, group, False, synth.seed_for(1, 8500 + M + d_out + group))
+    ref = orc.linear_group(L["X"], L["W_b"], L["B"], L["v"], group, dtype)
+    X, W_b, B, v = to_dev(L["X"], dtype), to_dev(L["W_b"], dtype), words_dev(L["B"]), v_dev(L["v"])
+    for yd in (torch.float32, TORCH16[dtype]):
+        got = []
+        for roles, kernel in ((0, 64), (1, 65)):
+            monkeypatch.setenv("PDELTA_TUNE", f"gemm_big=0,gemm_small=1,gemm_roles={roles}")
+            assert pd.lib().pdelta_probe_prefill_kernel(M, d_out, d_in, pd.BF16, 2, 1) == kernel
+            got.append(torch.full((M, d_out), float("nan"), dtype=yd, device=DEV))
+            pd.pdelta_linear_group(X, W_b, B, v, group, out=got[-1])
+        torch.cuda.synchronize()
+        check_y(got[0], ref, f"group linear (small tiles forced) M={M} {d_out}x{d_in} g={group} dt={dtype} y={yd}")
+        assert torch.equal(got[0].view(torch.uint8), got[1].view(torch.uint8))
 
 
 @pytest.mark.parametrize("M,d_out,d_in,group", [c for c in LINEAR_CASES if c[0] > 128])

@@ -65,12 +65,13 @@ def test_decode_stack_shapes_batch1(shape, dtype):
 @pytest.mark.parametrize("M,d_out,d_in", [(65, 128, 64), (200, 100, 96), (256, 300, 160), (129, 257, 1024),
                                           (128, 128, 32), (1000, 384, 512), (70, 1000, 448), (300, 65, 192)])
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
-@pytest.mark.parametrize("kernel", ["two_per_cu", "pipelined", "small_tile"])
+@pytest.mark.parametrize("kernel", ["two_per_cu", "pipelined", "small_tile", "small_tile_ring"])
 def test_prefill_path_small_and_ragged(M, d_out, d_in, dtype, kernel, monkeypatch):
-    # all three prefill kernels on every shape (the library would pick by tile count; the
-    # small-tile kernel needs d_in % 64 == 0 and otherwise leaves the shape to the others)
+    # the prefill kernels of pdelta_linear_gemm.hip on every shape (the library would pick by tile count; the small-tile
+    # kernels need d_in % 64 == 0 and otherwise leave the shape to the others: small_tile is the one with roles where
+    # d_in is a multiple of 128, small_tile_ring the one with a ring of steps)
     monkeypatch.setenv("PDELTA_TUNE", {"two_per_cu": "gemm_small=0,gemm_pipe=0", "pipelined": "gemm_small=0,gemm_pipe=1",
-                                       "small_tile": "gemm_small=1"}[kernel])
+                                       "small_tile": "gemm_small=1", "small_tile_ring": "gemm_small=1,gemm_roles=0"}[kernel])
     L = make_case(d_out, d_in, M, dtype, "row", synth.seed_for(2, M + d_out + d_in))
     run_both_axes(L, (pd.F32, pd.F16 if dtype == synth.F16 else pd.BF16), f"prefill {M}x{d_out}x{d_in} dt={dtype}")
 

@@ -1,6 +1,6 @@
-"""Seeded random shapes through every dispatch branch of pdelta_linear_row / pdelta_linear_col
-(staged and plain decode kernels, 8 and 16 waves, X staged or not, small-tile / two-per-CU /
-pipelined prefill), each compared with the fp64 oracle under the rule of parity_util.py."""
+"""Seeded random shapes through the default dispatch of pdelta_linear_row / pdelta_linear_col (decode with
+direct loads and from registers; prefill on 64 x 64 tiles with roles and with a ring of steps, 128 x 128,
+256 x 128 and split 256 x 256 tiles), each compared with the fp64 oracle under the rule of parity_util.py."""
 import numpy as np
 import pytest
 import torch

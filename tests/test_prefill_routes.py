@@ -37,3 +37,11 @@ def test_argument_errors():
     probe = pd.lib().pdelta_probe_prefill_kernel
     assert probe(0, 64, 64, pd.F16, ROW, 0) == pd.EINVAL and probe(65, 64, 64, pd.F16, 3, 0) == pd.EINVAL and probe(65, 64, 64, pd.F16, ROW, 2) == pd.EINVAL
     assert probe(64, 64, 64, pd.F16, ROW, 0) == pd.ESHAPE and probe(65, 64, 48, pd.F16, ROW, 0) == pd.ESHAPE and probe(65, 64, 64, pd.F32, ROW, 0) == pd.EDTYPE
+
+
+# the cases of the GPU tests that are there for one kernel reach it
+@pytest.mark.parametrize("M,d_out,d_in,kernel", [
+    (65, 128, 256, 65), (130, 257, 1024, 65), (300, 384, 512, 65), (200, 100, 96, 256), (65, 130, 192, 64), (100, 70, 448, 64), (300, 300, 320, 64)])
+def test_blockwise_cases_of_the_gpu_tests(M, d_out, d_in, kernel):
+    for dtype in (pd.F16, pd.BF16):
+        assert route(M, d_out, d_in, GROUP, dtype) == kernel
