@@ -342,8 +342,9 @@ int pdelta_linear_variants(const void* X, const void* W_b, const pdelta_variant*
  * workspace.  M = 0 writes zeros.
  */
 size_t pdelta_grad_v_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis);
-/* Bytes with which few tokens (or few outputs) also run fast: the contraction is then cut into parts with
- * partial sums of their own.  At least pdelta_grad_v_workspace_bytes; pdelta_grad_v takes either. */
+/* Bytes with which the call runs fastest: where that fills the chip better, the contraction is cut into up to 16 parts with
+ * partial sums of their own (2048 tokens on 4096 x 4096: two parts).  At least pdelta_grad_v_workspace_bytes; pdelta_grad_v
+ * takes either, and anything between them as the smaller one (the sums are then cut elsewhere). */
 size_t pdelta_grad_v_split_workspace_bytes(int64_t M, int64_t d_out, int64_t d_in, int axis);
 
 int pdelta_grad_v(const void* X, const void* dY, const uint32_t* B_packed, int axis, float* grad_v,

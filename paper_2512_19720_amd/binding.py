@@ -479,7 +479,8 @@ def pdelta_grad_v_workspace_bytes(M: int, d_out: int, d_in: int, axis: int) -> i
 
 
 def pdelta_grad_v_split_workspace_bytes(M: int, d_out: int, d_in: int, axis: int) -> int:
-    """Bytes with which calls of few tokens run fast (what ``pdelta_grad_v`` allocates); the size above also works."""
+    """Bytes with which the call runs fastest (what ``pdelta_grad_v`` allocates): large calls are cut into parts too.  The
+    size above also works, more slowly."""
     return int(lib().pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis))
 
 

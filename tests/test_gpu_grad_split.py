@@ -1,6 +1,7 @@
 """The 256 x 256 gradient kernel, whole and in parts of the contraction, at the edges of its tiles, steps and
 parts, against the fp64 oracle under the rule of test_gpu_grad_v.py, and its workspace sizes."""
 import pytest
+import torch
 
 from oracle import pdelta_oracle as orc
 from paper_2512_19720_amd import binding as pd
@@ -35,6 +36,24 @@ def test_transposed_signs_and_many_partial_rows(M, d_out, d_in, axis):
     check_grad(got, ref, f"M={M} {d_out}x{d_in} axis={axis}")
 
 
+# exactly the least workspace where the call would rather run in parts: the 256 x 128 kernel, which needs no more, and
+# nothing behind the workspace is written; and a byte less than the parts take
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,d_out,d_in", [(64, 128, 1024), (300, 640, 256), (513, 256, 384)])
+@pytest.mark.parametrize("axis", [orc.ROW, orc.COL])
+def test_least_workspace(M, d_out, d_in, axis):
+    least, parts = (f(M, d_out, d_in, axis) for f in (pd.pdelta_grad_v_workspace_bytes, pd.pdelta_grad_v_split_workspace_bytes))
+    X, dY, B = make(M, d_out, d_in, synth.BF16, 3 * M + d_out + d_in)
+    ref = orc.grad_v(X, dY, B, axis, synth.BF16)
+    Xd, dYd, Bd = to_dev(X, synth.BF16), to_dev(dY, synth.BF16), words_dev(B)
+    for size in sorted({least, max(least, parts - 1), parts}):
+        memory = torch.full((parts + 4096,), 0xCD, dtype=torch.uint8, device=Xd.device)
+        got = pd.pdelta_grad_v(Xd, dYd, Bd, axis, workspace=memory[:size])
+        torch.cuda.synchronize()
+        check_grad(got, ref, f"workspace of {size} bytes M={M} {d_out}x{d_in} axis={axis}")
+        assert bool((memory[size:] == 0xCD).all()), f"written behind a workspace of {size} bytes"
+
+
 def test_split_workspace_sizes():
     L = pd.lib()
     assert L.pdelta_grad_v_split_workspace_bytes(256, 4096, 4096, pd.ROW) == 8 * 4096 * 4        # 16 tiles in 8 parts
@@ -44,6 +63,12 @@ def test_split_workspace_sizes():
         for d_out, d_in in ((32, 32), (256, 640), (4096, 4096), (14336, 4096), (4096, 11008)):
             for axis in (pd.ROW, pd.COL):
                 assert L.pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis) >= pd.pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis)
+
+
+def test_cases_of_the_least_workspace_would_run_in_parts():
+    for M, d_out, d_in in ((64, 128, 1024), (300, 640, 256), (513, 256, 384)):
+        for axis, k in ((pd.ROW, d_in), (pd.COL, d_out)):
+            assert (pd.pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis) > pd.pdelta_grad_v_workspace_bytes(M, d_out, d_in, axis)) == (k > 128)
 
 
 def test_parts_of_few_tiles():
