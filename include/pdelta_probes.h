@@ -63,7 +63,7 @@ int pdelta_probe_prefill_parts(int parts, const void* X, const void* W_b, const 
  * Which kernel a decode call (1 <= M <= 64) would run, decided from the sizes alone: nothing is launched and no GPU is
  * needed.  axis: PDELTA_ROW, PDELTA_COL, or 2 for blockwise scales with `group` inputs per scale (ignored otherwise).
  * Returns 0 for the register kernel, 1, 2 or 3 for the kernel with direct loads into LDS and that many tiles of 16 output
- * rows per workgroup, 8 or 16 for the staged kernel with that many waves; PDELTA_EINVAL / PDELTA_ESHAPE / PDELTA_EDTYPE for
+ * rows per workgroup, 8 for the staged kernel; PDELTA_EINVAL / PDELTA_ESHAPE / PDELTA_EDTYPE for
  * arguments that the linear calls refuse as well, and PDELTA_ESHAPE above 64 tokens.
  */
 int pdelta_probe_decode_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int64_t group);

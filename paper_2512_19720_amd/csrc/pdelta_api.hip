@@ -575,7 +575,7 @@ int pdelta_probe_decode_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     if (!is_w_dtype(x_dtype)) return PDELTA_EDTYPE;
     const DecodeRoute route = linear_skinny_route(x_dtype, axis, M, d_out, d_in, g_shift);
     if (route.kernel == kDecodeDirect) return route.rows;
-    return route.kernel == kDecodeStaged ? 8 : route.kernel == kDecodeStaged16 ? 16 : 0;
+    return route.kernel == kDecodeStaged ? 8 : 0;
 }
 
 int pdelta_probe_prefill_kernel(int64_t M, int64_t d_out, int64_t d_in, int x_dtype, int axis, int may_split)

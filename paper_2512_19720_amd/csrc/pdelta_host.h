@@ -54,7 +54,7 @@ int launch_linear_skinny_group(int x_dtype, int y_dtype, const void* X, const vo
                                int64_t d_out, int64_t d_in, int v_stride, int g_shift, hipStream_t stream);
 // Which kernel takes a decode call (axis 2: blockwise scales), and of the one with direct loads how many tiles of 16 output
 // rows a workgroup takes.
-enum DecodeKernel { kDecodeRegisters, kDecodeStaged, kDecodeStaged16, kDecodeDirect };
+enum DecodeKernel { kDecodeRegisters, kDecodeStaged, kDecodeDirect };
 struct DecodeRoute { DecodeKernel kernel; int rows; };
 DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift);
 // The kernel with direct loads into LDS: d_in a multiple of 128, rows of 1 to 3 tiles.

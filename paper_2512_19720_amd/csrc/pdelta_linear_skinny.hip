@@ -455,33 +455,33 @@ static size_t staged_lds_bytes(int waves, int x_copies, bool stage_x, int64_t M,
 }
 
 // One layer with column or blockwise scales, its few tokens and their fp16 forms in LDS: see linear_skinny_route.
-template <int XDT, int AXIS, int WAVES>
-__global__ void __launch_bounds__(WAVES * 64)
+template <int XDT, int AXIS>
+__global__ void __launch_bounds__(512)
 linear_skinny_staged_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
                             const uint16_t* __restrict__ v, void* __restrict__ Y, int M, int d_out, int d_in, int y_dtype,
                             int v_stride, int g_shift)
 {
-    staged_body<XDT, AXIS, WAVES, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x, v_stride, g_shift);
+    staged_body<XDT, AXIS, 8, 2, true>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, (int)blockIdx.x, v_stride, g_shift);
 }
 
 // LDS bytes of a workgroup of that kernel, or 0 when it does not apply.
-static size_t staged_layer_bytes(int waves, int x_dtype, int axis, int64_t M, int64_t K, int g_shift)
+static size_t staged_layer_bytes(int x_dtype, int axis, int64_t M, int64_t K, int g_shift)
 {
     if (axis == 0 || K % 128 != 0 || M > 16) return 0;
-    const size_t bytes = staged_lds_bytes(waves, axis == 1 || x_dtype == kBF16 ? 2 : 1, true, M, K);
+    const size_t bytes = staged_lds_bytes(8, axis == 1 || x_dtype == kBF16 ? 2 : 1, true, M, K);
     const size_t scales = axis == 2 ? (size_t)16 * (g_shift < 31 ? K >> g_shift : 1) * 2 : 0;
     return bytes != 0 && bytes + scales <= kStagedLdsLimit ? bytes + scales : 0;
 }
 
-template <int XDT, int AXIS, int WAVES>
+template <int XDT, int AXIS>
 static int launch_staged(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                          int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
-    auto kernel = linear_skinny_staged_kernel<XDT, AXIS, WAVES>;
-    const size_t lds = staged_layer_bytes(WAVES, XDT, AXIS, M, d_in, g_shift);
+    auto kernel = linear_skinny_staged_kernel<XDT, AXIS>;
+    const size_t lds = staged_layer_bytes(XDT, AXIS, M, d_in, g_shift);
     static unsigned lds_opted_in = 0;                 // per template instance: one kernel
     if (lds > 48 * 1024 && opt_in_dynamic_lds((const void*)kernel, (int)kStagedLdsLimit, &lds_opted_in) != 0) return -1;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(WAVES * 64), lds, stream, (const uint16_t*)X,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((d_out + 15) / 16)), dim3(512), lds, stream, (const uint16_t*)X,
                        (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype, v_stride, g_shift);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -534,7 +534,8 @@ int launch_linear_skinny_batch(int x_dtype, int y_dtype, const pdelta_layer* lay
 }
 
 // Which kernel takes a decode call.  d_in not a multiple of 128: the register kernel.  Else the kernel with direct loads,
-// except up to 16 tokens where one of the older kernels was measured faster (us, changing weights, 24 calls in a row):
+// except up to 16 tokens where one of the older kernels was measured faster (below: us of the older one, then of the one
+// with direct loads, changing weights, calls in a row):
 // they hide one workgroup's start behind another's end, and a CU holds several of them.  That counts for rows of a multiple
 // of 4 KB (d_in a multiple of 2048) above all; the line was found by measuring, not derived (such rows begin at the same
 // few memory channels).
@@ -542,7 +543,7 @@ int launch_linear_skinny_batch(int x_dtype, int y_dtype, const pdelta_layer* lay
 // Row scales, up to 16 tokens: is the register kernel the better one?  `rows`, `rounds`: what the other one would take.
 static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int64_t rounds)
 {
-    if (d_out <= 256 * 16) return false;              // one round (4096 x 4096, one token: 8.7 there, 8.2 here)
+    if (d_out <= 256 * 16) return false;              // one round (4096 x 4096, one token: 8.7 and 8.2)
     if (M <= 4) return true;                          // 8192 x 4096 14.1 and 15.3, 14336 x 2048 13.4 and 14.4, 11008 x 4096 18.9 and 19.5
     const bool thin = rounds > 2 && rounds * rows * 4096 * 8 > d_out * 9;      // a ninth or more of the last round is empty
     // some waves have no unit: 10240 x 512, 12 tokens 4.7 and 5.3, 18432 x 512 6.8 and 7.5; 14336 x 512 6.3 and 5.6
@@ -557,49 +558,47 @@ static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int6
     return d_in % 4096 == 0 && rows == 1;             // 8192 x 4096, twelve 16.1 and 16.9, 28672 x 8192, sixteen 100 and 99.6-102
 }
 
-// Column and blockwise scales, up to 16 tokens: waves of the staged kernel where it is the better one, else 0.  It forms
-// fp16(X v) and fp16(X) once per workgroup.
-static int staged_pays(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift, int rows, int64_t rounds)
+// Column and blockwise scales, up to 16 tokens: is the staged kernel the better one?  It forms fp16(X v) and fp16(X) once per
+// workgroup.
+static bool staged_pays(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift, int rows, int64_t rounds)
 {
-    auto fits = [&](int waves, size_t lds) {
-        const size_t need = staged_layer_bytes(waves, x_dtype, axis, M, d_in, g_shift);
+    auto fits = [&](size_t lds) {
+        const size_t need = staged_layer_bytes(x_dtype, axis, M, d_in, g_shift);
         return need != 0 && need + 128 <= lds;        // (128: the table of signs)
     };
     constexpr size_t half = 80 * 1024;                // two workgroups a CU
-    // col, one and two tokens: 8192 x 4096 14.3 and 16.3, 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0
-    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return fits(8, kStagedLdsLimit) ? 8 : 0;
-    // one bf16 token with column scales in one round, 2048 x 4096 7.9 and 8.3, 4096 x 6144 12.6 and 13.4; sixteen waves for
-    // long rows, 2048 x 8192 11.7 and 12.5, 4096 x 11008 21.9 and 22.7 (4096 x 8192 even)
-    if (axis == 1 && x_dtype == kBF16 && M == 1 && d_out <= 256 * 16) {
-        if (d_in >= 8192 && d_in < 14336 && d_out <= (d_in % 4096 == 0 ? 2048 : 4096)) return fits(16, kStagedLdsLimit) ? 16 : 0;
-        return d_in < 8192 && d_in % 2048 == 0 && d_out >= 2048 && fits(8, half) ? 8 : 0;
-    }
-    // Rows of 8 or 12 KB: blockwise, one token, 8192 x 4096 15.6 and 16.5, 14336 x 4096 26.4 and 28.4, 32000 x 4096 51.3 and
-    // 55.7; 8192 x 6144 21.3 and 24.1; col, three tokens, 8192 x 4096 15.8 and 17.7.  Three tokens with bf16 blocks are
-    // even (29.0 and 28.7), and in a single round of 48-row workgroups the other one is ahead earlier (10240 x 4096, one
-    // token 21.0 and 19.7; two, 12288 x 4096 23.6 and 23.3).  One token on rows of 16 KB: 6144 x 8192 24.8 and 26.3.
-    if (d_in == 8192) return axis == 2 && M == 1 && d_out > 5120 && d_out <= 7168 && fits(8, half) ? 8 : 0;
-    if (d_in % 2048 != 0 || d_in < 4096 || d_in > 8192 || d_out <= 6144) return 0;
-    int64_t most = axis == 2 && g_shift < 31 && x_dtype == kBF16 ? 2 : 3;
-    if (rows == 3 && rounds == 1) most = axis == 1 || d_in != 4096 ? 2 : (d_out > 10240 ? 1 : 0);
-    return M <= most && fits(8, half) ? 8 : 0;
+    // col, one and two tokens: 8192 x 4096 14.3 and 16.2, 14336 x 2048 14.1 and 14.7; from 8192 inputs on 31.9 and 31.0
+    if (axis == 1 && d_out > 256 * 16 && M <= 2 && d_in < 8192) return fits(kStagedLdsLimit);
+    // One bf16 token with column scales on rows of 4 KB: 4096 x 2048 6.4 and 6.8 (4096 x 4096 even, 4096 x 1024 5.1 and 4.6)
+    if (axis == 1 && x_dtype == kBF16 && M == 1 && d_out >= 2048 && d_out <= 256 * 16 && d_in == 2048) return fits(half);
+    // Rows of 8 or 12 KB, above 6144 outputs.  8192 x 6144 blockwise, one token 21.3 and 22.8, 28672 x 6144 67 and 75; col, three
+    // tokens, 8192 x 4096 16.6 and 17.4; one scale per row, one token, 14336 x 4096 25.3 and 27.0; groups only with one bf16 token,
+    // 16384 x 4096 28.5 and 29.7 (two: even).  In a single round of 48-row workgroups the other one is ahead (10240 x 4096).
+    // One token on rows of 16 KB: 6144 x 8192 24.8 and 25.8.
+    if (d_in == 8192) return axis == 2 && M == 1 && d_out > 5120 && d_out <= 7168 && fits(half);
+    if (d_out <= 6144 || (d_in != 4096 && d_in != 6144)) return false;
+    const bool single = rows == 3 && rounds == 1, scalar = axis == 2 && g_shift >= 31;
+    int64_t most = 3;
+    if (d_in == 4096) most = single ? (scalar && d_out > 10240 ? 1 : 0) : (axis == 1 || scalar ? 3 : x_dtype == kBF16 ? 1 : 0);
+    return M <= most && fits(half);
 }
 
 DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out, int64_t d_in, int g_shift)
 {
     const int forced = tune_value("skinny_dma", -1), staged = tune_value("skinny_staged", -1);
     if (d_in % 128 != 0 || forced == 0) return DecodeRoute{kDecodeRegisters, 1};
-    if (staged > 0 && staged_layer_bytes(8, x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
+    if (staged > 0 && staged_layer_bytes(x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
     if (forced > 0) return DecodeRoute{kDecodeDirect, std::min(forced, 3)};
     const int mt = (int)((M + 15) / 16);
     // Row tiles per workgroup: the least rounds of 256 workgroups times what a round weighs, 8, 13, 20 for one token tile
     // (4096 inputs, 16 tokens: 9.0, 12.2, 12.6 us in one round; 18432 x 1024: 13.9, 10.1, 11.0 in five, three, two) and
     // 3 mt + k (4 + mt) for more, which only ranks them (64 tokens: 15, 19, 22 in one round).  Two tiles on more than 6144
     // rows of a multiple of 8 KB are left out: 11008 x 4096 24.9 against 21.1-22, 8192 x 8192 36 against 31-33.
-    // bf16 with column scales converts X in every workgroup, so three tiles weigh 18 there where two are left out (20480 x
-    // 4096, six tokens: 37.5 with three, 40.5 with one).
+    // Then three weigh 22 up to eight tokens (32000 x 4096 blockwise, one token: 55.5 and 53.4 with one; col fp16, sixteen: 58.9
+    // and 61.3), but 18 where bf16 with column scales converts X in every workgroup (20480 x 4096, six tokens: 37.5 with three,
+    // 40.5 with one).
     const bool no_two = mt == 1 && d_out > 6144 && d_in % 4096 == 0;
-    const int third = mt == 1 && !(no_two && axis == 1 && x_dtype == kBF16) ? 2 : 0;
+    const int third = mt > 1 ? 0 : !no_two ? 2 : axis == 1 && x_dtype == kBF16 ? 0 : M <= 8 ? 4 : 2;
     int rows = 1;
     int64_t best = 0, rounds = 0;
     for (int k = 1; k <= 3; ++k) {
@@ -609,8 +608,7 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
     }
     if (mt > 1) return DecodeRoute{kDecodeDirect, rows};
     if (axis == 0) return registers_pay(M, d_out, d_in, rows, rounds) ? DecodeRoute{kDecodeRegisters, 1} : DecodeRoute{kDecodeDirect, rows};
-    const int waves = staged == 0 ? 0 : staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds);
-    if (waves != 0) return DecodeRoute{waves == 16 ? kDecodeStaged16 : kDecodeStaged, 1};
+    if (staged != 0 && staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds)) return DecodeRoute{kDecodeStaged, 1};
     // Few tokens on long rows that fill their rounds: 12288 x 11008 blockwise, one token 59.0 with one tile, 64.0 with three
     if (M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288))) rows = 1;
     return DecodeRoute{kDecodeDirect, rows};
@@ -644,12 +642,10 @@ static int launch_axis(int axis, const void* X, const void* W_b, const uint32_t*
 #define PDELTA_GO(LAUNCH) return LAUNCH(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, v_stride, g_shift, stream)
     if (axis == 0) PDELTA_GO((launch_registers<XDT, 0>));
     if (axis == 1) {
-        if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 1, 8>));
-        if constexpr (XDT == kBF16)
-            if (route.kernel == kDecodeStaged16) PDELTA_GO((launch_staged<XDT, 1, 16>));
+        if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 1>));
         PDELTA_GO((launch_registers<XDT, 1>));
     }
-    if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 2, 8>));
+    if (route.kernel == kDecodeStaged) PDELTA_GO((launch_staged<XDT, 2>));
     PDELTA_GO((launch_registers<XDT, 2>));
 #undef PDELTA_GO
 }

@@ -36,12 +36,14 @@ constexpr int dma_wave_bytes(int axis, int mt, int nt, int depth)
     return depth * (mt + nt) * 2048 + kDmaBufs * (nt * 256 + (axis == 1 ? 256 : 0) + (axis == 2 ? nt * 256 : 0));
 }
 
-// One row tile: as many stages as the LDS of a CU holds, up to four (16 tokens, 4096 x 4096: 9.0 us, 9.3 with two); more
+// One row tile: as many stages as the LDS of a CU holds, up to three.  A fourth brings nothing to a call by itself (16 tokens,
+// 4096 x 4096 row: 9.0 us, 9.3 with two or four) and slows down calls on other streams (four streams, one token: 8.1 us a call,
+// 8.9 with four, 7.6 with two, which cost a call by itself 0.2).  More
 // tiles: one (32 rows, 24 tokens, 11008 x 4096: 25.9 us, 29.5 with two, which leave room for one workgroup a CU).
 constexpr int dma_depth(int axis, int mt, int nt)
 {
     if (nt > 1) return 1;
-    int depth = 4;
+    int depth = 3;
     while (kDmaWaves * dma_wave_bytes(axis, mt, nt, depth) > 160 * 1024) --depth;
     return depth;
 }

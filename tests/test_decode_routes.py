@@ -1,5 +1,5 @@
 """Which decode kernel the library takes, on both sides of the lines that were measured (no GPU needed): 0 the register
-kernel, 1 to 3 the one with direct loads and that many row tiles, 8 or 16 the staged one with that many waves."""
+kernel, 1 to 3 the one with direct loads and that many row tiles, 8 the staged one."""
 import pytest
 
 from paper_2512_19720_amd import binding as pd
@@ -22,22 +22,23 @@ def test_row_scales(M, d_out, d_in, kernel):
         assert route(M, d_out, d_in, ROW, dtype) == kernel
 
 
-# column scales: three tokens on rows of 8 KB, one bf16 token in one round, two tiles that do not meet at one channel
+# column scales: one to three tokens on rows of 8 KB, one bf16 token on rows of 4 KB, two tiles that do not meet at one channel
 @pytest.mark.parametrize("M,d_out,d_in,dtype,kernel", [
     (3, 8192, 4096, pd.BF16, 8), (3, 14336, 4096, pd.F16, 8), (3, 32000, 4096, pd.BF16, 8), (2, 8192, 4096, pd.F16, 8), (1, 14336, 2048, pd.BF16, 8),
-    (1, 2048, 4096, pd.BF16, 8), (1, 4096, 6144, pd.BF16, 8), (1, 2048, 8192, pd.BF16, 16), (1, 4096, 11008, pd.BF16, 16),
-    (3, 11008, 4096, pd.BF16, 3), (4, 8192, 4096, pd.BF16, 1), (4, 6144, 4096, pd.BF16, 2), (1, 2048, 4096, pd.F16, 1), (1, 4096, 8192, pd.BF16, 1),
-    (1, 4096, 11008, pd.F16, 1), (3, 14336, 2048, pd.BF16, 2), (6, 20480, 4096, pd.BF16, 3), (6, 20480, 4096, pd.F16, 1), (2, 8192, 8192, pd.BF16, 1)])
+    (1, 4096, 2048, pd.BF16, 8), (1, 2048, 2048, pd.BF16, 8), (1, 1024, 2048, pd.BF16, 1), (1, 4096, 2048, pd.F16, 1), (1, 2048, 4096, pd.BF16, 1),
+    (3, 11008, 4096, pd.BF16, 3), (4, 8192, 4096, pd.BF16, 1), (4, 6144, 4096, pd.BF16, 2), (3, 8192, 6144, pd.BF16, 2), (3, 14336, 2048, pd.BF16, 2),
+    (6, 20480, 4096, pd.BF16, 3), (6, 20480, 4096, pd.F16, 1), (2, 8192, 8192, pd.BF16, 1)])
 def test_column_scales(M, d_out, d_in, dtype, kernel):
     assert route(M, d_out, d_in, COL, dtype) == kernel
 
 
 # blockwise scales (0: one scale per row)
 @pytest.mark.parametrize("M,d_out,d_in,dtype,group,kernel", [
-    (1, 8192, 4096, pd.BF16, 128, 8), (1, 14336, 4096, pd.BF16, 128, 8), (2, 32000, 4096, pd.BF16, 128, 8), (3, 32000, 4096, pd.BF16, 0, 8),
-    (3, 14336, 4096, pd.F16, 128, 8), (2, 8192, 6144, pd.BF16, 128, 8), (1, 12288, 6144, pd.BF16, 0, 8), (1, 12288, 4096, pd.BF16, 128, 8),
+    (1, 8192, 4096, pd.BF16, 128, 8), (1, 32000, 4096, pd.BF16, 128, 8), (3, 32000, 4096, pd.BF16, 0, 8), (2, 14336, 4096, pd.F16, 0, 8),
+    (1, 12288, 4096, pd.F16, 0, 8), (2, 8192, 6144, pd.BF16, 128, 8), (3, 28672, 6144, pd.F16, 128, 8), (1, 12288, 6144, pd.BF16, 0, 8),
     (1, 6144, 8192, pd.BF16, 128, 8), (1, 12288, 11008, pd.BF16, 128, 1),
-    (3, 14336, 4096, pd.BF16, 128, 1), (1, 10240, 4096, pd.BF16, 128, 3), (2, 12288, 4096, pd.BF16, 128, 3), (1, 5120, 4096, pd.BF16, 128, 2),
+    (2, 8192, 4096, pd.BF16, 128, 1), (1, 8192, 4096, pd.F16, 128, 1), (1, 32000, 4096, pd.F16, 128, 1), (1, 12288, 4096, pd.BF16, 128, 3),
+    (2, 12288, 4096, pd.BF16, 0, 3), (1, 10240, 4096, pd.BF16, 0, 3), (1, 5120, 4096, pd.BF16, 128, 2), (3, 14336, 6144, pd.BF16, 128, 2),
     (1, 8192, 8192, pd.BF16, 128, 1), (1, 14336, 2048, pd.BF16, 128, 2), (1, 4096, 4096, pd.F16, 128, 1), (1, 8192, 4096 + 32, pd.F16, 32, 0)])
 def test_blockwise_scales(M, d_out, d_in, dtype, group, kernel):
     assert route(M, d_out, d_in, GROUP, dtype, group or d_in) == kernel
@@ -50,7 +51,7 @@ def test_routes_that_do_not_fit_are_not_taken(monkeypatch):
             for M in (1, 2, 3, 8, 16, 17, 64):
                 for d_in in (32, 128, 4096, 8192, 28672, 1 << 22):
                     for d_out in (1, 4096, 6000, 8192, 12288, 1 << 22):
-                        assert route(M, d_out, d_in, axis, dtype, 32) in (0, 1, 2, 3, 8, 16)
+                        assert route(M, d_out, d_in, axis, dtype, 32) in (0, 1, 2, 3, 8)
                         if d_in > 28672:
                             assert route(M, d_out, d_in, axis, dtype, 32) < 8
     monkeypatch.setenv("PDELTA_TUNE", "skinny_staged=1")

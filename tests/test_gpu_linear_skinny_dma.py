@@ -95,14 +95,3 @@ def test_staged_kernel(M, d_out, d_in, dtype, monkeypatch):
                 call(got[-1])
             check_y(got[0], ref, f"staged {name} M={M} {d_out}x{d_in} dt={dtype}")
             assert torch.equal(got[0].view(torch.uint8), got[1].view(torch.uint8)), f"staged {name} M={M} {d_out}x{d_in} dt={dtype}"
-
-
-# one bf16 token with column scales on few long rows runs on sixteen waves: sums of its own
-@pytest.mark.parametrize("d_out,d_in", [(17, 8192), (100, 11008), (16, 12288)])
-def test_staged_kernel_with_sixteen_waves(d_out, d_in):
-    assert pd.lib().pdelta_probe_decode_kernel(1, d_out, d_in, pd.BF16, pd.COL, 0) == 16
-    L = make_case(d_out, d_in, 1, synth.BF16, "col", d_out + d_in)
-    d = L["d"]
-    Y = torch.full((1, d_out), float("nan"), dtype=torch.float32, device=DEV)
-    pd.pdelta_linear_col(d["X"], d["W_b"], d["B"], d["v_col"], out=Y)
-    check_y(Y, orc.linear(L["X"], L["W_b"], L["B"], L["v_col"], orc.COL, L["dtype"]), f"16 waves {d_out}x{d_in}")
