@@ -11,7 +11,9 @@ namespace pdelta {
 
 // Whether pack and patch read (and write) the weights of a call, this many in each matrix, as non-temporal: from 16 MiB on.
 // Seven layers of 704 x 640 packed at once (6 MiB, in the caches) take 17.6 us without and 19.2 with; two of 1024 x 4096
-// (16 MiB) 21.8 and 20.1; one of 2048 x 4096 patched (16 MiB) 8.7 and 7.8, and above it is 3 to 18 % everywhere.
+// (16 MiB) 21.8 and 20.1; one of 2048 x 4096 patched (16 MiB) 8.7 and 7.8, and above it is 3 to 18 % everywhere.  A patched
+// layer is then not in the last-level cache: up to about 128 MiB who reads it next waits for what patch saved (8192 x 4096,
+// patch and one read of the result 36.8 without and 38.2 with, 4096 x 4096 21.0 and 21.5), above that both gain.
 inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)16 << 20; }
 
 // Bytes of fp64 partial sums pdelta_pack writes for these dimensions.
