@@ -40,3 +40,26 @@ def test_kernels_with_direct_loads_do_not_spill(tmp_path):
     assert len(found) == 72 + 6                                      # two operand types, three kinds of scales; 4 x 3 decode tiles
     for name, entry in found.items():
         assert re.search(r"\.vgpr_spill_count:\s+0\b", entry) and re.search(r"\.private_segment_fixed_size:\s+0\b", entry), name
+
+
+# Registers that a kernel may keep in scratch memory; every other kernel none.  The variants kernels hold the sums of 16 slots
+# (17 accumulators) beside what is in flight; the general prefill and gradient kernels run where no faster one does.
+SPILLS = {"linear_gemm_kernel": 31, "linear_variants_slab_kernel": 76, "linear_variants_kernel": 2, "grad_tile_kernel": 5}
+
+
+def test_spilled_registers_of_every_kernel(tmp_path):
+    found = kernels(tmp_path)
+    names = {n: re.match(r"_ZN6pdelta(\d+)", n) for n in found}
+    assert all(names.values())
+    seen = set()
+    for name, entry in found.items():
+        at = names[name].end()
+        family = name[at:at + int(names[name].group(1))]
+        seen.add(family)
+        spilled = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", entry).group(1))
+        scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", entry).group(1))
+        # 4 bytes a lane for each spilled register, and the alignment of the area
+        assert spilled <= SPILLS.get(family, 0), (name, spilled)
+        assert scratch <= (4 * SPILLS[family] + 16 if family in SPILLS else 0), (name, scratch)
+    assert {"grad_big_kernel", "grad_tile_pipe_kernel", "linear_skinny_kernel", "linear_skinny_staged_kernel",
+            "linear_gemm_small_kernel", "pack_main_kernel", "patch_kernel"} | set(SPILLS) <= seen
