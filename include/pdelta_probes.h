@@ -7,7 +7,8 @@
  *
  * Conventions as in pdelta.h: device pointers owned by the caller, `stream` is a hipStream_t
  * passed as void*, the call enqueues and returns, a pdelta_status comes back, arguments are
- * checked on the host before any HIP call.
+ * checked on the host before any HIP call.  The last two functions launch nothing: they say which
+ * kernel a linear call would run (for the tests of the dispatch).
  */
 #ifndef PDELTA_PROBES_H
 #define PDELTA_PROBES_H

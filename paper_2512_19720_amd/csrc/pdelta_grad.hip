@@ -575,8 +575,9 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
 // workgroups takes 4 us and 1.12 us per step of 64 inputs (1.44 when all CUs multiply and the clock falls); a part more
 // is one more row of partial sums for the second launch.  Up to 16 parts for at most 128 workgroups (one token, 8192 x 1024
 // col 24.9 us, 33.5 with eight; 2048 x 8192 row 20.8 and 29.4), else up to eight.  Changing
-// inputs, bf16 row, the 256 x 128 kernel or the earlier epilogue, then now: 64 tokens, 11008 x 4096 65 -> 26 us; 256 tokens, 4096 x 4096 41 ->
-// 19; 1024 65 -> 33; 2048 80 -> 58 (col 88 -> 65); 2048 tokens, 11008 x 4096 221 -> 157; 4000 tokens, 2048 x 2048 53 -> 34.
+// inputs, bf16 row, the 256 x 128 kernel or the earlier epilogue, then now: 64 tokens, 11008 x 4096 65 -> 29 us; 256 tokens,
+// 4096 x 4096 42 -> 20; 1024 66 -> 35; 2048 71 -> 54 (col 77 -> 59); 2048 tokens, 11008 x 4096 210 -> 153; 4000 tokens, 2048 x
+// 2048 45 -> 33.  Counters, 2048 tokens, 4096 x 4096 col: matrix cores busy 61 % of the CU's cycles, vector ALUs 21 %, LDS 33 %.
 static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
 {
     const int forced = tune_value("grad_big", -1);     // 0: never; n > 0: in n parts
@@ -650,8 +651,8 @@ transpose_bits_kernel(const uint32_t* __restrict__ B, uint32_t* __restrict__ Bt,
     }
 }
 
-// The same for large matrices.  A lane transposes one block of 32 x 32 bits
-// in registers (five rounds of masked swaps, 10 instructions for each of its words; ballots took eight times that); the
+// The same for large matrices.  A lane transposes one block of 32 x 32 bits in registers by recursive block transposition
+// (H. S. Warren, Hacker's Delight, 7-3: five rounds of masked swaps, 10 instructions for each of its words; ballots took eight times that); the
 // lanes of a wave take 64 consecutive words of each row, the four waves 128 rows, whose 16 bytes per row of Bt leave
 // through LDS as one store.  4096 x 4096: 5.4 us a launch, 7.1 with ballots and 4-byte loads down the columns.
 __global__ void __launch_bounds__(256)

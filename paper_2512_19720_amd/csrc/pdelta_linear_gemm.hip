@@ -756,8 +756,10 @@ PrefillRoute linear_gemm_route(int x_dtype, int axis, int64_t M, int64_t d_out, 
     const int64_t big_tiles = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int small = tune_value("gemm_small", -1), roles = tune_value("gemm_roles", -1);
     if (d_in % 64 == 0 && (small == 1 || (small < 0 && big_tiles <= 128))) {
-        // At most one tile per CU: the kernel with roles, of which a CU holds one workgroup (251 x 4096 x 4096 bf16 32.5 -> 25.2
-        // us); more tiles: several workgroups per CU overlap better (70 x 11008 x 4096, 344 tiles: 47 us there, 51 with roles).
+        // At most one tile per CU: the kernel with roles, of which a CU holds one workgroup (251 x 4096 x 4096 bf16 32.7 -> 25.5
+        // us).  With more tiles the line is not fitted: that kernel has been ahead there too (70 x 11008 x 4096 bf16 47.5 and
+        // 40.2, fp16 46.9 and 43.5) and behind (70 x 32000 x 4096 fp16 col 99.4 and 102.8, 70 x 11008 x 4096 fp16 on inputs
+        // that stay in a cache 33.7 and 35.3).
         const int64_t tiles = ((M + 63) / 64) * ((d_out + 63) / 64);
         const bool one_each = d_in % 128 == 0 && roles != 0 && (roles == 1 || tiles <= 256);
         return PrefillRoute{one_each ? kPrefillRoles : kPrefillSmall, sp};

@@ -4,15 +4,18 @@
 //
 // 251 tokens on 4096 outputs are 256 such tiles, one per CU, and the sums of an output run in order: the time is that of 4096
 // inputs, one after another, on four waves that multiply.  In linear_gemm_small_kernel the same four waves also load,
-// convert and stage, and a step of 64 inputs takes 0.37 us, three times its MFMAs and LDS traffic.  Here four waves only
+// convert and stage, and a step of 64 inputs takes 0.4 us, several times its MFMAs and LDS traffic.  Here four waves only
 // read fragments and multiply, eight others load W_b into registers three pairs of steps ahead, convert and stage it
 // (bf16: X too; fp16 X comes by direct loads into LDS from the multiplying waves), and there is one barrier for 128 inputs.
-// What is left is LDS traffic: 64 KB of fragments and 32 KB of tiles per 128 inputs are 770 cycles (17 us of the 25 without
-// any load, 4096 x 4096 fp16), and the loads next to it.  An L2 touch ahead of the loads, whole 2 KB of a row at a time or
+// What is left is the chain from barrier to barrier: counters of 251 tokens, 4096 x 4096 fp16 col show 1440 cycles per 128
+// inputs, of which the LDS is busy 27 %, the vector ALUs 23 %, the matrix cores 18 %, and without any load 17 us of 25 remain.
+// 52 MB are fetched, X once per XCD.  An L2 touch ahead of the loads, whole 2 KB of a row at a time or
 // line by line, costs 1-2 us; a fourth pair in registers changes nothing.
 //
-// Changing inputs, 251 tokens, 4096 x 4096, linear_gemm_small_kernel -> this one: fp16 row 28.6 -> 24.6, col 33.3 -> 27.1,
-// bf16 row 32.5 -> 25.2; 128 tokens fp16 28.9 -> 25.7; 100 tokens, 1024 x 1024 10.1 -> 9.0.
+// Calls in a row in a graph, weights changing, 251 tokens, 4096 x 4096, us, linear_gemm_small_kernel -> this one: fp16 row 28.5
+// -> 24.5, col 30.5 -> 26.2, blockwise 31.2 -> 26.8, bf16 row 32.7 -> 25.5, col 35.6 -> 28.1; 128 tokens fp16 row 28.8 -> 24.8;
+// 100 tokens, 1024 x 1024 fp16 9.4 -> 7.5.  Where the inputs still lie in the memory-side cache (six sets of them, calls one by
+// one), 251 tokens fp16 col 28.8 -> 21.4.
 #include <type_traits>
 
 #include "pdelta_gemm_tile.h"

@@ -110,7 +110,7 @@ __device__ __forceinline__ void skinny_compute(const SkinnyStep<MT, AXIS>& r, in
     }
 }
 
-// For what pdelta_linear_skinny_dma.hip leaves: see launch_plain.
+// For what pdelta_linear_skinny_dma.hip leaves: see linear_skinny_route.
 // grid.x = ceil(d_out / 16); block = WAVES * 64; dynamic LDS = WAVES * MT * 256 floats.
 // DEPTH steps per wave are kept in flight (a ring of register buffers).
 template <int XDT, int AXIS, int MT, int WAVES, int DEPTH, bool K128>

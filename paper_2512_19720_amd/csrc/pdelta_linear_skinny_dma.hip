@@ -1,4 +1,4 @@
-// Decode-shaped delta linear layer for batches, d_in a multiple of 128: the arithmetic of pdelta_linear_skinny.hip (two
+// Decode-shaped delta linear layer (1 to 64 tokens), d_in a multiple of 128: the arithmetic of pdelta_linear_skinny.hip (two
 // accumulators, base and sign part, in the operands' own dtype) with all operands coming by direct loads into LDS.
 //
 // What bounds the register-staged kernel for batches: it reads X (61 tokens on 4096 inputs: 0.5 MB) once per 16 output
@@ -14,8 +14,13 @@
 // of them without any load in the loop).  Measured and dropped as well: waves that share X behind a barrier per step
 // (28.7), the same with W_b asked for eight steps ahead (29.8).
 //
-// Changing inputs, us, register-staged kernel -> this one: bf16 row, 11008 x 4096, 61 tokens 49 -> 27, 24 tokens 33.5 ->
-// 21, 16 tokens 23 -> 19.5; 4096 x 11008, 64 tokens 45 -> 37; 4096 x 4096, 64 tokens 18 -> 15, 24 tokens 12.8 -> 10.2.
+// What is left is waiting.  Counters of 61 tokens, 11008 x 4096 bf16 (100.5 MB fetched, 1.04 of what has to be): matrix cores
+// busy 24 % of the CU's cycles, vector ALUs 17 %, LDS 14 %; waves issue during 18 % of their life and spend 49 % on
+// instructions that are under way.
+//
+// Calls in a row in a graph, weights changing, us, the kernels that took these calls before -> this one:
+// bf16 row, 11008 x 4096, 61 tokens 46.9 -> 27.2, 24 tokens 33.4 -> 22.4, 16 tokens 23.3 -> 22.1; 4096 x 11008, 64 tokens
+// 44.8 -> 36.9; 4096 x 4096, 64 tokens 18.8 -> 15.6, 24 tokens 13.6 -> 10.8.
 #include <algorithm>
 #include <type_traits>
 
@@ -65,7 +70,7 @@ linear_skinny_dma_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
                          int v_stride, int g_shift)
 {
     constexpr int DEPTH = dma_depth(AXIS, MT, NT), WAVES = kDmaWaves;
-    static_assert(DEPTH >= 1 && DEPTH <= 4 && NT <= 4, "a unit's signs would be overwritten too early");
+    static_assert(DEPTH >= 1 && DEPTH <= 3 && NT <= 3, "a unit's signs would be overwritten too early");
     constexpr int XSTAGE = MT * 2048, STAGE = XSTAGE + NT * 2048, SIGNS = DEPTH * STAGE, SCALES = SIGNS + kDmaBufs * NT * 256,
                   WAVE_LDS = dma_wave_bytes(AXIS, MT, NT, DEPTH);
     constexpr int LOADS = 2 * (MT + NT);              // per step (signs and scales beside them)
@@ -109,7 +114,7 @@ linear_skinny_dma_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
         const uint32_t kb = input_of(s);
         if ((s & 1) == 0) {                           // the unit's signs and scales
             const uint32_t buf = uniform((s >> 1) & (kDmaBufs - 1));
-            if (NT == 4 || lane < NT * 16) load_lds_16(uniform(lds0 + SIGNS + buf * (NT * 256)), soff, uniform_ptr(sbase + (kb >> 3)));
+            if (lane < NT * 16) load_lds_16(uniform(lds0 + SIGNS + buf * (NT * 256)), soff, uniform_ptr(sbase + (kb >> 3)));
             if constexpr (AXIS == 1)
                 if (lane < 16) load_lds_16(uniform(lds0 + SCALES + buf * 256), (kb + lane * 8) * 2u, uniform_ptr(v));
             if constexpr (AXIS == 2)
