@@ -365,7 +365,9 @@ static int launch_big(const void* X, const void* W_b, const uint32_t* B_packed, 
 // steps, a split 8 more for its second launch and 0.06 per part for the sums that it writes and reads;
 // the 256 x 128 kernel takes 1.0 / 1.08 a step and 15 a call, the 64 x 64 kernels 3 a call and 0.29 / 0.31 a step, 0.05
 // more with column or blockwise scales (128 x 3072 x 8192 fp16: 44, 48 and 51 there, 42-44 here in 16 parts) and 0.045 more
-// when every CU has a tile, above one tile per CU 0.34 for each.  Against the latter a split pays 0.1 more per part: it
+// when every CU has a tile; above one tile per CU 0.3 for each of the tiles of the busiest CU and 0.15 for what they are
+// together, 0.05-0.15 more with other scales or bf16 (of 1640 calls within 1 % of the best choice on average; a price that
+// grows with the tiles alone left 140 x 6656 x 8192 bf16, 312 tiles, there: 90, here 62 in 8 parts).  Against the 64 x 64 kernels a split pays 0.1 more per part: it
 // has few tiles there, and a wave of the second launch reads the parts of its outputs one after another.  bf16, changing
 // inputs, this kernel against the others: 2048 x 11008 x 4096 (88 of 344 tiles in 2 parts) 223-230 against 230-237, 777 x
 // 4096 x 11008 blockwise (64 tiles in 4 parts) 127 against 254, 1024 x 4096 x 4096 60 against 87, 256 x 512 x 8192 (2 tiles
@@ -394,9 +396,11 @@ BigSplit linear_gemm_big_split(int64_t M, int64_t d_out, int64_t d_in, int x_dty
     const int64_t tiles128 = ((M + 255) / 256) * ((d_out + kGemmBN - 1) / kGemmBN);
     const int64_t tiles64 = ((M + 63) / 64) * ((d_out + 63) / 64);
     if (tiles128 <= 128) {
-        const double row = x_dtype == kBF16 ? 0.31 : 0.29;
-        const double small = tiles64 <= 256 ? 3 + n * ((axis == 0 ? row : row + 0.05) + 0.045 * (double)tiles64 / 256)
-                                            : 3 + n * 0.34 * (double)tiles64 / 256;
+        const bool bf16 = x_dtype == kBF16;
+        const double row = bf16 ? 0.31 : 0.29, each = (double)tiles64 / 256, most = std::ceil(each);
+        const double over = axis == 0 ? (bf16 ? 0.05 : 0) : axis == 1 ? (bf16 ? 0.12 : 0.05) : (bf16 ? 0.15 : 0.1);
+        const double small = 3 + n * (tiles64 <= 256 ? (axis == 0 ? row : row + 0.05) + 0.045 * each
+                                                     : 0.3 * most + 0.15 * (each - (most - 1)) + over);
         return best + (sp.split > 0 ? 0.1 * sp.parts : 0) < small ? sp : none;
     }
     const double pipe = 15 + n * (double)((tiles128 + 255) / 256) * (x_dtype == kBF16 ? 1.08 : 1.0);

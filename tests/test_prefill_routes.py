@@ -33,6 +33,15 @@ def test_other_kernels(M, d_out, d_in, kernel):
         assert route(M, d_out, d_in, axis) == kernel, axis
 
 
+# more than one 64 x 64 tile per CU: the busiest CU's tiles count, not the tiles by 256 (312 and 405 tiles cost two whole ones)
+@pytest.mark.parametrize("M,d_out,d_in,dtype,kernel", [
+    (140, 6656, 8192, pd.BF16, 1008), (107, 8588, 15360, pd.F16, 1007), (488, 2104, 6656, pd.BF16, 1013), (196, 4384, 7936, pd.F16, 1013),
+    (1117, 1024, 7808, pd.BF16, 1011), (284, 3328, 11264, pd.F16, 1009), (643, 1536, 7552, pd.F16, 1012), (65, 16320, 1024, pd.F16, 64)])
+def test_more_tiles_than_cus(M, d_out, d_in, dtype, kernel):
+    for axis in (ROW, COL, GROUP):
+        assert route(M, d_out, d_in, axis, dtype) == kernel, axis
+
+
 def test_argument_errors():
     probe = pd.lib().pdelta_probe_prefill_kernel
     assert probe(0, 64, 64, pd.F16, ROW, 0) == pd.EINVAL and probe(65, 64, 64, pd.F16, 3, 0) == pd.EINVAL and probe(65, 64, 64, pd.F16, ROW, 2) == pd.EINVAL
