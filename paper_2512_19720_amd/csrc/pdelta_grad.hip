@@ -730,7 +730,11 @@ int launch_grad_v(int dtype, int axis, const void* X, const void* dY, const uint
         uint32_t* Bt = (uint32_t*)((char*)workspace + off);
         // Above 2^23 signs by blocks in registers, whose few waves each take longer (col gradient of 256 tokens, ballots /
         // blocks: 1024 x 1024 13.9 / 15.0 us, 2048 x 4096 18.7 / 18.9, 4096 x 4096 25.7 / 24.7, 4096 x 11008 41.5 / 34.6).
-        if (d_out * d_in > (int64_t)1 << 23) {
+        // Rows of Bt that are not a multiple of 16 bytes leave word by word: then from 2^24 on (one token, 672 x 14336
+        // 21.0 / 23.4), and not where a quarter of the words that the workgroups take are beyond the row (25440 x 2464: 4 us
+        // slower with blocks).
+        const int64_t words = d_in / 32, signs = d_out * d_in;
+        if (d_out % 128 == 0 ? signs > (int64_t)1 << 23 : signs >= (int64_t)1 << 24 && 4 * words >= 3 * ((words + 63) / 64 * 64)) {
             const dim3 grid((unsigned)((d_in / 32 + 63) / 64), (unsigned)((d_out + 127) / 128));
             hipLaunchKernelGGL(transpose_bits_blocks_kernel, grid, dim3(256), 0, stream, B_packed, Bt, (int)d_out, (int)d_in);
         } else {

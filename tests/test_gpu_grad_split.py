@@ -24,10 +24,10 @@ def test_whole_and_split_contraction(M, d_out, d_in, dtype, axis, parts, monkeyp
     check_grad(got, ref, f"grad big M={M} {d_out}x{d_in} dt={dtype} axis={axis} parts={parts}")
 
 
-# the transposition of the signs, by ballots and (above 2^23 signs) at the edges of its 128 x 2048 tiles (d_out % 128 != 0:
+# the transposition of the signs, by ballots and (above 2^23 signs, from 2^24 on with d_out % 128 != 0) at the edges of its 128 x 2048 tiles (d_out % 128 != 0:
 # rows of the result that are not 16-byte aligned), and sums over many partial rows (9 token tiles in 5 parts; 64 x 9 outputs of a reduction block)
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,d_out,d_in", [(2, 4096, 2080), (1, 2080, 4128), (2, 128, 2048), (5, 288, 64), (2304, 640, 576)])
+@pytest.mark.parametrize("M,d_out,d_in", [(2, 4096, 2080), (1, 2080, 4128), (2, 128, 2048), (5, 288, 64), (2304, 640, 576), (2, 4160, 4064), (1, 2080, 8160)])
 @pytest.mark.parametrize("axis", [orc.ROW, orc.COL])
 def test_transposed_signs_and_many_partial_rows(M, d_out, d_in, axis):
     X, dY, B = make(M, d_out, d_in, synth.BF16, 5 * M + d_out + d_in)
