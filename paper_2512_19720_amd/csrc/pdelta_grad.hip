@@ -571,7 +571,8 @@ grad_big_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, 
 
 // Parts of the contraction for the 256 x 256 kernel, or 0 for the 256 x 128 kernel, which is taken where the
 // contraction is not a multiple of 128, the caller's workspace has no room for the parts, or a few tokens meet one or two
-// units (one token, 512 x 256 row 9.5 us and 10.9 here; 64: 13.8 and 10.9).  A round of up to 256
+// units (one token, 512 x 256 row 9.5 us and 10.9 here; 64: 13.8 and 10.9) or up to five and so many tiles that two parts
+// are the most (one token, 22784 x 384 row 12.1 and 14.1, eight, 21888 x 640 15.9 and 17.1; 1152 inputs 21.6 and 22.0).  A round of up to 256
 // workgroups takes 4 us and 1.12 us per step of 64 inputs (1.44 when all CUs multiply and the clock falls); a part more
 // is one more row of partial sums for the second launch.  Up to 16 parts for at most 128 workgroups (one token, 8192 x 1024
 // col 24.9 us, 33.5 with eight; 2048 x 8192 row 20.8 and 29.4), else up to eight.  Changing
@@ -585,7 +586,7 @@ static int grad_big_parts(int64_t M, int64_t Nc, int64_t Kc)
     const int64_t m_tiles = (M + kGbTile - 1) / kGbTile, tiles = m_tiles * ((Nc + kGbTile - 1) / kGbTile), units = Kc / kGbUnitK;
     if (tiles > (1 << 24)) return 0;
     if (forced > 0) return (int)std::min<int64_t>(forced, units);
-    if (units <= 2 && M <= 16) return 0;
+    if (M <= 16 && (units <= 2 || (units <= 5 && tiles > 256 / 3))) return 0;
     const int64_t most = std::max<int64_t>(8, std::min<int64_t>(16, 128 / tiles));
     double best = 0;
     int parts = 0;

@@ -73,10 +73,12 @@ def test_cases_of_the_least_workspace_would_run_in_parts():
 
 def test_parts_of_few_tiles():
     """One to sixteen tokens, where the epilogue is short: sixteen parts for at most 128 workgroups, and the 256 x 128 kernel
-    (no parts) for one or two units of the contraction."""
+    (no parts) for one or two units of the contraction, and for three to five where there is room for two parts only."""
     L = pd.lib()
     for M, d_out, d_in, axis, parts in ((1, 1024, 4096, pd.ROW, 16), (16, 8192, 1024, pd.COL, 16), (1, 2048, 8192, pd.ROW, 16), (1, 2560, 2560, pd.ROW, 10),
                                         (1, 3072, 8192, pd.ROW, 10), (16, 4096, 4096, pd.ROW, 8), (1, 512, 256, pd.ROW, 1), (16, 256, 512, pd.COL, 1),
-                                        (17, 512, 256, pd.ROW, 2), (1, 512, 384, pd.ROW, 3)):
+                                        (17, 512, 256, pd.ROW, 2), (1, 512, 384, pd.ROW, 3),
+                                        (1, 22784, 384, pd.ROW, 1), (16, 21888, 640, pd.ROW, 1), (17, 22784, 384, pd.ROW, 2), (16, 21760, 384, pd.ROW, 3),
+                                        (16, 22784, 768, pd.ROW, 2)):
         n, signs = (d_out, 0) if axis == pd.ROW else (d_in, d_in * d_out // 8)
         assert L.pdelta_grad_v_split_workspace_bytes(M, d_out, d_in, axis) == parts * n * 4 + signs, (M, d_out, d_in, axis)
