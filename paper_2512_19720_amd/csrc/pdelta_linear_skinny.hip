@@ -589,6 +589,9 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
     if (d_in % 128 != 0 || forced == 0) return DecodeRoute{kDecodeRegisters, 1};
     if (staged > 0 && staged_layer_bytes(x_dtype, axis, M, d_in, g_shift) != 0) return DecodeRoute{kDecodeStaged, 1};
     if (forced > 0) return DecodeRoute{kDecodeDirect, std::min(forced, 3)};
+    // One round and one to three units for eight waves (up to 16 tokens; one or two above): row scales 3-5 % (1152 x 256,
+    // one token 2.15 and 2.22), column and blockwise scales up to 16 tokens 2-5 %, 64 tokens 1536 x 256 3.3 and 3.6.
+    if (d_out <= 256 * 16 && d_in <= (M <= 16 ? 384 : 256)) return DecodeRoute{kDecodeRegisters, 1};
     const int mt = (int)((M + 15) / 16);
     // Row tiles per workgroup: the least rounds of 256 workgroups times what a round weighs, 8, 13, 20 for one token tile
     // (4096 inputs, 16 tokens: 9.0, 12.2, 12.6 us in one round; 18432 x 1024: 13.9, 10.1, 11.0 in five, three, two) and
@@ -615,15 +618,21 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
 }
 
 // The register kernel.  Two steps in flight per wave, except row mode above 8 tokens, where one is 3-4 % faster (the X
-// loads double the bytes in flight per step), and above 32 tokens (registers).
+// loads double the bytes in flight per step), and above 32 tokens (registers).  Widths that are a multiple of 128 have
+// instances without the guards of the last step (64 tokens, 1536 x 256 3.5 -> 3.3 us).
 template <int XDT, int AXIS>
 static int launch_registers(const void* X, const void* W_b, const uint32_t* B_packed, const uint16_t* v, void* Y, int64_t M,
                             int64_t d_out, int64_t d_in, int y_dtype, int v_stride, int g_shift, hipStream_t stream)
 {
 #define PDELTA_GO(MT, DEPTH, K128) \
     return launch_one<XDT, AXIS, MT, 8, DEPTH, K128>(X, W_b, B_packed, v, Y, M, d_out, d_in, y_dtype, stream, v_stride, g_shift)
-    if (AXIS == 0 && M <= 8 && d_in % 128 == 0) PDELTA_GO(1, 2, true);
-    if (AXIS == 0 && M <= 16 && d_in % 128 == 0) PDELTA_GO(1, 1, true);
+    if (d_in % 128 == 0) {
+        if (AXIS == 0 && M > 8 && M <= 16) PDELTA_GO(1, 1, true);
+        if (M <= 16) PDELTA_GO(1, 2, true);
+        if (M <= 32) PDELTA_GO(2, 2, true);
+        if (M <= 48) PDELTA_GO(3, 1, true);
+        PDELTA_GO(4, 1, true);
+    }
     if (AXIS == 0 && M > 8 && M <= 16) PDELTA_GO(1, 1, false);
     if (M <= 16) PDELTA_GO(1, 2, false);
     if (M <= 32) PDELTA_GO(2, 2, false);

@@ -22,6 +22,13 @@ def test_row_scales(M, d_out, d_in, kernel):
         assert route(M, d_out, d_in, ROW, dtype) == kernel
 
 
+# few inputs: one round of workgroups with up to three units, any scales
+@pytest.mark.parametrize("M,d_out,d_in,kernel", [
+    (1, 1152, 256, 0), (16, 4096, 384, 0), (16, 4096, 512, 1), (17, 4096, 256, 0), (17, 4096, 384, 1), (64, 1536, 128, 0), (64, 4112, 128, 2)])
+def test_few_inputs(M, d_out, d_in, kernel):
+    assert [route(M, d_out, d_in, axis, dtype) for axis in (ROW, COL, GROUP) for dtype in (pd.F16, pd.BF16)] == 6 * [kernel]
+
+
 # column scales: one to three tokens on rows of 8 KB, one bf16 token on rows of 4 KB, two tiles that do not meet at one channel
 @pytest.mark.parametrize("M,d_out,d_in,dtype,kernel", [
     (3, 8192, 4096, pd.BF16, 8), (3, 14336, 4096, pd.F16, 8), (3, 32000, 4096, pd.BF16, 8), (2, 8192, 4096, pd.F16, 8), (1, 14336, 2048, pd.BF16, 8),
