@@ -545,14 +545,20 @@ static bool registers_pay(int64_t M, int64_t d_out, int64_t d_in, int rows, int6
 {
     if (d_out <= 256 * 16) return false;              // one round (4096 x 4096, one token: 8.7 and 8.2)
     if (M <= 4) return true;                          // 8192 x 4096 14.1 and 15.3, 14336 x 2048 13.4 and 14.4, 11008 x 4096 18.9 and 19.5
-    const bool thin = rounds > 2 && rounds * rows * 4096 * 8 > d_out * 9;      // a ninth or more of the last round is empty
-    // some waves have no unit: 10240 x 512, 12 tokens 4.7 and 5.3, 18432 x 512 6.8 and 7.5; 14336 x 512 6.3 and 5.6
-    if (d_in < 1024 && (d_out <= 8192 || (M > 8 && (d_out <= 12288 || thin)))) return true;
+    const bool thin = rounds > 2 && rounds * rows * 4096 * 8 > d_out * 9;      // a ninth or more of the rounds is empty
+    // some waves have no unit: 10240 x 512, 12 tokens 4.7 and 5.3, 18432 x 512 6.8 and 7.5; 14336 x 512 6.3 and 5.6, 21760 x 896,
+    // sixteen, 12.2 and 10.8; 22784 x 256, sixteen, 6.2 and 6.8
+    if (d_in < 1024 && d_out <= 8192) return true;
+    if (d_in < 768 && M > 8 && (d_out <= 12288 || thin || (d_in < 512 && d_out > 16384))) return true;
+    // one wave has two units, seven one: 7680 x 1152, six tokens 6.1 and 6.5
+    if (M <= 8 && d_in == 1152 && d_out <= 8192) return true;
+    // 17408 x 2688, six tokens 21.3 and 22.1, 20224 x 4352 35.2 and 37.8, 17664 x 9216 67.0 and 71.7; 20736 x 1024, eight 12.6 and 11.2
+    if (M <= 8 && rows == 2 && thin && d_in > 1024) return true;
     // 12288 x 4096, eight tokens 21.0 and 23.1, 16384 x 2048 15.3 and 16.4, 32000 x 4096 50.7 and 56.4; six, 6144 x 4096 13.1 and
     // 13.7, 10240 x 6144 29.8 and 31.6; 9216 x 4096 even, 10240 x 8192, eight, 40.2 and 38.3
     if (M <= 8 && d_in % 2048 == 0 && (d_out > (d_in % 4096 == 0 ? 10240 : 9216) || (d_out > (d_in % 4096 == 0 ? 5120 : 7168) && d_out <= 8192)))
         return true;
-    if (M <= 8 && rows == 3 && d_out > 11264 && d_in >= 6144) return true;     // 12288 x 11008, six 59.4 and 62.7
+    if (M <= 8 && rows == 3 && d_out > 256 * 47 && d_in >= 6144) return true;  // 12288 x 11008, six 59.4 and 62.7; 11492 x 7168, eight 37.6 and 32.6
     // 12288 x 4096, ten tokens 22.1 and 23.2, 32000 x 4096 52.5 and 55-57, 18432 x 6144 52.4 and 55.6; 11008 x 4096 21.6 and 21.1
     if (M <= 12 && d_out > 11264 && (d_in % 4096 == 0 || (d_in % 2048 == 0 && thin))) return true;
     return d_in % 4096 == 0 && rows == 1;             // 8192 x 4096, twelve 16.1 and 16.9, 28672 x 8192, sixteen 100 and 99.6-102
@@ -612,8 +618,9 @@ DecodeRoute linear_skinny_route(int x_dtype, int axis, int64_t M, int64_t d_out,
     if (mt > 1) return DecodeRoute{kDecodeDirect, rows};
     if (axis == 0) return registers_pay(M, d_out, d_in, rows, rounds) ? DecodeRoute{kDecodeRegisters, 1} : DecodeRoute{kDecodeDirect, rows};
     if (staged != 0 && staged_pays(x_dtype, axis, M, d_out, d_in, g_shift, rows, rounds)) return DecodeRoute{kDecodeStaged, 1};
-    // Few tokens on long rows that fill their rounds: 12288 x 11008 blockwise, one token 59.0 with one tile, 64.0 with three
-    if (M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288))) rows = 1;
+    // Few tokens on long rows that fill their rounds: 12288 x 11008 blockwise, one token 59.0 with one tile, 64.0 with three.
+    // With column scales rows of 4 KB multiples only (23232 x 9216, eight tokens 87.7, and 80.4 with two).
+    if (M <= 8 && d_in > 8192 && (d_out > 14336 || (d_out > 11264 && d_out <= 12288)) && (axis == 2 || d_in % 2048 == 0)) rows = 1;
     return DecodeRoute{kDecodeDirect, rows};
 }
 

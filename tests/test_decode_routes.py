@@ -29,12 +29,20 @@ def test_few_inputs(M, d_out, d_in, kernel):
     assert [route(M, d_out, d_in, axis, dtype) for axis in (ROW, COL, GROUP) for dtype in (pd.F16, pd.BF16)] == 6 * [kernel]
 
 
+# row scales, rounds of workgroups that come out badly, and waves without a unit (other scales: the kernel with direct loads)
+@pytest.mark.parametrize("M,d_out,d_in,row,other", [
+    (16, 22784, 256, 0, 2), (16, 21760, 896, 2, 2), (12, 8605, 896, 3, 3), (8, 8192, 896, 0, 2), (6, 7680, 1152, 0, 2), (6, 7680, 1280, 2, 2),
+    (6, 17408, 2688, 0, 2), (6, 20224, 4352, 0, 2), (8, 20736, 1024, 2, 2), (8, 11492, 7168, 3, 3), (5, 11904, 6784, 3, 3)])
+def test_thin_rounds(M, d_out, d_in, row, other):
+    assert [route(M, d_out, d_in, axis) for axis in (ROW, COL, GROUP)] == [row, other, other]
+
+
 # column scales: one to three tokens on rows of 8 KB, one bf16 token on rows of 4 KB, two tiles that do not meet at one channel
 @pytest.mark.parametrize("M,d_out,d_in,dtype,kernel", [
     (3, 8192, 4096, pd.BF16, 8), (3, 14336, 4096, pd.F16, 8), (3, 32000, 4096, pd.BF16, 8), (2, 8192, 4096, pd.F16, 8), (1, 14336, 2048, pd.BF16, 8),
     (1, 4096, 2048, pd.BF16, 8), (1, 2048, 2048, pd.BF16, 8), (1, 1024, 2048, pd.BF16, 1), (1, 4096, 2048, pd.F16, 1), (1, 2048, 4096, pd.BF16, 1),
     (3, 11008, 4096, pd.BF16, 3), (4, 8192, 4096, pd.BF16, 1), (4, 6144, 4096, pd.BF16, 2), (3, 8192, 6144, pd.BF16, 2), (3, 14336, 2048, pd.BF16, 2),
-    (6, 20480, 4096, pd.BF16, 3), (6, 20480, 4096, pd.F16, 1), (2, 8192, 8192, pd.BF16, 1)])
+    (6, 20480, 4096, pd.BF16, 3), (6, 20480, 4096, pd.F16, 1), (2, 8192, 8192, pd.BF16, 1), (8, 23232, 9216, pd.F16, 2), (8, 14336, 10240, pd.BF16, 2)])
 def test_column_scales(M, d_out, d_in, dtype, kernel):
     assert route(M, d_out, d_in, COL, dtype) == kernel
 
