@@ -1,5 +1,7 @@
 """Which prefill kernel the library takes, on both sides of the lines that were measured (no GPU needed): 64 and 65 the 64 x
 64 tiles with a ring of steps and with roles, 128, 256 and 257 the 128 x 128 and 256 x 128 ones, 1000 + parts the 256 x 256 ones."""
+import random
+
 import pytest
 
 from paper_2512_19720_amd import binding as pd
@@ -40,6 +42,21 @@ def test_other_kernels(M, d_out, d_in, kernel):
 def test_more_tiles_than_cus(M, d_out, d_in, dtype, kernel):
     for axis in (ROW, COL, GROUP):
         assert route(M, d_out, d_in, axis, dtype) == kernel, axis
+
+
+def test_workspace_holds_the_parts_of_every_kind_of_scales():
+    """The size that callers ask for does not know the scales: whichever kinds split a call split it alike, and the size is
+    that of its parts (256 x 256 fp32 sums each) where any of them does."""
+    rng = random.Random(5)
+    for _ in range(4000):
+        M, d_out = (int(2 ** rng.uniform(lo, hi)) for lo, hi in ((6.03, 12.5), (5, 14.5)))
+        d_in, dtype = 128 * rng.randint(1, 120), rng.choice((pd.F16, pd.BF16))
+        kernels = [route(M, d_out, d_in, axis, dtype) for axis in (ROW, COL, GROUP)]
+        parts = {k - 1000 for k in kernels if k > 1001}
+        tiles = -(-M // 256) * -(-d_out // 256) % 256
+        assert len(parts) <= 1, (M, d_out, d_in, dtype, kernels)
+        need = pd.lib().pdelta_linear_workspace_bytes(M, d_out, d_in, dtype)
+        assert need == sum(parts) * tiles * 256 * 256 * 4 and need <= 64 << 20, (M, d_out, d_in, dtype, kernels)
 
 
 def test_argument_errors():
