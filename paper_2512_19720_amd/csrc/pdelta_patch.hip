@@ -141,15 +141,15 @@ __device__ __forceinline__ void patch_values(const PatchUnits<N>& S, uint4v (&ou
 // by u).  Units are counted from the start of row `row_base`: the passes that start at first_rel,
 // first_rel + stride, ... below last_rel, each clipped at last_rel.  A pass covers 1024
 // consecutive units: thread t takes units t, t + 256, t + 512, t + 768 of it, issues all its loads,
-// sums, stores.  Every weight is read once and written once, so both are marked as non-temporal (NT): a block of seven layers
-// bf16 151.6 -> 133.3 us (6.3 TB/s), 4096 x 4096 bf16 15.8 -> 13.6, 1024 x 4096 5.1 -> 4.8 (signs, of which a 128-byte line
-// serves four waves, are not: 134.8).  Measured on MI355X this plain shape (what a library elementwise kernel does)
+// sums, stores.  Every weight is read once and written once, so the stores of larger calls are marked as non-temporal
+// (STREAM 1), those of the largest and their loads (2): a block of seven layers
+// bf16 151.6 -> 133.3 us (6.3 TB/s; signs, of which a 128-byte line serves four waves, are not marked: 134.8).  Measured on MI355X this plain shape (what a library elementwise kernel does)
 // streams 5-8 % faster than walking rows with the next step's loads in flight, and equals the
 // box's in-place update rate.  Loads are unconditional (unit index clamped to last_rel - 1); only
 // stores are guarded.
 // AXIS 2: blockwise scales v[row * v_stride + (col >> g_shift)] (groups are multiples of 8 inputs,
 // so the eight weights of a unit share one scale).
-template <int DT, int AXIS, bool NT>
+template <int DT, int AXIS, int STREAM>
 __device__ __forceinline__ void
 patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint16_t* __restrict__ v,
             uint16_t* W_out, int d_in, int row_base, int first_rel, int last_rel, int stride, int v_stride = 0,
@@ -170,7 +170,7 @@ patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint
             const int r = rc / upr;
             const int col = (rc - r * upr) * 8;
             const int row = row_base + r;
-            S.w[j] = load_weights<NT>((const uint4v*)(w_base + (int64_t)rc * 8));
+            S.w[j] = load_weights<(STREAM > 1)>((const uint4v*)(w_base + (int64_t)rc * 8));
             S.byte[j] = b_base[rc];
             S.v16[j] = AXIS == 0   ? (uint32_t)v[row]
                        : AXIS == 2 ? (uint32_t)v[(int64_t)row * v_stride + (col >> g_shift)]
@@ -181,12 +181,12 @@ patch_units(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint
         patch_values<DT, AXIS, kPatchUnits>(S, out);
 #pragma unroll
         for (int j = 0; j < kPatchUnits; ++j)
-            if (rel[j] < last_rel) store_weights<NT>((uint4v*)(out_base + (int64_t)rel[j] * 8), out[j]);
+            if (rel[j] < last_rel) store_weights<(STREAM > 0)>((uint4v*)(out_base + (int64_t)rel[j] * 8), out[j]);
     }
 }
 
 // One layer: workgroup b patches units 1024 b .. 1024 b + 1023.
-template <int DT, int AXIS, bool NT>
+template <int DT, int AXIS, int STREAM>
 __global__ void __launch_bounds__(kPatchThreads)
 patch_kernel(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uint16_t* __restrict__ v,
              uint16_t* W_out, int d_in, int64_t total_units, int v_stride, int g_shift)
@@ -196,15 +196,15 @@ patch_kernel(const uint16_t* W_b, const uint8_t* __restrict__ B_bytes, const uin
     const int64_t last = min(first + kPatchChunk, total_units);
     const int row_base = (int)(first / upr);
     const int64_t unit0 = (int64_t)row_base * upr;
-    patch_units<DT, AXIS, NT>(W_b, B_bytes, v, W_out, d_in, row_base, (int)(first - unit0), (int)(last - unit0),
-                          kPatchChunk, v_stride, g_shift);
+    patch_units<DT, AXIS, STREAM>(W_b, B_bytes, v, W_out, d_in, row_base, (int)(first - unit0), (int)(last - unit0),
+                              kPatchChunk, v_stride, g_shift);
 }
 
 // Batched merge: the plan counts blocks of 16 rows; block b belongs to the last layer whose
 // first_block is <= b, and kPatchBatchParts workgroups share its units in equal contiguous parts
 // (at d_in = 4096 a part is exactly one pass; dealing the passes out round-robin instead was
 // measured slower, 5.15 against 5.33 TB/s on a 7B-shaped stack).  The layer's Y field is W_out.
-template <int DT, bool NT>
+template <int DT, int STREAM>
 __global__ void __launch_bounds__(kPatchThreads)
 patch_batch_kernel(const pdelta_layer* __restrict__ layers, int n_layers)
 {
@@ -224,8 +224,23 @@ patch_batch_kernel(const pdelta_layer* __restrict__ layers, int n_layers)
     uint16_t* W_out = as_global((uint16_t*)L.Y);
     const int per_part = (block_units + kPatchBatchParts - 1) / kPatchBatchParts;
     const int first = part * per_part, last = min(first + per_part, block_units);
-    if (L.axis == 0) patch_units<DT, 0, NT>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
-    else patch_units<DT, 1, NT>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
+    if (L.axis == 0) patch_units<DT, 0, STREAM>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
+    else patch_units<DT, 1, STREAM>(W_b, B_bytes, v, W_out, d_in, row0, first, last, kPatchChunk);
+}
+
+// What a call over this many weights marks as non-temporal: nothing below 16 MiB; from there on the stores; the loads too from
+// 64 MiB on, and in place, where the store would find the line that an ordinary load has left.  Out of place, stores alone are
+// faster whether the weights come out of memory or of the memory-side cache, loads only out of memory.  us without, with
+// stores, with both; three sets of inputs in turn (the cache holds them up to some 40 MiB), then out of memory:
+// 5120 x 1920 fp16 (19 MiB) 7.8, 7.3, 8.2 and 10.6, 8.8, 8.8; 2622 x 6656 fp16 col (33 MiB) 11.6, 11.5, 14.1 and 16.0, 14.8, 14.4;
+// 3685 x 3968 bf16 (28 MiB) 11.1, 10.6, 11.8 and 14.5, 12.5, 12.3; 13248 x 2560 bf16 col (65 MiB) 28.4, 22.0, 24.3 and 28.1, 25.6, 24.4;
+// 11 layers of 448 x 10496 (99 MiB) 46.4, 42.6, 41.4.  In place, out of memory: 2112 x 4096 9.7, 9.6, 8.0, 4096 x 4096 16.1, 15.8,
+// 12.9, 4096 x 7168 25.1, 24.6, 20.9.  A patched layer is then not in that cache: who reads it next waits for what patch
+// saved (4096 x 4096 and a linear of 16 tokens 19.5, 19.9, 22.3; 5120 x 5120 34.8, 34.7, 34.7; 11008 x 4096 52.6, 51.5 with both).
+static int streamed(int64_t weights, bool in_place)
+{
+    if (weights < (int64_t)8 << 20) return 0;
+    return in_place || weights >= (int64_t)32 << 20 ? 2 : 1;
 }
 
 // Returns 1 when the batch has too many blocks for one grid (the caller then patches layer by layer).
@@ -237,10 +252,15 @@ int launch_patch_batch(int w_dtype, const pdelta_layer* layers_host, const pdelt
     if (total * kPatchBatchParts > 0x7FFFFFFF) return 1;
     const dim3 grid((unsigned)(total * kPatchBatchParts));
     int64_t weights = 0;
-    for (int l = 0; l < n_layers; ++l) weights += layers_host[l].d_out * layers_host[l].d_in;
-    const bool nt = streams_weights(weights);
-    auto kernel = w_dtype == kBF16 ? (nt ? patch_batch_kernel<kBF16, true> : patch_batch_kernel<kBF16, false>)
-                                   : (nt ? patch_batch_kernel<kF16, true> : patch_batch_kernel<kF16, false>);
+    bool in_place = true;
+    for (int l = 0; l < n_layers; ++l) {
+        weights += layers_host[l].d_out * layers_host[l].d_in;
+        in_place = in_place && layers_host[l].Y == layers_host[l].W_b;
+    }
+    const int how = streamed(weights, in_place);
+    auto pick = [&](auto none, auto stores, auto both) { return how == 0 ? none : how == 1 ? stores : both; };
+    auto kernel = w_dtype == kBF16 ? pick(patch_batch_kernel<kBF16, 0>, patch_batch_kernel<kBF16, 1>, patch_batch_kernel<kBF16, 2>)
+                                   : pick(patch_batch_kernel<kF16, 0>, patch_batch_kernel<kF16, 1>, patch_batch_kernel<kF16, 2>);
     hipLaunchKernelGGL(kernel, grid, dim3(kPatchThreads), 0, stream, layers_device, n_layers);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -252,7 +272,8 @@ static int launch_patch(const void* W_b, const uint32_t* B_packed, const uint16_
     const int64_t total_units = d_out * (d_in / 8);
     const int64_t n_blocks = (total_units + kPatchChunk - 1) / kPatchChunk;
     if (n_blocks > 0x7FFFFFFF) return -1;             // 2^41 weights and more: not a layer
-    auto kernel = streams_weights(d_out * d_in) ? patch_kernel<DT, AXIS, true> : patch_kernel<DT, AXIS, false>;
+    const int how = streamed(d_out * d_in, W_out == W_b);
+    auto kernel = how == 0 ? patch_kernel<DT, AXIS, 0> : how == 1 ? patch_kernel<DT, AXIS, 1> : patch_kernel<DT, AXIS, 2>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(kPatchThreads), 0, stream,
                        (const uint16_t*)W_b, (const uint8_t*)B_packed, v, (uint16_t*)W_out, (int)d_in, total_units,
                        v_stride, g_shift);

@@ -124,6 +124,31 @@ def test_patch_matches_oracle_bit_for_bit(shape, dtype, axis):
     assert np.array_equal(synth.torch_to_bits(W_b), want)
 
 
+@pytest.mark.parametrize("d_out,d_in", [(2577, 3296), (4099, 8224)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_large_patches_have_the_bits_of_their_slices(d_out, d_in, dtype):
+    """From 8 Mi weights on stores are non-temporal, in place or from 32 Mi on loads too, single and batched: against patches of
+    slices of 512 rows, where nothing is (and which equal the oracle, above)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d_out + dtype)
+    W_b = (torch.randn((d_out, d_in), generator=g, device=DEV) * 0.02).to(torch.bfloat16 if dtype == synth.BF16 else torch.float16)
+    B = torch.randint(-2 ** 31, 2 ** 31, (d_out, d_in // 32), generator=g, device=DEV, dtype=torch.int64).to(torch.int32)
+    assert 512 * d_in < 8 << 20 <= d_out * d_in
+    slices = [slice(r, min(r + 512, d_out)) for r in range(0, d_out, 512)]
+    for axis, n in ((pd.ROW, d_out), (pd.COL, d_in)):
+        v = (torch.rand(n, generator=g, device=DEV) * 0.01).to(torch.float16)
+        want = torch.cat([pd.pdelta_patch(W_b[s], B[s], v[s] if axis == pd.ROW else v, axis) for s in slices]).view(torch.int16)
+        out = torch.full_like(W_b, float("nan"))
+        pd.pdelta_patch(W_b, B, v, axis, out=out)
+        assert torch.equal(out.view(torch.int16), want)
+        outs = pd.pdelta_patch_batch(pd.pdelta_patch_batch_plan([(W_b, B, v, axis), (W_b[:33], B[:33], v[:33].contiguous() if axis == pd.ROW else v, axis)]))
+        assert torch.equal(outs[0].view(torch.int16), want) and torch.equal(outs[1].view(torch.int16), want[:33])
+        single, batched = W_b.clone(), W_b.clone()
+        pd.pdelta_patch(single, B, v, axis, out=single)
+        pd.pdelta_patch_batch(pd.pdelta_patch_batch_plan([(batched, B, v, axis, batched)]))
+        assert torch.equal(single.view(torch.int16), want) and torch.equal(batched.view(torch.int16), want)
+
+
 def test_patch_rounding_cases_large_scales_and_negative_scales():
     # scales comparable to the weights, negative scales, subnormal weights: the single rounding
     # of the exact sum must still match
