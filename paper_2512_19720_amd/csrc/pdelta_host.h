@@ -9,12 +9,12 @@
 
 namespace pdelta {
 
-// Whether pack and patch read (and write) the weights of a call, this many in each matrix, as non-temporal: from 16 MiB on.
-// Seven layers of 704 x 640 packed at once (6 MiB, in the caches) take 17.6 us without and 19.2 with; two of 1024 x 4096
-// (16 MiB) 21.8 and 20.1; one of 2048 x 4096 patched (16 MiB) 8.7 and 7.8, and above it is 3 to 18 % everywhere.  A patched
-// layer is then not in the last-level cache: up to about 128 MiB who reads it next waits for what patch saved (8192 x 4096,
-// patch and one read of the result 36.8 without and 38.2 with, 4096 x 4096 21.0 and 21.5), above that both gain.
-inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)16 << 20; }
+// Whether pack reads the weights of a call, this many in each matrix, as non-temporal: from 48 MiB on, where two matrices and
+// what was there before no longer share the memory-side cache.  us with ordinary loads and with non-temporal ones, three sets of
+// inputs in turn: four layers of 1600 x 2176 (27 MiB) 18.7 and 21.4, nine of 1920 x 1280 (42 MiB) 30.8 and 32.1, 2752 x 5632 with one
+// scale (30 MiB) 17.2 and 18.0; 7552 x 4096 (59 MiB) 29.1 and 27.0, 10560 x 3968 (80 MiB) 38.5 and 37.0.  (The first three out of
+// memory: 24.4 and 22.0, 36.0 and 32.4, 20.4 and 18.0.)
+inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)48 << 20; }
 
 // Bytes of fp64 partial sums pdelta_pack writes for these dimensions.
 size_t pack_workspace_bytes(int64_t d_out, int64_t d_in);
