@@ -9,12 +9,12 @@
 
 namespace pdelta {
 
-// Whether pack reads the weights of a call, this many in each matrix, as non-temporal: from 48 MiB on, where two matrices and
+// Whether pack reads the weights of a call, this many in each matrix, as non-temporal: from 40 MiB on, where two matrices and
 // what was there before no longer share the memory-side cache.  us with ordinary loads and with non-temporal ones, three sets of
-// inputs in turn: four layers of 1600 x 2176 (27 MiB) 18.7 and 21.4, nine of 1920 x 1280 (42 MiB) 30.8 and 32.1, 2752 x 5632 with one
-// scale (30 MiB) 17.2 and 18.0; 7552 x 4096 (59 MiB) 29.1 and 27.0, 10560 x 3968 (80 MiB) 38.5 and 37.0.  (The first three out of
-// memory: 24.4 and 22.0, 36.0 and 32.4, 20.4 and 18.0.)
-inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)48 << 20; }
+// inputs in turn: four layers of 1600 x 2176 (27 MiB) 18.7 and 21.4, seven of 768 x 3968 (41 MiB) 23.4 and 24.0, 2752 x 5632 with one
+// scale (30 MiB) 17.2 and 18.0; six of 446 x 9216 (47 MiB) 27.0 and 24.8, 7552 x 4096 (59 MiB) 29.1 and 27.0, 10560 x 3968 (80 MiB)
+// 38.5 and 37.0.  Out of memory non-temporal loads gain at every size (the first three: 24.4 and 22.0, 28.6 and 24.6, 20.4 and 18.0).
+inline bool streams_weights(int64_t weights) { return weights * 2 >= (int64_t)40 << 20; }
 
 // Bytes of fp64 partial sums pdelta_pack writes for these dimensions.
 size_t pack_workspace_bytes(int64_t d_out, int64_t d_in);
