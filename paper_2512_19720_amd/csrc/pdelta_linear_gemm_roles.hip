@@ -36,6 +36,14 @@ struct RoleRegs {
     uint32_t sb[2], vg[2];
 };
 
+// Whether whole output-row tiles go to the XCDs in turn: while no XCD gets more tiles than its 32 CUs, of which each holds one
+// workgroup.  Above that the busiest XCD takes twice as long (1224 tokens x 628 x 256 fp16 col 9.5 us, 7.2 with consecutive tiles; 332
+// x 2634 x 768 bf16 10.1 and 7.5); below, fp16 calls are 1-4 % faster (94 x 1792 x 2560 row 12.6 and 13.1) and bf16 even.
+__host__ __device__ inline bool role_columns(int m_tiles, int n_tiles)
+{
+    return (int64_t)m_tiles * ((n_tiles + kXcds - 1) / kXcds) <= 256 / kXcds;
+}
+
 template <int XDT, int AXIS>
 __global__ void __launch_bounds__(kRoleThreads, 3)
 linear_gemm_roles_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W_b, const uint32_t* __restrict__ B_packed,
@@ -46,10 +54,11 @@ linear_gemm_roles_kernel(const uint16_t* __restrict__ X, const uint16_t* __restr
     constexpr int XST = XDMA ? kRoleXStages : 2, WBUF = XST * kRoleTile;
     extern __shared__ __attribute__((aligned(16))) unsigned char role_lds[];     // [XST] tiles of X, [2] of W_hat
 
-    // An XCD takes consecutive tiles, all token tiles of an output-row tile one after another, and no XCD takes more than its
-    // eighth: a CU holds one workgroup, so an XCD with more than 32 takes twice as long (whole output-row tiles in turn: 1224
-    // tokens x 628 x 256 9.5 us, 444 x 2233 x 256 9.6).
-    const int per_xcd = gridDim.x / kXcds, tile = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    // The XCDs take output-row tiles in turn, each with all its token tiles, or, where one would get more tiles than it has CUs,
+    // consecutive tiles, at most its eighth (see role_columns).
+    const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
+    const bool columns = role_columns(m_tiles, n_tiles);
+    const int tile = columns ? (local / m_tiles * kXcds + xcd) * m_tiles + local % m_tiles : xcd * per_xcd + local;
     if (tile >= m_tiles * n_tiles) return;            // whole workgroup
     const int tile_n = tile / m_tiles, tile_m = tile % m_tiles;
     const int n0 = tile_n * 64, m0 = tile_m * 64;
@@ -201,7 +210,8 @@ static int launch_roles(const void* X, const void* W_b, const uint32_t* B_packed
     auto kernel = linear_gemm_roles_kernel<XDT, AXIS>;
     static unsigned lds_opted_in = 0;                 // per template instance: one kernel
     if (opt_in_dynamic_lds((const void*)kernel, lds, &lds_opted_in) != 0) return -1;
-    const int m_tiles = (int)((M + 63) / 64), n_tiles = (int)((d_out + 63) / 64), per_xcd = (m_tiles * n_tiles + kXcds - 1) / kXcds;
+    const int m_tiles = (int)((M + 63) / 64), n_tiles = (int)((d_out + 63) / 64);
+    const int per_xcd = role_columns(m_tiles, n_tiles) ? (n_tiles + kXcds - 1) / kXcds * m_tiles : (m_tiles * n_tiles + kXcds - 1) / kXcds;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(kRoleThreads), lds, stream, (const uint16_t*)X,
                        (const uint16_t*)W_b, B_packed, v, Y, (int)M, (int)d_out, (int)d_in, y_dtype, m_tiles, n_tiles, v_stride, g_shift);
     return hipGetLastError() == hipSuccess ? 0 : -1;

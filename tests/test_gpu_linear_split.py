@@ -50,7 +50,7 @@ def test_whole_tiles_have_the_bits_of_the_other_kernels(M, d_out, d_in, dtype, m
 
 
 # the 64 x 64 kernel with roles: one pair of steps, as many as are held in registers and in LDS, one more, and many; tiles
-# cut in both directions; 35 and 200 tiles, which the eight XCDs share evenly but not by whole rows of tiles.  Bit for bit the 256 x 256 kernel's whole tiles
+# cut in both directions; 35 tiles, whole columns of them per XCD, and 200, of which that would give one XCD 40.  Bit for bit the 256 x 256 kernel's whole tiles
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
 @pytest.mark.parametrize("M,d_out,d_in", [(65, 63, 128), (66, 65, 256), (128, 64, 384), (97, 130, 512), (129, 72, 640), (70, 200, 4224), (444, 300, 256), (1224, 628, 128)])
